@@ -1685,6 +1685,8 @@ apt_status apt_cluster_ms(const apt_cloud* cloud, uint8_t species, float d_max, 
     la.lim2 = dm * dm;
     la.parent = parent;
     ClusterOutArgs oa{};
+    oa.plan = w.plan;
+    oa.tid = w.tid;
     oa.lab = cl.lab;
     oa.d_bnd = cloud->d_bnd;
     oa.d_srf = d_srf;
@@ -1699,10 +1701,13 @@ apt_status apt_cluster_ms(const apt_cloud* cloud, uint8_t species, float d_max, 
     oa.n_size_bins = size_hist ? n_size_bins : 0;
     {
         TraceSpan span("cluster", st);
-        hipLaunchKernelGGL(k_ms_init, dim3(g), dim3(kBlock), 0, st, parent, size, n);
+        // (the kernels over the species' ions alone: two workgroups per CU at
+        // most, whose merged counts are the atomics that remain)
+        const int gs = std::min(g, 2 * device_info().cus);
+        hipLaunchKernelGGL(k_ms_init, dim3(g), dim3(kBlock), 0, st, oa);
         hipLaunchKernelGGL(k_ms_link, dim3(resident_grid(k_ms_link, 0)), dim3(kBlock), 0, st, la);
         hipLaunchKernelGGL(k_ms_roots, dim3(g), dim3(kBlock), 0, st, oa);
-        hipLaunchKernelGGL(k_ms_final, dim3(g), dim3(kBlock), 0, st, oa);
+        hipLaunchKernelGGL(k_ms_final, dim3(gs), dim3(kBlock), 0, st, oa);
     }
     return hip_check("clustering launch");
 }

@@ -21,7 +21,11 @@ struct ClusterLinkArgs {
     uint32_t* parent;            // [n] forest over ion indices, parent[v] <= v
 };
 
+constexpr int kMsLdsSizes = 1024;   // cluster sizes counted in LDS before the global histogram
+
 struct ClusterOutArgs {
+    const GridPlan* plan;        // nT: ions of the species
+    const uint32_t* tid;         // [nT] their indices, ascending
     const uint8_t* lab;
     const float* d_bnd;          // may be NULL: no cluster is truncated
     float d_srf;                 // an ion with !(d_bnd >= d_srf) lies at the edge
@@ -36,7 +40,7 @@ struct ClusterOutArgs {
     int32_t n_size_bins;
 };
 
-__global__ void k_ms_init(uint32_t* parent, uint32_t* size, uint32_t n);
+__global__ void k_ms_init(ClusterOutArgs a);
 __global__ void k_ms_link(ClusterLinkArgs a);
 __global__ void k_ms_roots(ClusterOutArgs a);
 __global__ void k_ms_final(ClusterOutArgs a);

@@ -125,6 +125,23 @@ def test_edge_cases(gpu, orc, small_needle):
     assert len(gl) == 0 and (gc == 0).all() and gh.sum() == 0 and st == 0
 
 
+@pytest.mark.parametrize("n_size_bins", [1, 2, 1023, 1024, 1025, 4096])
+def test_size_histogram_around_its_lds_range(gpu, orc, n_size_bins):
+    """Chains of 1, 2, 1023, 1024, 1025 and 3000 ions: sizes on both sides of the 1024 counters kept in LDS."""
+    _say(f"case cluster size histogram n_size_bins={n_size_bins}")
+    rows = []
+    for q, m in enumerate([1] * 600 + [2] * 70 + [1023, 1024, 1024, 1025, 3000]):
+        c = np.zeros((m, 3), np.float32)
+        c[:, 0] = np.arange(m, dtype=np.float32) * np.float32(0.25)
+        c[:, 1], c[:, 2] = 2.0 * (q % 32), 2.0 * (q // 32)
+        rows.append(c)
+    xyz = np.concatenate(rows)
+    xyz = xyz[np.random.default_rng(3).permutation(len(xyz))]
+    lab = np.full(len(xyz), SC, np.uint8)
+    _, c = check(orc, gpu, xyz, lab, None, SC, 0.5, 3, n_size_bins=n_size_bins)
+    assert c[0] == 5
+
+
 def test_repeat_determinism(gpu, small_needle):
     xyz, lab, d = small_needle
     a = run_ms(gpu, xyz, lab, d, ANY, 0.3, 2, 1.0)
