@@ -425,10 +425,20 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     // chunks from the XCD's counter, so that the chunks in flight on an XCD
     // stay one compact region whose target rows its L2 keeps (a static deal
     // lets the wavefronts drift apart).  (workgroup b runs on XCD b mod 8)
+    // The batches are cut to leave every wavefront several of them, and a
+    // cloud with fewer chunks than that splits each chunk's targets into
+    // `split` items: 1e6 ions, every ion against every ion, are 15 600 chunks,
+    // which in batches of 16 kept 977 of 8192 wavefronts busy (the call 8.71 ms,
+    // now 2.01 ms).  2^32 - 1 neighbours are 6.7e7 items at most.
     const int xcd = blockIdx.x % kXcd;
     const uint32_t c0 = (uint32_t)((uint64_t)n_chunks * (uint64_t)xcd / kXcd);
-    const uint32_t c1 = (uint32_t)((uint64_t)n_chunks * (uint64_t)(xcd + 1) / kXcd);
-    constexpr uint32_t kBatch = 16;
+    const uint32_t n_own = (uint32_t)((uint64_t)n_chunks * (uint64_t)(xcd + 1) / kXcd) - c0;
+    const uint32_t n_waves = gridDim.x / kXcd * kWavesPerBlock;   // of this XCD
+    uint32_t lg_split = 0;
+    while (lg_split < 3 && ((uint64_t)n_own << lg_split) < 4ull * n_waves) ++lg_split;
+    const uint64_t n_items = (uint64_t)n_own << lg_split;
+    const uint32_t per_wave = (uint32_t)(n_items / (8ull * n_waves));
+    const uint32_t batch = per_wave < 1u ? 1u : per_wave > 16u ? 16u : per_wave;
     const float Re = a.r_enum + P.eps;
     const float R2 = Re * Re;
     const float thr2 = a.thr2, inv_w = a.inv_w, lo_b = a.delta_b, hi_b = 1.0f - a.delta_b;
@@ -437,12 +447,14 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     const uint32_t flush_at = 0xFFFFFFFFu - (uint32_t)(kWave * kNbrList);
 
     for (;;) {
-    uint32_t cb = 0;
-    if (l == 0) cb = atomicAdd(a.work_q + xcd, kBatch);
-    cb = c0 + (uint32_t)__shfl((int)cb, 0, kWave);
-    if (cb >= c1) break;
-    const uint32_t ce = cb + kBatch < c1 ? cb + kBatch : c1;
-    for (uint32_t c = cb; c < ce; ++c) {
+    uint32_t ib = 0;
+    if (l == 0) ib = atomicAdd(a.work_q + xcd, batch);
+    ib = (uint32_t)__shfl((int)ib, 0, kWave);
+    if (ib >= n_items) break;
+    const uint32_t ie = ib + batch < n_items ? ib + batch : (uint32_t)n_items;
+    for (uint32_t item = ib; item < ie; ++item) {
+        const uint32_t c = c0 + (item >> lg_split);
+        const uint32_t part = item & ((1u << lg_split) - 1u);   // of the chunk's targets
         const uint32_t j = c * (uint32_t)kWave + (uint32_t)l;
         const bool valid = j < nB;
         const float4 rec = a.bpos[valid ? j : nB - 1];
@@ -525,9 +537,12 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
                 if (r < nrows)
                     row_span(P, a.t_cell_start, cy0 + r % ny, cz0 + r / ny, x0, y0, z0, x1, y1, z1, R2, st, len);
                 const uint32_t inc = wave_incl_scan(len);
-                const uint32_t tot = readlane(inc, kWave - 1);
+                const uint32_t all = readlane(inc, kWave - 1);
                 const uint32_t offr = inc - len;
-                for (uint32_t b0 = 0; b0 < tot; b0 += kWave) {
+                // this item's part of the rows' targets, in whole steps
+                const uint32_t share = ((all >> lg_split) + kWave) / kWave * kWave;
+                const uint32_t tot = lg_split && (part + 1u) * share < all ? (part + 1u) * share : all;
+                for (uint32_t b0 = lg_split ? part * share : 0u; b0 < tot; b0 += kWave) {
                     // the target slot of lane v: the last row starting at or before v
                     const uint32_t v = b0 + (uint32_t)l;
                     const uint32_t lim = b0 + kWave < tot ? b0 + kWave : tot;
