@@ -203,10 +203,22 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
     else if (pp.tile_policy == 4) P.tile_mode = (pp.k <= 16 && (pp.k >= 1 || pp.r_enum > 0.0f)) ? 3 : 0;
     else {
         // a tile pays when its 64 targets fill a region no larger than the
-        // search reach, so that they share most of their candidates
+        // search reach, so that they share most of their candidates, and when
+        // those candidates are few: every lane evaluates all of them, while
+        // one target per wavefront spends a fixed ~0.6 ns and a 64-candidate
+        // step per 64.  Box of 1e6 targets at 30 ions/nm^3, r_max 2 nm, tiles
+        // against one target per wavefront (against neighbour-major) in ms:
+        // RDF with 10 neighbours within r_max (44 candidates) 0.50 / 0.69, 30
+        // (133) 0.82 / 0.79, 100 (322) 4.02 / 1.17, 700 26.8 / 3.43 (1.61);
+        // with k = 10 (137) 0.84 / 1.29, (167) 1.31 / 1.70, (322) 5.1 / 2.0,
+        // 33.5 / 4.1 (2.6).  With a kNN also only for 2^18 targets or more,
+        // below which its tiles leave SIMDs empty (2e5 targets: 0.45 / 0.39)
         const double R = fmax((double)pp.r_enum, 1.6 / 1.15 * rk_raw);
         const double v64 = 64.0 * vol / (double)(totT > 0 ? totT : 1);
-        P.tile_mode = (pp.k <= 16 && totT >= totB && totT >= 4096 && v64 <= R * R * R) ? 1 : 0;
+        const double side = cbrt(v64) + 2.0 * R;
+        const double cand = rho * side * side * side;
+        P.tile_mode = (pp.k <= 16 && totT >= totB && totT >= (pp.k > 0 ? 1u << 18 : 4096u) && v64 <= R * R * R &&
+                       cand <= (pp.k > 0 ? 200.0 : 100.0)) ? 1 : 0;
         // neighbours so dense that 64 of them span well under r_max: the RDF
         // runs neighbour-major (64 records per wavefront against every target
         // within reach), and the kNN, whose radius is then well below r_max,
@@ -214,9 +226,18 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
         // targets or more: with fewer, the per-lane kNN fills under four
         // wavefronts per SIMD and every neighbour chunk is still visited
         // (the 7.7e6-ion needle's 74 000 Sc targets against Al: 0.59 ms
-        // against 0.40 ms one target per wavefront)
+        // against 0.40 ms one target per wavefront).  Where the targets are
+        // about as dense as the neighbours each chunk has thousands of them:
+        // then from 2^17 targets without a kNN (1.5e5 targets 0.64 / 0.71 ms,
+        // 6e4 0.42 / 0.40), and from 2^18 with neighbours a little farther
+        // apart (1e6 targets, 200 neighbours within r_max, a64 = 1.1 r_max:
+        // 1.28 / 1.58 ms; 100 neighbours, 1.4 r_max: 1.14 / 1.17; 2e5 targets
+        // with 200 neighbours 0.53 / 0.44)
         const double a64 = cbrt(64.0 / rho);
-        if (!P.tile_mode && pp.k <= 16 && pp.r_enum > 0.0f && a64 <= (double)pp.r_enum && totT >= (1u << 18) &&
+        const bool even = 2ull * totT >= totB;
+        if (!P.tile_mode && pp.k <= 16 && pp.r_enum > 0.0f &&
+            a64 <= (even && totT >= (1u << 18) ? 1.15 : 1.0) * (double)pp.r_enum &&
+            totT >= (even && pp.k == 0 ? 1u << 17 : 1u << 18) &&
             (pp.k == 0 || rk_raw <= 0.5 * (double)pp.r_enum))
             P.tile_mode = 3;
     }
