@@ -1569,14 +1569,16 @@ apt_status apt_edge_distance(const apt_cloud* cloud, const float* tri, int64_t n
     InitArgs ia{status, nullptr, 0, nullptr, 0, nullptr, w.plain.strag_count};
     const apt_tuning tu = tuning();
     PlanParams pp;
-    pp.h_min = tu.h_min_frac;                  // about 0.5 nm: the lanes of a wavefront stay close
-    pp.occ = tu.cell_occ;
+    // 64 consecutive ions are one search group: with about 16 per cell of the
+    // bounding box (a needle fills it by half) they span two cells of a row
+    pp.h_min = 0.0f;
+    pp.occ = 16.0f;
     pp.tile_occ = tu.tile_occ;
     pp.k = 0;
     pp.cell_cap = cell_cap_for(cl.n);
     pp.tile_policy = 1;
     pp.r_enum = 1.0f;
-    pp.h_shrink = 0.7f;
+    pp.h_shrink = 0.0f;
     EdgeArgs a{};
     a.plan = w.plain.plan;
     a.bpos = w.plain.bpos;
@@ -1601,22 +1603,26 @@ apt_status apt_edge_distance(const apt_cloud* cloud, const float* tri, int64_t n
         TraceSpan span("binning", st);
         if ((s = run_binning(&cl, q, pp, w.plain, status, st, nullptr, 0, &ia)) != APT_OK) return s;
     }
-    const int gn = (int)std::min<int64_t>(std::max<int64_t>((cl.n + kBlock - 1) / kBlock, 1), 8192);
-    const int gt = (int)std::min<int64_t>(std::max<int64_t>((n_tri + kBlock - 1) / kBlock, 1), 4096);
+    auto blocks = [](int64_t items, int64_t per, int64_t most) {
+        return (int)std::min<int64_t>(std::max<int64_t>((items + per - 1) / per, 1), most);
+    };
+    const int gn = blocks(cl.n, kWave / 4, 1 << 17);         // a wavefront each, for 64 ions or for 16 of them
+    const int gt = blocks(n_tri, kEdgePrepBlock, 64);        // (few: each ends in atomics on the same words)
+    const int gp = blocks(n_tri, kBlock, 4096);
+    const int gf = blocks(w.piece_cap, kBlock, 4096);
     {
         TraceSpan span("edge", st);
-        hipLaunchKernelGGL(k_edge_zero, dim3(gn), dim3(kBlock), 0, st, a);
-        hipLaunchKernelGGL(k_edge_prep, dim3(gt), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL(k_edge_zero, dim3(1), dim3(64), 0, st, a);
+        hipLaunchKernelGGL(k_edge_prep, dim3(gt), dim3(kEdgePrepBlock), 0, st, a);
         hipLaunchKernelGGL(k_edge_plan, dim3(1), dim3(64), 0, st, a);
-        hipLaunchKernelGGL(k_edge_measure, dim3(gt), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL(k_edge_measure, dim3(gt), dim3(kEdgePrepBlock), 0, st, a);
         hipLaunchKernelGGL(k_edge_plan_pieces, dim3(1), dim3(64), 0, st, a);
-        hipLaunchKernelGGL(k_edge_pieces, dim3(gt), dim3(kBlock), 0, st, a);
-        hipLaunchKernelGGL(k_edge_clear, dim3(1024), dim3(kBlock), 0, st, a);
-        hipLaunchKernelGGL(k_edge_count, dim3(4096), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL(k_edge_pieces, dim3(gp), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL(k_edge_count, dim3(gf), dim3(kBlock), 0, st, a);
         hipLaunchKernelGGL(k_edge_scan_blocks, dim3(kTriScanBlocks), dim3(kBlock), 0, st, a);
         hipLaunchKernelGGL(k_edge_scan_add, dim3(kTriScanBlocks), dim3(kBlock), 0, st, a);
-        hipLaunchKernelGGL(k_edge_fill, dim3(4096), dim3(kBlock), 0, st, a);
-        hipLaunchKernelGGL(k_edge_dist, dim3(gn), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL(k_edge_fill, dim3(gf), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL(k_edge_dist, dim3(gn), dim3(kWave), 0, st, a);
     }
     return hip_check("edge distance launch");
 }

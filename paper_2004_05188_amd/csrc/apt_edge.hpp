@@ -9,22 +9,26 @@ constexpr uint32_t kTriCells = 1u << 22;     // cells of the triangle grid at mo
 constexpr int kTriScanTile = 4096;           // cells per block of the offset scan
 constexpr uint32_t kTriScanBlocks = kTriCells / kTriScanTile;
 
-constexpr int kPieceSizes = 17;              // piece radii tried: h/2 * 2^j (j < 16), and the largest radius
+constexpr int kPieceSizes = 17;              // piece radii tried: 3h/4 * 2^j (j < 16), and the largest radius
+
+constexpr int kEdgePrepBlock = 1024;         // threads of the kernels that sum over the triangles
+constexpr int kEdgeList = 192;               // pieces per round of k_edge_dist
 
 // The triangle grid, planned on the device from the ions' bounding box and
-// the triangles' sizes.  Every triangle is covered by pieces, the m x m
-// sub-triangles of a barycentric subdivision, registered by the centroid of
-// each piece with its radius; a piece stands for its whole triangle.
+// the triangles' sizes.  Every triangle is covered by pieces (parts of
+// slices parallel to its shortest edge), registered by the centroid of each
+// piece with its radius; a piece stands for its whole triangle.
 struct TriPlan {
     uint32_t rmax_bits;          // largest triangle radius (FP32 bits; radii are >= 0)
+    uint32_t cmax_bits;          // largest coordinate of a triangle
     uint32_t n_valid;            // triangles with finite vertices
     double r_sum;                // sum of their radii
     unsigned long long pieces_at[kPieceSizes];   // pieces for each candidate piece radius
     uint32_t piece_ctr;          // pieces written so far
     uint32_t piece_rmax_bits;    // largest piece radius
-    uint32_t n_pieces;
+    uint32_t n_pieces;           // pieces planned
     uint32_t piece_cap;          // pieces the workspace holds
-    float rho;                   // piece radius aimed at (a triangle gets ceil(r / rho)^2 pieces)
+    float rho;                   // piece radius aimed at (triangles no larger are one piece)
     float lo[3];
     float h, inv_h;
     int32_t dim[3];
@@ -42,7 +46,7 @@ struct EdgeArgs {
     uint32_t n_tri;
     float d_prb;
     uint32_t piece_cap;          // pieces the workspace holds
-    float4* tc;                  // [n_tri] centroid and radius (radius < 0: left out)
+    float4* tc;                  // [n_tri] centroid and radius (radius < 0: left out), then the unit normal
     float4* pc;                  // [piece_cap] piece centroid and radius
     uint32_t* ptri;              // [piece_cap] the piece's triangle
     uint32_t* pcell;             // [piece_cap] triangle grid cell of the piece
@@ -62,7 +66,6 @@ __global__ void k_edge_plan(EdgeArgs a);
 __global__ void k_edge_measure(EdgeArgs a);
 __global__ void k_edge_plan_pieces(EdgeArgs a);
 __global__ void k_edge_pieces(EdgeArgs a);
-__global__ void k_edge_clear(EdgeArgs a);
 __global__ void k_edge_count(EdgeArgs a);
 __global__ void k_edge_scan_blocks(EdgeArgs a);
 __global__ void k_edge_scan_add(EdgeArgs a);

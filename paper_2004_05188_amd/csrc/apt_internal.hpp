@@ -96,6 +96,28 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
     return (uint32_t)x;
 }
 
+// Smallest (largest) of a value over the wavefront, by the same moves: lanes
+// shifted in from outside a row bring the identity, lane 63 ends with the
+// result.
+template <class OP>
+__device__ __forceinline__ float wave_reduce_f(float v, float none, OP op) {
+    const int id = __builtin_bit_cast(int, none);
+    auto step = [&](auto moved) { v = op(v, __builtin_bit_cast(float, moved)); };
+    step(__builtin_amdgcn_update_dpp(id, __builtin_bit_cast(int, v), 0x111, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(id, __builtin_bit_cast(int, v), 0x112, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(id, __builtin_bit_cast(int, v), 0x114, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(id, __builtin_bit_cast(int, v), 0x118, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(id, __builtin_bit_cast(int, v), 0x142, 0xa, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(id, __builtin_bit_cast(int, v), 0x143, 0xc, 0xf, false));
+    return readlane(v, kWave - 1);
+}
+__device__ __forceinline__ float wave_min_f(float v) {
+    return wave_reduce_f(v, __builtin_inff(), [](float a, float b) { return fminf(a, b); });
+}
+__device__ __forceinline__ float wave_max_f(float v) {
+    return wave_reduce_f(v, -__builtin_inff(), [](float a, float b) { return fmaxf(a, b); });
+}
+
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);

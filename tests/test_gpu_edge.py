@@ -124,6 +124,25 @@ def test_box_far_coordinates(gpu, orc):
     assert np.all(np.abs(g.astype(np.float64) - expect) <= 1e-6 * np.maximum(expect, 1e-3) + 1e-9)
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 1000])
+def test_groups_and_cut_triangles(gpu, orc, n):
+    """Ions at the edges of a search group (16 and 64), against triangles far larger than the cloud (cut into many
+    pieces), thin fans around one point, a sliver of 1e-4 nm, and a hull the ions lie outside of."""
+    _say(f"case edge groups n={n}")
+    rng = np.random.default_rng(n)
+    xyz = (rng.uniform(-3.0, 3.0, (n, 3)) + np.array([40.0, -10.0, 5.0])).astype(np.float32)
+    fan = [[[40, -10, 9], [40 + 30 * np.cos(p), -10 + 30 * np.sin(p), 9], [40 + 30 * np.cos(p + 0.05),
+            -10 + 30 * np.sin(p + 0.05), 9]] for p in np.arange(0, 6.25, 0.05)]
+    big = [[[-400, -300, -8], [500, -250, -9], [30, 600, -7]], [[47, -300, -300], [47, 400, -200], [47, 40, 500]]]
+    thin = [[[36, -40, 0], [36, 60, 0], [36, 10, 1e-4]], [[30, -10, 5], [30.5, -10, 5], [30.25, -9.5, 5]]]
+    tri = np.array(fan + big + thin, np.float32)
+    for d_prb in (0.5, 4.0, 50.0, float("inf")):
+        check(orc, gpu, xyz, tri, d_prb, method="brute")
+    far = tri + np.float32(300.0)
+    for d_prb in (100.0, float("inf")):
+        check(orc, gpu, xyz, far, d_prb, method="brute")
+
+
 def test_edge_cases(gpu, orc, needle):
     _say("case edge edge cases")
     spec, xyz, d_an, mesh = needle
