@@ -1075,7 +1075,15 @@ static apt_status run_sdm(const apt_cloud* cl, apt_query q, float R, int32_t n_v
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
     const int64_t nv = (int64_t)n_vox * n_vox * n_vox;
-    InitArgs ia{status, hist, (int32_t)nv, nullptr, 0, nullptr, w.strag_count};
+    // the histogram is zeroed by the binning's first kernel, unless that has
+    // too few workgroups for it (16 voxels per thread: 3 workgroups took
+    // 130 us over 160^3 voxels)
+    const bool own_zero = nv > (int64_t)count_blocks(cl->n) * kBlock * 16;
+    if (own_zero) {
+        InitArgs za{nullptr, hist, (int32_t)nv};
+        hipLaunchKernelGGL(k_init, dim3(device_info().cus * 8), dim3(256), 0, st, za);
+    }
+    InitArgs ia{status, own_zero ? nullptr : hist, (int32_t)nv, nullptr, 0, nullptr, w.strag_count};
     const apt_tuning tu = tuning();
     const double Rd = (double)R;
     PlanParams pp;
@@ -1091,7 +1099,6 @@ static apt_status run_sdm(const apt_cloud* cl, apt_query q, float R, int32_t n_v
         TraceSpan span("binning", st);
         if ((s = run_binning(cl, q, pp, w, status, st, nullptr, 0, &ia)) != APT_OK) return s;
     }
-    hipLaunchKernelGGL(k_sdm_faces, dim3(1), dim3(kBlock), 0, st, w.E2, R, n_vox);
     SdmArgs a{};
     a.plan = w.plan;
     a.t_id = w.t_id;
@@ -1113,9 +1120,25 @@ static apt_status run_sdm(const apt_cloud* cl, apt_query q, float R, int32_t n_v
     a.band = (float)fmin(0.25, fmax(1e-4, 16.0 * 5.9604645e-8 * (double)n_vox));
     a.F = w.E2;
     a.hist = hist;
+    // the lists take the arrays that only the binning needed (the ion lists,
+    // both sorts' keys and values, the second record buffer: one contiguous
+    // part of the workspace), their fill counts the sort's digit counts
+    const size_t room = (size_t)(reinterpret_cast<char*>(w.t_rank) - reinterpret_cast<char*>(w.tid));
+    const size_t cap = std::min<size_t>(room / sizeof(uint16_t) / (kXcd * kSdmRuns) / 64 * 64, 0x7FFFFFC0u);
+    a.used = reinterpret_cast<unsigned long long*>(w.rs_counts);
+    // (fewer than 64 entries each: the cloud has too few ions for a list)
+    a.lg_run = kSdmLgRunMin;
+    while (a.lg_run < kSdmLgRunMax && ((int64_t)kSdmRuns << a.lg_run) < nv) ++a.lg_run;
+    a.list = nv <= ((int64_t)kSdmRuns << a.lg_run) && cap > 0 ? reinterpret_cast<uint16_t*>(w.tid) : nullptr;
+    a.cap = (uint32_t)cap;
+    hipLaunchKernelGGL(k_sdm_faces, dim3(1), dim3(kBlock), 0, st, a, w.E2);
     {
         TraceSpan span("sdm", st);
         hipLaunchKernelGGL(k_sdm, dim3(resident_grid(k_sdm, 0)), dim3(kBlock), 0, st, a);
+        if (a.list) {
+            hipLaunchKernelGGL(k_sdm_list, dim3(resident_grid(k_sdm_list, 0)), dim3(kBlock), 0, st, a);
+            hipLaunchKernelGGL(k_sdm_merge, dim3(kSdmParts, kSdmRuns), dim3(kSdmMergeBlock), 0, st, a);
+        }
     }
     return hip_check("two-point statistic launch");
 }

@@ -91,10 +91,17 @@ __device__ __forceinline__ void row_span(const GridPlan& P, const uint32_t* __re
     }
 }
 
-template <class F>
+struct NoStep {
+    __device__ __forceinline__ void operator()() const {}
+};
+
+// after_step() is called by all lanes after each kUnroll batches (work that
+// would cost registers in every unrolled copy of f).
+template <class F, class G = NoStep>
 __device__ __forceinline__ void enumerate_box(const GridPlan& P, const uint32_t* __restrict__ cell_start,
                                               const float4* __restrict__ bpos, float x0, float y0, float z0,
-                                              float x1, float y1, float z1, float R, F&& f, bool centre = false) {
+                                              float x1, float y1, float z1, float R, F&& f, bool centre = false,
+                                              G&& after_step = G{}) {
     // neighbours within R of the box [x0,x1] x [y0,y1] x [z0,z1]
     const int l = lane_id();
     const float Re = R + P.eps;
@@ -152,16 +159,17 @@ __device__ __forceinline__ void enumerate_box(const GridPlan& P, const uint32_t*
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
                 if (b0 + (uint32_t)(kWave * u) < tot) f(idx[u] != kNone, c[u]);
+            after_step();
         }
     }
 }
 
 
-template <class F>
+template <class F, class G = NoStep>
 __device__ __forceinline__ void enumerate(const GridPlan& P, const uint32_t* __restrict__ cell_start,
                                           const float4* __restrict__ bpos, float px, float py, float pz,
-                                          float R, F&& f, bool centre = false) {
-    enumerate_box(P, cell_start, bpos, px, py, pz, px, py, pz, R, f, centre);
+                                          float R, F&& f, bool centre = false, G&& after_step = G{}) {
+    enumerate_box(P, cell_start, bpos, px, py, pz, px, py, pz, R, f, centre, after_step);
 }
 
 // Everything one target needs besides its position and index.

@@ -72,6 +72,17 @@ def test_needle(gpu, orc, small_needle, A, B, d_srf, R, n_vox):
     assert g.sum() > 0
 
 
+@pytest.mark.parametrize("n_vox", [1, 6, 25, 26, 160, 161, 162])
+def test_voxel_runs(gpu, orc, small_needle, n_vox):
+    """Histograms on both sides of the sizes at which the voxel runs of the pair lists grow (25^3 <= 2^14 < 26^3) and
+    the lists end (161^3 <= 2^22 < 162^3), with more pairs than the lists hold (every ion against every ion)."""
+    _say(f"case sdm voxel runs n={n_vox}")
+    xyz, lab, d = small_needle
+    g = check(orc, gpu, xyz, lab, d, ANY, ANY, 0.5, 1.0, n_vox)
+    assert int(g.sum()) > 10_000_000
+    check(orc, gpu, xyz, lab, d, SC, ANY, 0.0, 1.5, n_vox)
+
+
 @pytest.mark.parametrize("A,B", [(SC, AL), (ANY, ANY)])
 def test_far_coordinates_faces(gpu, orc, small_needle, A, B):
     # coordinates near 3000 nm: a 2.4e-4 nm FP32 grid, so many components are
