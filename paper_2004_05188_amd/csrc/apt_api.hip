@@ -430,19 +430,34 @@ __global__ void k_finish(FinishArgs a) {
 // zscale (device, may be NULL) scales z before binning; sel_union makes
 // targets and neighbours both the ions that take part in a pair in either
 // role.
-static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams& pp, const PlainWs& w,
+static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams& plan, const PlainWs& w,
                               int32_t* status, hipStream_t st, const double* zscale = nullptr,
                               int sel_union = 0, const InitArgs* init = nullptr) {
     const int64_t n = cl->n;
     const int G = count_blocks(n);
     const int64_t chunk = count_chunk(n, G);
     const int cus = device_info().cus;
+    // (the smoothed RDF adds in the order of the records, which has to be the
+    // same from run to run: it passes no `init` and keeps the stable sort)
+    const bool every = q.target == APT_ANY || q.neighbor == APT_ANY;
+    const bool counting = init && n <= (every ? kCountSortMax / 2 : kCountSortMax);
+    PlanParams pp = plan;
+    if (counting) {
+        // a counter per cell and list, in the radix sort's value arrays
+        pp.cell_cap = (uint32_t)std::min<int64_t>(pp.cell_cap, std::max<int64_t>(n, 1));
+        pp.key_cap = pp.cell_cap;
+    }
 
     CountArgs ca{cl->xyz, cl->lab, cl->d_bnd, n, chunk, q.target, q.neighbor, q.d_srf, zscale,
                  w.part_cnt, w.part_bbox, w.part_nf, sel_union};
     if (init) {
         ca.init = *init;
         ca.do_init = 1;
+    }
+    if (counting) {
+        ca.init.zero[0] = w.V[0];
+        ca.init.zero[1] = w.V[1];
+        ca.init.n_zero = pp.key_cap;
     }
     hipLaunchKernelGGL(k_count, dim3(G), dim3(kBlock), 0, st, ca);
     PlanArgs pa{G, w.part_cnt, w.part_bbox, w.part_nf, w.part_off, pp, zscale, w.plan, status};
@@ -452,6 +467,23 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
     CompactArgs cm{cl->lab, cl->d_bnd, n, chunk, q.target, q.neighbor, q.d_srf, w.part_off, w.tid,
                    all_b ? nullptr : w.bsel, sel_union, w.plan, cl->xyz, zscale, w.K[0], w.V[0], w.KB[0],
                    {w.bpos, w.brec2}};
+    const bool occ = pp.k > 0 && !zscale;
+    if (counting) {
+        cm.tcnt = w.V[0];
+        cm.bcnt = w.V[1];
+        cm.trank = w.K[1];
+        cm.brank = w.KB[1];
+        hipLaunchKernelGGL(k_compact, dim3(G), dim3(kBlock), 0, st, cm);
+        CountSortArgs cs{w.plan, pp.key_cap, {w.V[0], w.V[1]}, {w.rs_counts, w.rs_counts + kCsTiles},
+                         {occ ? w.strag_count + 1 : nullptr, occ ? w.strag_count + 2 : nullptr},
+                         w.tid, w.K[0], w.K[1], cl->xyz, w.t_rank, w.t_id, w.tx, w.ty, w.tz, w.t_cell_start,
+                         w.KB[0], w.KB[1], w.brec2, w.bpos, w.cell_start};
+        const int tiles = (int)((pp.key_cap + kCsTile - 1) / kCsTile);
+        hipLaunchKernelGGL(k_cs_scan, dim3(tiles, 2), dim3(kBlock), 0, st, cs);
+        const int gp = (int)std::min<int64_t>(std::max<int64_t>((n + kBlock - 1) / kBlock, 1), cus * 8);
+        hipLaunchKernelGGL(k_cs_place, dim3(gp), dim3(kBlock), 0, st, cs);
+        return hip_check("binning launch");
+    }
     hipLaunchKernelGGL(k_compact, dim3(G), dim3(kBlock), 0, st, cm);
 
     // both sorts share each pass's launches; target keys never need more
@@ -475,7 +507,6 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
     }
     // targets in cell order and the neighbour records, in one launch;
     // occupied cells (distinct sorted keys) feed the kNN radii
-    const bool occ = pp.k > 0 && !zscale;
     OrderArgs oa{w.plan, cl->xyz, w.tid, {w.V[0], w.V[1]}, w.t_rank, w.t_id, w.tx, w.ty, w.tz,
                  {w.K[0], w.K[1]}, occ ? w.strag_count + 1 : nullptr, w.t_cell_start};
     GatherArgs ga{w.plan, nullptr, zscale, {w.KB[0], w.KB[1]}, {nullptr, nullptr}, w.bpos, w.cell_start,

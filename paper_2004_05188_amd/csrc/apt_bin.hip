@@ -305,7 +305,8 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
         const uint64_t kmax = nbx * nby * nbz * 512u - 1u;
         const int cap_passes = sort_passes_for(pp.cell_cap - 1u);
         // (mode 3 looks targets up by cell: plain cell order)
-        if (P.tile_mode != 3 && kmax <= 0xFFFFFFFFull && sort_passes_for(kmax) <= cap_passes) {
+        if (P.tile_mode != 3 && kmax <= 0xFFFFFFFFull &&
+            (pp.key_cap ? kmax < pp.key_cap : sort_passes_for(kmax) <= cap_passes)) {
             P.tblock = 8;
             P.nbx = (int32_t)nbx;
             P.nby = (int32_t)nby;
@@ -379,12 +380,16 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
         }
     };
     run(a.tid, t0, t1, [&](uint32_t j, uint32_t, float x, float y, float z) {
-        a.tkeys[j] = target_key(P, x, y, z);
-        a.tvals[j] = j;
+        const uint32_t key = target_key(P, x, y, z);
+        a.tkeys[j] = key;
+        if (a.tcnt) a.trank[j] = atomicAdd(a.tcnt + key, 1u);
+        else a.tvals[j] = j;
     });
-    float4* __restrict__ brec = rec_after(a.brec[0], a.brec[1], (int)P.passes, -1);
+    float4* __restrict__ brec = a.bcnt ? a.brec[1] : rec_after(a.brec[0], a.brec[1], (int)P.passes, -1);
     auto bkey = [&](uint32_t j, uint32_t id, float x, float y, float z) {
-        a.bkeys[j] = cell_id(P, x, y, z);
+        const uint32_t key = cell_id(P, x, y, z);
+        a.bkeys[j] = key;
+        if (a.bcnt) a.brank[j] = atomicAdd(a.bcnt + key, 1u);
         brec[j] = make_float4(x, y, z, __builtin_bit_cast(float, id));
     };
     if (a.bsel) run(a.bsel, b0, b1, bkey);
@@ -975,6 +980,94 @@ __device__ __forceinline__ void gather(const GatherArgs& a, uint32_t bid, uint32
         distinct = wave_sum(distinct);
         if (lane_id() == 0 && distinct) atomicAdd(a.distinct, distinct);
     }
+}
+
+// ------------------------------------------------------------------------
+// 8. counting sort (small clouds): the counts of each key, made by the
+//    compaction, scanned and used
+// ------------------------------------------------------------------------
+// keys of list q: the targets' keys (block-raster order or cells), the cells
+__device__ __forceinline__ uint32_t cs_keys(const GridPlan& P, int q) {
+    if (q == 1 || P.tblock == 1) return P.n_cells;
+    return (uint32_t)P.nbx * (uint32_t)P.nby * (((uint32_t)P.dim[2] + 7u) / 8u) * 512u;
+}
+
+__global__ __launch_bounds__(kBlock) void k_cs_scan(CountSortArgs a) {
+    const GridPlan P = *a.plan;
+    const int q = blockIdx.y;
+    const uint32_t n = cs_keys(P, q), base = blockIdx.x * (uint32_t)kCsTile;
+    if (base >= n) return;
+    __shared__ uint32_t s_w[kWavesPerBlock], s_d[kWavesPerBlock];
+    constexpr uint32_t per = kCsTile / kBlock;
+    uint32_t* __restrict__ cnt = a.cnt[q];
+    const uint32_t c0 = base + threadIdx.x * per;
+    uint32_t v[per], sum = 0, some = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < per; ++k) {
+        v[k] = c0 + k < n ? cnt[c0 + k] : 0u;
+        sum += v[k];
+        some += v[k] != 0u;
+    }
+    const uint32_t inc = wave_incl_scan(sum);
+    some = wave_sum(some);
+    const int w = threadIdx.x / kWave;
+    if (lane_id() == kWave - 1) {
+        s_w[w] = inc;
+        s_d[w] = some;
+    }
+    __syncthreads();
+    uint32_t run = inc - sum;
+    for (int u = 0; u < w; ++u) run += s_w[u];
+#pragma unroll
+    for (uint32_t k = 0; k < per; ++k) {
+        if (c0 + k < n) cnt[c0 + k] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == kBlock - 1) {
+        a.sums[q][blockIdx.x] = run;
+        for (int u = 1; u < kWavesPerBlock; ++u) s_d[0] += s_d[u];
+        if (a.distinct[q] && s_d[0]) atomicAdd(a.distinct[q], s_d[0]);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
+    __shared__ uint32_t s_off[2][kCsTiles], s_w[2][kWavesPerBlock];
+    const GridPlan P = *a.plan;
+    const uint32_t nk[2] = {cs_keys(P, 0), cs_keys(P, 1)};
+    {
+        // where each tile starts: the sums of the tiles before it
+        const int t = threadIdx.x, w = t / kWave;
+        uint32_t v[2], inc[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            v[q] = t < kCsTiles && (uint32_t)t * kCsTile < nk[q] ? a.sums[q][t] : 0u;
+            inc[q] = wave_incl_scan(v[q]);
+            if (lane_id() == kWave - 1) s_w[q][w] = inc[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            uint32_t run = inc[q] - v[q];
+            for (int u = 0; u < w; ++u) run += s_w[q][u];
+            if (t < kCsTiles) s_off[q][t] = run;
+        }
+        __syncthreads();
+    }
+    auto start = [&](int q, uint32_t key) { return a.cnt[q][key] + s_off[q][key / kCsTile]; };
+    const uint32_t first = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
+    for (uint32_t j = first; j < P.nB; j += stride) a.bpos[start(1, a.bkeys[j]) + a.brank[j]] = a.brec[j];
+    for (uint32_t c = first; c <= P.n_cells; c += stride) a.cell_start[c] = c < P.n_cells ? start(1, c) : P.nB;
+    for (uint32_t j = first; j < P.nT; j += stride) {
+        const uint32_t id = a.tid[j], p = start(0, a.tkeys[j]) + a.trank[j];
+        a.t_rank[p] = j;
+        a.t_id[p] = id;
+        a.tx[p] = a.xyz[3 * (size_t)id];
+        a.ty[p] = a.xyz[3 * (size_t)id + 1];
+        a.tz[p] = a.xyz[3 * (size_t)id + 2];
+    }
+    // (mode 3: the targets are in plain cell order)
+    if (P.tile_mode == 3 && a.t_cell_start)
+        for (uint32_t c = first; c <= P.n_cells; c += stride) a.t_cell_start[c] = c < P.n_cells ? start(0, c) : P.nT;
 }
 
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a) { gather(a, blockIdx.x, gridDim.x); }

@@ -66,6 +66,8 @@ struct InitArgs {
     float ke2_rmax;
     int32_t ke2_nbins;
     uint32_t* work_q = nullptr;   // [2 kXcd] per-XCD work counters of the pair kernels, or NULL
+    uint32_t* zero[2] = {nullptr, nullptr};   // [n_zero] the counting sort's counters, or NULL
+    uint32_t n_zero = 0;
 };
 
 __device__ inline void fill_edges(double* E2, float r_max, int n_bins, int t, int stride);
@@ -86,6 +88,11 @@ __device__ inline void init_body(const InitArgs& a, int t, int st) {
         for (int b = t; b < a.n1; b += st) a.h1[b] = 0;
     if (a.h2)
         for (int b = t; b < a.n2; b += st) a.h2[b] = 0;
+    if (a.zero[0])
+        for (uint32_t b = (uint32_t)t; b < a.n_zero; b += (uint32_t)st) {
+            a.zero[0][b] = 0;
+            a.zero[1][b] = 0;
+        }
 }
 
 struct CountArgs {
@@ -140,6 +147,54 @@ struct CompactArgs {
     uint32_t* tvals;
     uint32_t* bkeys;
     float4* brec[2];
+    // the counting sort (tcnt non-NULL): each key's count so far is the ion's
+    // rank within its key; the records go to brec[1]
+    uint32_t* tcnt = nullptr;
+    uint32_t* bcnt = nullptr;
+    uint32_t* trank = nullptr;
+    uint32_t* brank = nullptr;
+};
+
+// Counting sort of clouds up to kCountSortMax ions: the compaction counts
+// each key with an atomic that also gives the ion its rank within the key, one
+// launch scans the counts (each workgroup a tile, leaving the tiles' sums),
+// one puts every ion in its place.  Five launches where the radix sort takes
+// up to thirteen at about 5 us each; beyond, its atomics (2.4e10 a second,
+// 0.3 ms for 7.5e6 records) cost more than the passes.  Needle of n ions, RDF
+// of Sc against every ion, radix / counting sort in us: 12 000 93 / 72, 240 000
+// 151 / 133, 5e5 225 / 216, 1e6 291 / 309; kNN and RDF of Sc against Sc: 12 000
+// 82 / 57, 240 000 122 / 88, 1e6 208 / 174.  So half the size where a list is
+// certain to hold every ion.  The order within a
+// cell is that of the atomics: only sums that depend on no order may follow
+// (counts, kNN keys that carry the index, the smallest index of a cluster).
+constexpr int64_t kCountSortMax = (int64_t)1 << 20;
+constexpr int kCsTile = kBlock * 16;             // keys per workgroup of the scan
+constexpr int kCsTiles = (int)(kCountSortMax / kCsTile);   // tiles per list at most (cells: at most an ion each)
+static_assert(kCsTiles <= kBlock, "one thread per tile sum");
+
+struct CountSortArgs {
+    const GridPlan* plan;
+    uint32_t n_keys_max;    // counters per list
+    uint32_t* cnt[2];       // [targets, neighbours] counts, then exclusive prefixes within their tile
+    uint32_t* sums[2];      // [kCsTiles] counts of each tile
+    uint32_t* distinct[2];  // += keys with a count, or NULL
+    // targets
+    const uint32_t* tid;
+    const uint32_t* tkeys;
+    const uint32_t* trank;
+    const float* xyz;
+    uint32_t* t_rank;
+    uint32_t* t_id;
+    float* tx;
+    float* ty;
+    float* tz;
+    uint32_t* t_cell_start; // written when the plan chose mode 3
+    // neighbours
+    const uint32_t* bkeys;
+    const uint32_t* brank;
+    const float4* brec;
+    float4* bpos;
+    uint32_t* cell_start;
 };
 
 struct KeyArgs {
@@ -271,6 +326,8 @@ __global__ void k_rs_scan(SortSet a);
 __global__ void k_rs_downsweep_large(SortSet a);   // kDsLargeBlock threads
 __global__ void k_rs_downsweep_small(SortSet a);   // kDsSmallBlock threads
 __global__ void k_gather(GatherArgs a);
+__global__ void k_cs_scan(CountSortArgs a);      // grid (kCsTiles, 2)
+__global__ void k_cs_place(CountSortArgs a);
 // the target order (first g_order workgroups) and the neighbour gather (the
 // rest) in one launch: they read and write disjoint arrays
 __global__ void k_order_gather(OrderArgs oa, GatherArgs ga, int32_t g_order);

@@ -62,6 +62,9 @@ struct PlanParams {
     // mode 3's RDF kernel: 0 automatic (neighbour-major), 1 neighbour-major,
     // 2 one target per wavefront
     int32_t rdf_kernel = 0;
+    // > 0: the counting sort's counters per list, which bound the target keys
+    // (0: the radix sort, whose passes do)
+    uint32_t key_cap = 0;
 };
 
 // ---------------------------------------------------------------- waves --

@@ -56,3 +56,55 @@ def test_automatic_mode_equals_one_target_per_wavefront(n, frac, A, B, k, r_max,
     for x, y in zip((*a.trimmed(), a.knn_hist, a.rdf_hist, a.status), (*b.trimmed(), b.knn_hist, b.rdf_hist, b.status)):
         assert torch.equal(x, y)
     assert int(a.rdf_hist.sum()) > 0
+
+
+@pytest.mark.parametrize("A,B,k", [(0, 1, 10), (1, 0, 0), (1, 1, 5), (ANY, ANY, 0)])
+def test_counting_and_radix_sort_agree(A, B, k):
+    """The largest cloud of the counting sort, and one ion more (of a species in no query, or without a finite
+    position): the radix sort bins the same ions and every result is the same."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    n = 1 << (19 if ANY in (A, B) else 20)
+    print(f"case counting sort n={n} A={A} B={B} k={k}", flush=True)
+    xyz, lab, d = _box(torch, n, 0.02, 5)
+    more = torch.full((1, 3), float("nan") if A == ANY else 3.0, device="cuda")
+    big = (torch.cat([xyz, more]), torch.cat([lab, torch.full((1,), 7, dtype=torch.uint8, device="cuda")]),
+           torch.cat([d, torch.ones(1, device="cuda")]))
+    ws = aptstat.Workspace()
+    r = []
+    for c in ((xyz, lab, d), big):
+        cloud = aptstat.Cloud(*c)
+        if k == 0:
+            r.append((aptstat.rdf(cloud, A, B, 0.5, 2.0, 200, ws=ws),))
+        else:
+            q = aptstat.knn_rdf(cloud, A, B, 0.5, k, ws=ws)
+            r.append((*q.trimmed(), q.knn_hist, q.rdf_hist, q.status))
+    assert int(r[0][-1 if k == 0 else -2].sum()) > 0
+    for x, y in zip(*r):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 4095, 4096, 4097, 70_001])
+def test_counting_sort_sizes(orc, n):
+    """Clouds around the scan's tile of 4096 keys, stretched so that there are about as many cells as ions, against
+    the oracle."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    print(f"case counting sort sizes n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    xyz = (rng.random((n, 3)) * np.array([60.0, 40.0, max(1.0, n / 600.0)])).astype(np.float32)
+    lab = (rng.random(n) < 0.3).astype(np.uint8)
+    d = rng.random(n).astype(np.float32)
+    cloud = aptstat.Cloud(*(torch.from_numpy(v).cuda() for v in (xyz, lab, d)))
+    for A, B in ((ANY, ANY), (1, 0), (0, ANY)):
+        g = aptstat.knn_rdf(cloud, A, B, 0.25, 6, r_max=2.0, n_bins=100, kb_nbins=500)
+        t, dist, nid, h = orc.knn(xyz, lab, d, A, B, 0.25, 6, kb_rmax=5.0, kb_nbins=500)
+        tid, gd, gn = (v.cpu().numpy() for v in g.trimmed())
+        assert np.array_equal(tid, t) and np.array_equal(gn, nid)
+        assert np.allclose(gd, dist, rtol=1e-6, atol=0)
+        assert np.array_equal(g.knn_hist.cpu().numpy().astype(np.uint64), h)
+        assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, A, B, 0.25, 2.0, 100))
