@@ -912,7 +912,7 @@ static apt_status run_batched(const apt_cloud* cl, const apt_query* pairs, int32
         }
         ba.items = w.items;
         ba.titems = w.titems;
-        ba.work = w.work;
+        ba.work = reinterpret_cast<uint64_t*>(w.plain.rs_counts);   // (free once the ions are binned)
         ba.tile_ok = (k <= 16 && batched_tile_lds_bytes(rb.n_bins) <= kMaxLds && bt.tiles == 0) ? 1 : 0;
         ba.tile_reach = bt.tile_reach;
         ba.occ = reinterpret_cast<const uint32_t*>(w.work + 4);

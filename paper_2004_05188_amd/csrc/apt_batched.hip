@@ -233,12 +233,41 @@ __global__ void k_batch_items(BatchPairArgs a) {
         }
     a.items[a.R * a.n_pairs] = acc;
     a.titems[a.R * a.n_pairs] = tacc;
-    a.work[0] = 0;
-    a.work[1] = 0;
+    for (int x = 0; x < 2 * kXcd; ++x) a.work[x * kQueueStride] = 0;
+}
+
+// The next batch of work for this wavefront: [*c0, *c1) of [0, total), of
+// which XCD x's queue holds the x-th eighth.  A wavefront takes from its own
+// XCD's queue (a compact region, whose records its L2 keeps) and, when that is
+// empty, from the next ones; false when all are.  One counter for all
+// wavefronts was the tile kernel's limit: an atomic on one address takes about
+// 16 ns, and a replicate's dense pairs are 2e5 tiles (eight replicates of the
+// 7.7e6-ion needle's six pairs: 26.9 ms of tiles whatever a tile cost, then
+// 22.5 ms).
+__device__ __forceinline__ bool next_work(uint64_t* queue, uint64_t total, uint32_t batch, int& x, int& empty,
+                                          uint64_t* c0, uint64_t* c1) {
+    while (empty < kXcd) {
+        const uint64_t g0 = total * (uint64_t)x / kXcd, g1 = total * (uint64_t)(x + 1) / kXcd;
+        uint64_t c = 0;
+        if (lane_id() == 0)
+            c = atomicAdd((unsigned long long*)&queue[x * kQueueStride], (unsigned long long)batch);
+        // broadcast as a wave-uniform value
+        c = g0 + (((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32)) << 32) |
+                  (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c));
+        if (c < g1) {
+            *c0 = c;
+            *c1 = c + batch < g1 ? c + batch : g1;
+            return true;
+        }
+        x = x + 1 < kXcd ? x + 1 : 0;
+        ++empty;
+    }
+    return false;
 }
 
 // ---- 5. the pair launch over (replicate, pair, target)
-constexpr uint64_t kChunk = 32;
+constexpr uint32_t kChunk = 32;       // targets per batch
+constexpr uint32_t kTileBatch = 8;    // tiles per batch
 
 __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {   // 6 waves per SIMD (<= 80 VGPRs)
     extern __shared__ __align__(16) uint8_t smem[];
@@ -272,17 +301,9 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
     const float* d_bnd = a.d_bnd;
     float d_srf = 0.0f;
     int rp = 0;
-    for (;;) {
-        uint64_t c0 = 0;
-        if (l == 0) c0 = atomicAdd((unsigned long long*)a.work, (unsigned long long)kChunk);
-        {
-            // broadcast lane 0's chunk start as a wave-uniform value
-            const uint64_t b = __shfl((unsigned long long)c0, 0, kWave);
-            c0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32) |
-                 (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-        }
-        if (c0 >= total) break;
-        const uint64_t c1 = c0 + kChunk < total ? c0 + kChunk : total;
+    int x = blockIdx.x % kXcd, empty = 0;
+    uint64_t c0, c1;
+    while (next_work(a.work, total, kChunk, x, empty, &c0, &c1)) {
         // (replicate, pair) of the first item: last rp with items[rp] <= c0
         {
             int lo = 0, hi = RP;      // items[lo] <= c0 < items[hi]
@@ -377,15 +398,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
     uint64_t seg_a0 = 0, seg_len = 0;
     float d_srf = 0.0f, Rk = 0.0f;
     int rp = 0;
-    for (;;) {
-        uint64_t g = 0;
-        if (l == 0) g = atomicAdd((unsigned long long*)&a.work[1], 1ull);
-        {
-            const uint64_t b = __shfl((unsigned long long)g, 0, kWave);
-            g = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32) |
-                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-        }
-        if (g >= total) break;
+    int x = blockIdx.x % kXcd, empty = 0;
+    uint64_t c0, c1;
+    while (next_work(a.work + kXcd * kQueueStride, total, kTileBatch, x, empty, &c0, &c1)) {
+    for (uint64_t g = c0; g < c1; ++g) {
         {
             int lo = 0, hi = RP;      // titems[lo] <= g < titems[hi]
             while (hi - lo > 1) {
@@ -459,6 +475,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
             flush_hist(T.hist_l, T.hist_g, a.n_bins);
             since_flush = 0;
         }
+    }
     }
     if (cur >= 0) flush_hist(T.hist_l, T.hist_g, a.n_bins);
 }

@@ -36,6 +36,8 @@ struct BatchPair {
     int32_t pad;
 };
 
+constexpr int kQueueStride = 16;   // u64 between work counters: a cache line each
+
 struct BatchPairArgs {
     const GridPlan* plan;
     const float* xyz;
@@ -50,7 +52,7 @@ struct BatchPairArgs {
     BatchPair pairs[kMaxPairs];
     uint64_t* items;          // [R * n_pairs + 1] prefix of target counts (one-per-wavefront pairs)
     uint64_t* titems;         // [R * n_pairs + 1] prefix of 64-target tiles (tiled pairs)
-    uint64_t* work;           // [2] work counters: targets, tiles (zeroed by k_batch_items)
+    uint64_t* work;           // [2][kXcd] work queues: targets, tiles (kQueueStride apart; zeroed by k_batch_items)
     const uint32_t* occ;      // [1] cells holding at least one ion (the specimen's volume in cells)
     int32_t tile_ok;          // tiles allowed (k <= 16, LDS fits, tuning)
     float tile_reach;         // certified kNN reach of a tile, times the Poisson mean k-th distance
