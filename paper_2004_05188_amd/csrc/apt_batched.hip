@@ -442,7 +442,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
             valid = a.d_bnd == nullptr || a.d_bnd[i] >= d_srf;
         }
         uint32_t hits = 0;
-        const uint64_t kth = run_tile_kth<kRdfLds | kSelf, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, hits);
+        const uint64_t kth = run_tile_kth<kRdfLds | kSelf, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, hits,
+                                                                 a.knn_hist ? a.kb_nbins : 0, a.kb_inv_w64);
         const bool fin = isfinite(px) && isfinite(py) && isfinite(pz);
         const bool certified = valid && (kth != ~0ull || !fin);
         uint64_t* kh = a.knn_hist ? a.knn_hist + ((size_t)(a.rep0 + r) * a.n_pairs + p) * (size_t)(a.kb_nbins + 1)

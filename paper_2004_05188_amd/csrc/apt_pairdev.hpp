@@ -296,6 +296,18 @@ __device__ __forceinline__ int run_target(const GridPlan& P, const PairTask& T, 
 }
 
 // ---------------------------------------------------------------- tiles --
+// Bin of a k-th squared distance as far as FP32 decides it (the band of
+// key_bin, below): -1 where the FP64 distance has to.
+__device__ __forceinline__ int kth_bin_fp32(float d2, int kb_nbins, double kb_inv_w64) {
+    const float t = __builtin_amdgcn_sqrtf(d2) * (float)kb_inv_w64;
+    if (!(t < (float)kb_nbins + 2.0f)) return kb_nbins;
+    const float band = (float)fmin(0.25, fmax(1e-6 * kb_inv_w64, 4e-6 * (double)kb_nbins));
+    const int bf = (int)t;
+    const float fr = t - (float)bf;
+    if (fr > band && fr < 1.0f - band) return bf < kb_nbins ? bf : kb_nbins;
+    return -1;
+}
+
 // 64 targets per wavefront, one per lane: the neighbour records within R of
 // the targets' bounding box are staged through LDS in chunks, and every lane
 // scans them for its own target, keeping its KMAX smallest kNN keys (FP32
@@ -477,37 +489,33 @@ __device__ __forceinline__ void run_lane(const GridPlan& P, const PairTask& T, b
     }
 }
 
-// As run_tile, for callers that need only each lane's k-th neighbour key
-// (the k-th distance histogram).  The scan keeps the KMAX smallest FP32
-// squared distances per lane with a min/max network (two instructions a
-// slot, no keys); a second, smaller enumeration (radius: the largest k-th
-// distance of the tile) then finds the k-th neighbour's index: the smallest
-// index among the candidates at exactly that distance when the k-1 nearer
-// ones are strictly nearer.  Returns the k-th key (FP32 d2 bits << 32 |
-// index), or ~0 when it is not settled here: fewer than k neighbours within
-// Rk, or the k-th distance shared by several of the k nearest (the caller
-// finishes those targets exactly).
+// The k-th key of each lane's target only (with the RDF counts), for the
+// k-th distance histogram: the scan keeps the k smallest squared distances,
+// ascending, with one median per place (place q takes the middle of its left
+// neighbour, the newcomer and itself), and no indices.  An index is needed only
+// where FP32 leaves the k-th distance's bin open, about one target in 25: the
+// wavefront then looks through the staged records for it together.  (A second
+// enumeration and scan for all lanes' indices, and a minimum and a maximum per
+// place, took the 7.7e6-ion needle's dense pairs 2.8 ms per replicate
+// instead of 2.0.)  Tiles with more candidates than the stage holds
+// enumerate twice.  kb_nbins <= 0: no histogram, no index needed.  Returns the
+// k-th key (FP32 d2 bits << 32 | index), or ~0 when it is not settled here:
+// fewer than k neighbours within Rk, or an index needed at a distance that
+// several of the k nearest share (the caller finishes those targets exactly).
 template <int FLAGS, int KMAX>
 __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTask& T, bool valid, float px,
                                                  float py, float pz, uint32_t i, float Rk, int k, float4* stage,
-                                                 uint32_t& hits) {
+                                                 uint32_t& hits, int kb_nbins, double kb_inv_w64) {
     constexpr bool RDF = (FLAGS & (kRdfLds | kRdfGlobal)) != 0;
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
     constexpr bool SELF = (FLAGS & kSelf) != 0;
     static_assert(KMAX > 0, "k-th key needs KMAX > 0");
+    const int l = lane_id();
     const bool fin = valid && isfinite(px) && isfinite(py) && isfinite(pz);
-    float x0 = fin ? px : INFINITY, y0 = fin ? py : INFINITY, z0 = fin ? pz : INFINITY;
-    float x1 = fin ? px : -INFINITY, y1 = fin ? py : -INFINITY, z1 = fin ? pz : -INFINITY;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        x0 = fminf(x0, __shfl_xor(x0, d, kWave));
-        y0 = fminf(y0, __shfl_xor(y0, d, kWave));
-        z0 = fminf(z0, __shfl_xor(z0, d, kWave));
-        x1 = fmaxf(x1, __shfl_xor(x1, d, kWave));
-        y1 = fmaxf(y1, __shfl_xor(y1, d, kWave));
-        z1 = fmaxf(z1, __shfl_xor(z1, d, kWave));
-    }
     if (!__any(fin)) return ~0ull;
+    const float x0 = wave_min_f(fin ? px : INFINITY), x1 = wave_max_f(fin ? px : -INFINITY);
+    const float y0 = wave_min_f(fin ? py : INFINITY), y1 = wave_max_f(fin ? py : -INFINITY);
+    const float z0 = wave_min_f(fin ? pz : INFINITY), z1 = wave_max_f(fin ? pz : -INFINITY);
     const float rk2 = Rk * Rk;
     const float R = RDF ? fmaxf(T.r_enum, Rk * 1.000001f) : Rk * 1.000001f;
     float top[KMAX];
@@ -536,18 +544,16 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
             }
             const bool in = me && d2 <= rk2;
             if (__ballot(in && d2 < top[KMAX - 1])) {
-                float x = in ? d2 : INFINITY;
+                const float x = in ? d2 : INFINITY;
 #pragma unroll
-                for (int q = 0; q < KMAX; ++q) {
-                    const float lo = fminf(x, top[q]);
-                    x = fmaxf(x, top[q]);
-                    top[q] = lo;
-                }
+                for (int q = KMAX - 1; q > 0; --q) top[q] = __builtin_amdgcn_fmed3f(top[q - 1], x, top[q]);
+                top[0] = fminf(top[0], x);
             }
         }
         wave_sync();
     };
-    int m = 0;
+    int m = 0;              // records in the stage
+    bool once = true;       // it holds all of the tile's
     auto stage_one = [&](auto&& sc) {
         return [&, sc](bool v, float4 c) {
             const uint64_t bal = __ballot(v);
@@ -555,6 +561,7 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
             if (m + nn > kStage) {
                 sc(m);
                 m = 0;
+                once = false;
             }
             if (v) stage[m + __popcll(bal & lanemask_lt())] = c;
             m += nn;
@@ -571,13 +578,33 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
     int nearer = 0;
 #pragma unroll
     for (int q = 0; q < KMAX; ++q) nearer += (q < k && top[q] < tau);
-    bool settled = fin && tau <= rk2 && nearer == k - 1;
-    // second pass: the smallest index at exactly the k-th distance
-    float tmax = settled ? tau : 0.0f;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) tmax = fmaxf(tmax, __shfl_xor(tmax, d, kWave));
-    uint32_t jk = 0xFFFFFFFFu;
-    if (__any(settled)) {
+    // the smallest index at exactly the k-th distance, for the lanes that need
+    // it (others keep an index that nothing reads, and may share the distance)
+    const bool within = fin && tau <= rk2;
+    const bool needs = within && kb_nbins > 0 && kth_bin_fp32(tau, kb_nbins, kb_inv_w64) < 0;
+    const bool open = needs && nearer == k - 1;
+    bool settled = within && (open || !needs);
+    uint32_t jk = open ? 0xFFFFFFFFu : 0u;
+    if (once) {
+        for (uint64_t todo = __ballot(open); todo; todo &= todo - 1) {
+            const int ln = __builtin_ctzll(todo);
+            const uint32_t ti = readlane(i, ln);
+            const float tx = readlane(px, ln), ty = readlane(py, ln), tz = readlane(pz, ln), tt = readlane(tau, ln);
+            uint32_t best = 0xFFFFFFFFu;
+            for (int j0 = 0; j0 < m; j0 += kWave) {
+                const float4 c = stage[j0 + l < m ? j0 + l : j0];
+                const float dx = c.x - tx, dy = c.y - ty, dz = c.z - tz;
+                const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                const uint32_t cj = __builtin_bit_cast(uint32_t, c.w);
+                for (uint64_t hit = __ballot(j0 + l < m && d2 == tt && (!SELF || cj != ti)); hit; hit &= hit - 1) {
+                    const uint32_t cand = readlane(cj, __builtin_ctzll(hit));
+                    best = cand < best ? cand : best;
+                }
+            }
+            if (l == ln) jk = best;
+        }
+    } else if (__any(open)) {
+        const float tmax = wave_max_f(open ? tau : 0.0f);
         auto scan2 = [&](int mm) {
             wave_sync();
             for (int j = 0; j < mm; ++j) {
@@ -585,7 +612,7 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
                 const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;
                 const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
                 const uint32_t cj = __builtin_bit_cast(uint32_t, c.w);
-                const bool me = settled && (!SELF || cj != i);
+                const bool me = open && (!SELF || cj != i);
                 if (me && d2 == tau && cj < jk) jk = cj;
             }
             wave_sync();
@@ -615,12 +642,8 @@ __device__ __forceinline__ void flush_hist(uint32_t* hist_l, uint64_t* hist_g, i
 // the FP64 distance of the stored positions decides.
 __device__ __forceinline__ int key_bin(uint64_t key, const float* xyz, float px, float py, float pz,
                                        const double* KE2, int kb_nbins, double kb_inv_w64) {
-    const float t = __builtin_amdgcn_sqrtf(u2f((uint32_t)(key >> 32))) * (float)kb_inv_w64;
-    if (!(t < (float)kb_nbins + 2.0f)) return kb_nbins;
-    const float band = (float)fmin(0.25, fmax(1e-6 * kb_inv_w64, 4e-6 * (double)kb_nbins));
-    const int bf = (int)t;
-    const float fr = t - (float)bf;
-    if (fr > band && fr < 1.0f - band) return bf < kb_nbins ? bf : kb_nbins;
+    const int bf = kth_bin_fp32(u2f((uint32_t)(key >> 32)), kb_nbins, kb_inv_w64);
+    if (bf >= 0) return bf;
     const uint32_t j = (uint32_t)key;
     return exact_bin(exact_D2(px, py, pz, xyz[3 * (size_t)j], xyz[3 * (size_t)j + 1], xyz[3 * (size_t)j + 2]),
                      KE2, kb_nbins, kb_inv_w64);
