@@ -774,6 +774,21 @@ __global__ __launch_bounds__(kDsSmallBlock) void k_rs_downsweep_small(SortSet se
     downsweep_body<kDsSmallBlock, kDsSmallItems>(set);
 }
 
+// *sum += the workgroup's total of v, with one atomic per workgroup (atomics
+// on one address take about 16 ns each, one after the other: a wavefront's own
+// were 50 of k_order_gather's 67 us on 7.5e6 neighbours).  Every thread of the
+// workgroup calls it.
+__device__ __forceinline__ void add_block_sum(uint32_t* sum, uint32_t v) {
+    __shared__ uint32_t s_v[kWavesPerBlock];
+    v = wave_sum(v);
+    if (lane_id() == 0) s_v[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kWavesPerBlock; ++w) v += s_v[w];
+        if (v) atomicAdd(sum, v);
+    }
+}
+
 // ------------------------------------------------------------------------
 // 6. targets in cell order as SoA: rank, ion index, position
 // ------------------------------------------------------------------------
@@ -857,10 +872,7 @@ __device__ __forceinline__ void take_order(const OrderArgs& a, uint32_t bid, uin
             }
         }
     }
-    if (a.distinct) {
-        distinct = wave_sum(distinct);
-        if (lane_id() == 0 && distinct) atomicAdd(a.distinct, distinct);
-    }
+    if (a.distinct) add_block_sum(a.distinct, distinct);
 }
 
 // ------------------------------------------------------------------------
@@ -976,10 +988,7 @@ __device__ __forceinline__ void gather(const GatherArgs& a, uint32_t bid, uint32
                 for (uint32_t q = c + 1; q <= nc; ++q) a.cell_start[q] = nB;
         }
     }
-    if (a.distinct) {
-        distinct = wave_sum(distinct);
-        if (lane_id() == 0 && distinct) atomicAdd(a.distinct, distinct);
-    }
+    if (a.distinct) add_block_sum(a.distinct, distinct);
 }
 
 // ------------------------------------------------------------------------

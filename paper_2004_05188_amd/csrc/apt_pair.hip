@@ -172,7 +172,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
         const bool list = P.tile_mode != 0;
         pair_items<FLAGS, KNN>(a, P, T, list, !list, since_flush, flush_at);
     }
-    if (LDS_HIST) flush_hist(T.hist_l, a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
 // Mode 3 with the RDF one target per wavefront (tuning): the RDF of every
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_tgt(PairArgs a) {
     uint32_t since_flush = 0;
     const uint32_t flush_at = P.nB >= 0x7FFFFFFFu ? 0u : 0xFFFFFFFFu - P.nB;
     pair_items<FLAGS, false>(a, P, T, false, true, since_flush, flush_at);
-    if (LDS_HIST) flush_hist(T.hist_l, a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
 template __global__ void k_rdf_tgt<kRdfLds>(PairArgs);
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
         }
     }
     }
-    if (LDS_HIST) flush_hist(T.hist_l, a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
 // ---------------------------------------------------- neighbour-major RDF --
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
         }
     }
     }
-    if (LDS_HIST) flush_hist(hist_l, a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins + 1), a.hist, a.n_bins);
     if (COUNT && l == 0 && evals) atomicAdd((unsigned long long*)a.hist, evals);
 }
 
@@ -598,10 +598,16 @@ __global__ __launch_bounds__(kBlock) void k_nbr_self(PairArgs a) {
         if (!(isfinite(a.tx[q]) && isfinite(a.ty[q]) && isfinite(a.tz[q]))) continue;
         if (a.nbr_species == APT_ANY || (int)a.lab[a.t_id[q]] == a.nbr_species) ++cnt;
     }
+    // (one atomic per workgroup: they run one after the other)
+    __shared__ uint32_t s_cnt;
+    if (threadIdx.x == 0) s_cnt = 0;
+    __syncthreads();
     cnt = wave_sum(cnt);
+    if (lane_id() == 0 && cnt) atomicAdd(&s_cnt, cnt);
+    __syncthreads();
     // (u64 arithmetic modulo 2^64: the order of this and the kernel's adds
     // does not matter)
-    if (lane_id() == 0 && cnt) atomicAdd((unsigned long long*)a.hist, 0ull - (unsigned long long)cnt);
+    if (threadIdx.x == 0 && s_cnt) atomicAdd((unsigned long long*)a.hist, 0ull - (unsigned long long)s_cnt);
 }
 template __global__ void k_rdf_nbr<kRdfGlobal | kCountEvals>(PairArgs);
 
