@@ -321,9 +321,15 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
         }
         uint32_t hits = 0;
         TopK<KMAX> top;
+        bool unsure = false;
         // mode 3: the kNN only (the one-per-wavefront pass counts the RDF)
         if (P.tile_mode >= 2) run_lane<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, top, hits, P.tile_mode == 2);
-        else run_tile<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, stage, top, hits);
+        else if constexpr (KMAX > 0) {
+            if (!run_tile_packed<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, top, hits, &unsure))
+                run_tile<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, stage, top, hits);
+        } else {
+            run_tile<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, stage, top, hits);
+        }
         if (KMAX > 0) {
             // certified: k keys within Rk, or the radius already is r_knn_max
             uint64_t kth = top.key[0];
@@ -331,7 +337,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
             for (int q = 1; q < KMAX; ++q)
                 if (q == a.k - 1) kth = top.key[q];
             const bool fin = isfinite(px) && isfinite(py) && isfinite(pz);
-            const bool done = valid && (kth != ~0ull || Rk >= a.rknn || !fin);
+            const bool done = valid && !unsure && (kth != ~0ull || Rk >= a.rknn || !fin);
             if (valid && !done) {
                 const uint64_t m = __ballot(true);
                 uint32_t base = 0;
