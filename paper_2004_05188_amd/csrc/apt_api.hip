@@ -244,7 +244,7 @@ static PlainWs carve_plain(void* base, int64_t n) {
     w.bpos = c.take<float4>(N);
     w.cell_start = c.take<uint32_t>((size_t)cell_cap_for(n) + 1);
     w.strag = c.take<uint32_t>(N);
-    w.strag_count = c.take<uint32_t>(64);
+    w.strag_count = c.take<uint32_t>(64 + 2 * kXcd * kWorkStride);   // [0], [3] stragglers, [1..2] occupied cells, [64..] work queues
     w.t_cell_start = c.take<uint32_t>((size_t)cell_cap_for(n) + 1);
     w.bytes = c.off;
     return w;
@@ -555,7 +555,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
                 knn_hist ? kb->n_bins + 1 : 0, n_targets, w.strag_count,
                 do_rdf ? w.E2 : nullptr, do_rdf ? rb->r_max : 0.0f, do_rdf ? rb->n_bins : 0,
                 knn_hist ? w.KE2 : nullptr, knn_hist ? kb->r_max : 0.0f, knn_hist ? kb->n_bins : 0};
-    ia.work_q = w.strag_count + 8;
+    ia.work_q = w.strag_count + 64;
     // (zeroed and filled by the binning's first kernel)
 
     const apt_tuning tu = tuning();
@@ -590,7 +590,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
             ca.t_id = w.t_id;
             ca.bpos = w.bpos;
             ca.t_cell_start = w.t_cell_start;
-            ca.work_q = w.strag_count + 8;
+            ca.work_q = w.strag_count + 64;
             ca.r_enum = (float)((double)rb->r_max * (1.0 + 4e-5));
             ca.hist = cand;
             ca.n_bins = 1;
@@ -656,7 +656,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     pa.strag = w.strag;
     pa.strag_count = w.strag_count;
     pa.t_cell_start = w.t_cell_start;
-    pa.work_q = w.strag_count + 8;
+    pa.work_q = w.strag_count + 64;
     // the kNN radii from the occupied cells that the binning counted
     pa.occ = do_knn ? w.strag_count + 1 : nullptr;
     pa.n_targets = do_knn ? n_targets : nullptr;

@@ -249,8 +249,15 @@ __device__ __forceinline__ bool next_work(uint64_t* queue, uint64_t total, uint3
     while (empty < kXcd) {
         const uint64_t g0 = total * (uint64_t)x / kXcd, g1 = total * (uint64_t)(x + 1) / kXcd;
         uint64_t c = 0;
-        if (lane_id() == 0)
-            c = atomicAdd((unsigned long long*)&queue[x * kQueueStride], (unsigned long long)batch);
+        if (lane_id() == 0) {
+            // (others' queues are read first: every wavefront passes every
+            // queue at the end)
+            uint64_t* q = queue + x * kQueueStride;
+            if (empty == 0 || __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < g1 - g0)
+                c = atomicAdd((unsigned long long*)q, (unsigned long long)batch);
+            else
+                c = g1 - g0;
+        }
         // broadcast as a wave-uniform value
         c = g0 + (((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32)) << 32) |
                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c));
@@ -430,18 +437,27 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
             d_srf = bp.d_srf;
         }
         const uint64_t slot = (g - a.titems[rp]) * kWave + (uint64_t)l;
-        bool valid = slot < seg_len;
+        bool valid0 = slot < seg_len;
         uint32_t i = 0;
         float px = 0.0f, py = 0.0f, pz = 0.0f;
-        if (valid) {
+        if (valid0) {
             const float4 rec = a.Pp[seg_a0 + slot];
             i = __builtin_bit_cast(uint32_t, rec.w);
             px = rec.x;
             py = rec.y;
             pz = rec.z;
-            valid = a.d_bnd == nullptr || a.d_bnd[i] >= d_srf;
+            valid0 = a.d_bnd == nullptr || a.d_bnd[i] >= d_srf;
         }
         uint32_t hits = 0;
+        // (cell order: a tile that runs over the end of a row of cells is
+        // taken a row at a time, or its box would span the specimen)
+        const uint32_t row = isfinite(py + pz) ? (uint32_t)cell_axis(P, 2, pz) * (uint32_t)P.dim[1] +
+                                                     (uint32_t)cell_axis(P, 1, py)
+                                               : 0u;
+        uint64_t todo = __ballot(valid0);
+        while (todo) {
+        const bool valid = valid0 && row == readlane(row, __builtin_ctzll(todo));
+        todo &= ~__ballot(valid);
         const uint64_t kth = run_tile_kth<kRdfLds | kSelf, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, hits,
                                                                  a.knn_hist ? a.kb_nbins : 0, a.kb_inv_w64);
         const bool fin = isfinite(px) && isfinite(py) && isfinite(pz);
@@ -470,6 +486,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
                 atomicAdd((unsigned long long*)&kh[b], 1ull);
             }
             wave_sync();
+        }
         }
         since_flush += wave_sum(hits);
         if (since_flush >= 0x7FFFFFFFu - (uint32_t)min((uint64_t)a.n * kWave, (uint64_t)0x7FFFFFFFu)) {

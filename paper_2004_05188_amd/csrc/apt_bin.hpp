@@ -57,7 +57,7 @@ struct InitArgs {
     uint64_t* h2;
     int32_t n2;
     int64_t* n_targets;
-    uint32_t* counter;      // [4]: [0] stragglers, [1..2] occupied cells
+    uint32_t* counter;      // [4]: [0] and [3] stragglers, [1..2] occupied cells
     // squared bin edges of the RDF and of the k-th distance histogram, or NULL
     double* e2;
     float e2_rmax;
@@ -65,7 +65,7 @@ struct InitArgs {
     double* ke2;
     float ke2_rmax;
     int32_t ke2_nbins;
-    uint32_t* work_q = nullptr;   // [2 kXcd] per-XCD work counters of the pair kernels, or NULL
+    uint32_t* work_q = nullptr;   // [2][kXcd] work counters of the pair kernels, kWorkStride apart, or NULL
     uint32_t* zero[2] = {nullptr, nullptr};   // [n_zero] the counting sort's counters, or NULL
     uint32_t n_zero = 0;
 };
@@ -82,7 +82,7 @@ __device__ inline void init_body(const InitArgs& a, int t, int st) {
         if (a.counter)
             for (int c = 0; c < 4; ++c) a.counter[c] = 0;
         if (a.work_q)
-            for (int c = 0; c < 2 * kXcd; ++c) a.work_q[c] = 0;
+            for (int c = 0; c < 2 * kXcd; ++c) a.work_q[c * kWorkStride] = 0;
     }
     if (a.h1)
         for (int b = t; b < a.n1; b += st) a.h1[b] = 0;

@@ -14,6 +14,7 @@ constexpr int kBlock = 256;                 // 4 wavefronts per workgroup
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kXcd = 8;                      // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr uint32_t kNone = 0xFFFFFFFFu;
+constexpr int kWorkStride = 32;              // u32 between per-XCD work counters: a cache line each
 
 // Device-resident description of the cell grid of one call, written by
 // k_plan and read by every later kernel (launch grids do not depend on it).
@@ -144,15 +145,27 @@ __device__ __forceinline__ uint32_t cell_id(const GridPlan& P, float x, float y,
 }
 
 // Sort key of a target: its cell in block-raster order (blocks of 8^3 cells
-// in raster order, cells in raster order inside a block), so that any run
-// of consecutive targets is a compact region of space; plain cell order
+// in raster order, the cells of a block along a path that turns back at each
+// row's and layer's end), so that any run of consecutive targets of a block
+// is a compact region of space (with rows all in one direction, a 64-target
+// tile in twelve stretched over a whole row of the block); plain cell order
 // when the plan chose tblock = 1.
 __device__ __forceinline__ uint32_t target_key(const GridPlan& P, float x, float y, float z) {
     const uint32_t cx = (uint32_t)cell_axis(P, 0, x), cy = (uint32_t)cell_axis(P, 1, y),
                    cz = (uint32_t)cell_axis(P, 2, z);
     if (P.tblock == 1) return (cz * (uint32_t)P.dim[1] + cy) * (uint32_t)P.dim[0] + cx;
     const uint32_t blk = ((cz >> 3) * (uint32_t)P.nby + (cy >> 3)) * (uint32_t)P.nbx + (cx >> 3);
-    return (blk << 9) | ((cz & 7u) << 6) | ((cy & 7u) << 3) | (cx & 7u);
+    const uint32_t py = (cy ^ ((cz & 1u) ? 7u : 0u)) & 7u, px = (cx ^ ((py & 1u) ? 7u : 0u)) & 7u;
+    return (blk << 9) | ((cz & 7u) << 6) | (py << 3) | px;
+}
+
+// Consecutive targets with the same value lie close together: a block of the
+// order above, or a row of cells in plain cell order.
+__device__ __forceinline__ uint32_t target_region(const GridPlan& P, float x, float y, float z) {
+    const uint32_t cx = (uint32_t)cell_axis(P, 0, x), cy = (uint32_t)cell_axis(P, 1, y),
+                   cz = (uint32_t)cell_axis(P, 2, z);
+    if (P.tblock == 1) return cz * (uint32_t)P.dim[1] + cy;
+    return ((cz >> 3) * (uint32_t)P.nby + (cy >> 3)) * (uint32_t)P.nbx + (cx >> 3);
 }
 
 // ------------------------------------------------------- exact binning --

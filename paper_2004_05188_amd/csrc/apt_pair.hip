@@ -33,17 +33,18 @@ size_t pair_lds_bytes(bool rdf, bool knn, int n_bins, bool hist_in_lds) {
     return b;
 }
 
-// Targets [t0, t1) of this XCD's share of a list of n_items (the eligible
-// targets in cell order, or the straggler list when `list`), one per
-// wavefront: RDF counts (rdf_on) and kNN rows (KNN).
+// Targets [t0, t1) of this XCD's share of n_items (list 0: the eligible
+// targets in cell order; the tile pass's lists: 1 targets whose kNN it could
+// not certify, 2 targets it left altogether), one per wavefront: RDF counts
+// (rdf_on) and kNN rows (KNN).
 template <int FLAGS, bool KNN>
-__device__ __forceinline__ void pair_items(const PairArgs& a, const GridPlan& P, PairTask& T, bool list,
+__device__ __forceinline__ void pair_items(const PairArgs& a, const GridPlan& P, PairTask& T, int list,
                                            bool rdf_on, uint32_t& since_flush, uint32_t flush_at) {
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int l = lane_id();
-    const uint32_t n_items = list ? *a.strag_count : P.nT;
-    auto slot_of = [&](uint32_t s) { return list ? a.strag[s] : s; };
+    const uint32_t n_items = list == 1 ? a.strag_count[0] : list == 2 ? a.strag_count[3] : P.nT;
+    auto slot_of = [&](uint32_t s) { return list == 1 ? a.strag[s] : list == 2 ? a.strag[P.nT - 1u - s] : s; };
 
     // XCD-aware deal: XCD x takes the x-th eighth of the items in cell order
     // (the grid is a multiple of kXcd workgroups)
@@ -160,18 +161,13 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
 
     uint32_t since_flush = 0;      // hits counted into hist_l since its last flush (wave total)
     const uint32_t flush_at = P.nB >= 0x7FFFFFFFu ? 0u : 0xFFFFFFFFu - P.nB;
-    if (P.tile_mode == 3) {
-        // the neighbour-major kernel counts the RDF and the lane pass found
-        // the kNN of most targets: the kNN of the targets it left in the list
-        (void)RDF_T;
-        if (KNN) pair_items<FLAGS, KNN>(a, P, T, true, false, since_flush, flush_at);
-    } else {
-        // In tile mode the tile pass already counted the RDF of every target
-        // and left the targets whose kNN it could not certify in a list: this
-        // pass finishes their kNN only.
-        const bool list = P.tile_mode != 0;
-        pair_items<FLAGS, KNN>(a, P, T, list, !list, since_flush, flush_at);
-    }
+    // In a tile mode the tile pass (mode 3: the neighbour-major kernel) counted
+    // the RDF and left the targets whose kNN it could not certify in a list;
+    // tiles with too many candidates in another, which needs both.
+    (void)RDF_T;
+    if (KNN || P.tile_mode == 0)
+        for (int list = P.tile_mode != 0; list <= (P.tile_mode == 1 ? 2 : P.tile_mode != 0); ++list)
+            pair_items<FLAGS, KNN>(a, P, T, list, list != 1, since_flush, flush_at);
     if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
@@ -210,7 +206,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_tgt(PairArgs a) {
     wave_sync();
     uint32_t since_flush = 0;
     const uint32_t flush_at = P.nB >= 0x7FFFFFFFu ? 0u : 0xFFFFFFFFu - P.nB;
-    pair_items<FLAGS, false>(a, P, T, false, true, since_flush, flush_at);
+    pair_items<FLAGS, false>(a, P, T, 0, true, since_flush, flush_at);
     if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
@@ -291,28 +287,21 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
     wave_sync();
     const float Rk = KMAX > 0 ? fminf(P.rk_tile, a.rknn) : 0.0f;
 
-    // XCD-aware work queue over tiles (cell order): each XCD takes one
-    // eighth of them, its wavefronts take batches of consecutive tiles from
-    // the XCD's counter, so the tiles in flight stay one compact region
+    // work queues over tiles (cell order), an eighth per XCD
     const uint32_t n_tiles = (P.nT + kWave - 1) / kWave;
-    const int xcd = blockIdx.x % kXcd;
-    const uint32_t g0 = (uint32_t)((uint64_t)n_tiles * (uint64_t)xcd / kXcd);
-    const uint32_t g1 = (uint32_t)((uint64_t)n_tiles * (uint64_t)(xcd + 1) / kXcd);
     constexpr uint32_t kBatch = 4;
     uint32_t since_flush = 0;
     const uint32_t flush_at = P.nB >= 0x7FFFFFFFu / kWave ? 0u : 0xFFFFFFFFu - P.nB * kWave;
-    for (;;) {
-    uint32_t gb = 0;
-    if (l == 0) gb = atomicAdd(a.work_q + kXcd + xcd, kBatch);
-    gb = g0 + (uint32_t)__shfl((int)gb, 0, kWave);
-    if (gb >= g1) break;
-    const uint32_t ge = gb + kBatch < g1 ? gb + kBatch : g1;
-    for (uint32_t g = gb; g < ge; ++g) {
+    int x = blockIdx.x % kXcd, empty = 0;
+    uint32_t gb, ge;
+    while (next_batch(a.work_q + kXcd * kWorkStride, n_tiles, 0, kBatch, x, empty, &gb, &ge)) {
+    const uint32_t g0 = (uint32_t)((uint64_t)n_tiles * (uint64_t)x / kXcd);
+    for (uint32_t g = g0 + gb; g < g0 + ge; ++g) {
         const uint32_t slot = g * kWave + (uint32_t)l;
-        const bool valid = slot < P.nT;
+        const bool valid0 = slot < P.nT;
         uint32_t rank = 0, i = 0;
         float px = 0.0f, py = 0.0f, pz = 0.0f;
-        if (valid) {
+        if (valid0) {
             rank = a.t_rank[slot];
             i = a.t_id[slot];
             px = a.tx[slot];
@@ -320,15 +309,33 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
             pz = a.tz[slot];
         }
         uint32_t hits = 0;
+        // a tile that runs from one region of the order into the next is
+        // taken a region at a time: its box, and with it the candidates of
+        // every lane, would span both (a few such tiles, with thousands of
+        // candidates from one side of the specimen to the other, ran on for a
+        // third of the launch after all others)
+        const uint32_t region = P.tile_mode == 1 && isfinite(px + py + pz) ? target_region(P, px, py, pz) : 0u;
+        uint64_t todo = __ballot(valid0);
+        while (todo) {
+        const bool valid = valid0 && region == readlane(region, __builtin_ctzll(todo));
+        todo &= ~__ballot(valid);
         TopK<KMAX> top;
         bool unsure = false;
         // mode 3: the kNN only (the one-per-wavefront pass counts the RDF)
         if (P.tile_mode >= 2) run_lane<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, top, hits, P.tile_mode == 2);
         else if constexpr (KMAX > 0) {
-            if (!run_tile_packed<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, top, hits, &unsure))
-                run_tile<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, stage, top, hits);
+            if (!run_tile_packed<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, top, hits, &unsure)) {
+                // too many candidates: RDF and kNN one target at a time (the
+                // list's other end)
+                const uint64_t m = __ballot(valid);
+                uint32_t base = 0;
+                if (l == 0) base = atomicAdd(a.strag_count + 3, (uint32_t)__popcll(m));
+                base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+                if (valid) a.strag[P.nT - 1u - (base + (uint32_t)__popcll(m & lanemask_lt()))] = slot;
+                continue;
+            }
         } else {
-            run_tile<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, stage, top, hits);
+            run_tile<FLAGS>(P, T, valid, px, py, pz, i, stage, hits);
         }
         if (KMAX > 0) {
             // certified: k keys within Rk, or the radius already is r_knn_max
@@ -372,6 +379,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
                     atomicAdd((unsigned long long*)&a.knn_hist[b], 1ull);
                 }
             }
+        }
         }
         if (LDS_HIST) {
             since_flush += wave_sum(hits);
@@ -430,20 +438,17 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     // eighth of the chunks, and its wavefronts take batches of consecutive
     // chunks from the XCD's counter, so that the chunks in flight on an XCD
     // stay one compact region whose target rows its L2 keeps (a static deal
-    // lets the wavefronts drift apart).  (workgroup b runs on XCD b mod 8)
-    // The batches are cut to leave every wavefront several of them, and a
+    // lets the wavefronts drift apart; next_batch).  (workgroup b runs on XCD b
+    // mod 8)  The batches are cut to leave every wavefront several of them, and a
     // cloud with fewer chunks than that splits each chunk's targets into
     // `split` items: 1e6 ions, every ion against every ion, are 15 600 chunks,
     // which in batches of 16 kept 977 of 8192 wavefronts busy (the call 8.71 ms,
     // now 2.01 ms).  2^32 - 1 neighbours are 6.7e7 items at most.
-    const int xcd = blockIdx.x % kXcd;
-    const uint32_t c0 = (uint32_t)((uint64_t)n_chunks * (uint64_t)xcd / kXcd);
-    const uint32_t n_own = (uint32_t)((uint64_t)n_chunks * (uint64_t)(xcd + 1) / kXcd) - c0;
-    const uint32_t n_waves = gridDim.x / kXcd * kWavesPerBlock;   // of this XCD
+    const uint32_t n_own = (n_chunks + kXcd - 1) / kXcd;          // of an XCD
+    const uint32_t n_waves = gridDim.x / kXcd * kWavesPerBlock;   // of an XCD
     uint32_t lg_split = 0;
     while (lg_split < 3 && ((uint64_t)n_own << lg_split) < 4ull * n_waves) ++lg_split;
-    const uint64_t n_items = (uint64_t)n_own << lg_split;
-    const uint32_t per_wave = (uint32_t)(n_items / (8ull * n_waves));
+    const uint32_t per_wave = (uint32_t)(((uint64_t)n_own << lg_split) / (8ull * n_waves));
     const uint32_t batch = per_wave < 1u ? 1u : per_wave > 16u ? 16u : per_wave;
     const float Re = a.r_enum + P.eps;
     const float R2 = Re * Re;
@@ -452,12 +457,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     uint32_t since_flush = 0;
     const uint32_t flush_at = 0xFFFFFFFFu - (uint32_t)(kWave * kNbrList);
 
-    for (;;) {
-    uint32_t ib = 0;
-    if (l == 0) ib = atomicAdd(a.work_q + xcd, batch);
-    ib = (uint32_t)__shfl((int)ib, 0, kWave);
-    if (ib >= n_items) break;
-    const uint32_t ie = ib + batch < n_items ? ib + batch : (uint32_t)n_items;
+    int x = blockIdx.x % kXcd, empty = 0;
+    uint32_t ib, ie;
+    while (next_batch(a.work_q, n_chunks, lg_split, batch, x, empty, &ib, &ie)) {
+    const uint32_t c0 = (uint32_t)((uint64_t)n_chunks * (uint64_t)x / kXcd);
     for (uint32_t item = ib; item < ie; ++item) {
         const uint32_t c = c0 + (item >> lg_split);
         const uint32_t part = item & ((1u << lg_split) - 1u);   // of the chunk's targets

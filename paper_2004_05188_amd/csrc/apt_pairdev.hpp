@@ -10,6 +10,39 @@ namespace apt {
 __device__ __forceinline__ uint32_t f2u(float f) { return __builtin_bit_cast(uint32_t, f); }
 __device__ __forceinline__ float u2f(uint32_t u) { return __builtin_bit_cast(float, u); }
 
+// The next batch of a wavefront's work: items [*i0, *i1) of queue *x, which
+// holds 2^lg items for each of [n x / kXcd, n (x + 1) / kXcd).  A wavefront
+// takes from its own XCD's queue (consecutive items: a compact region, whose
+// records its L2 keeps) and, once that is empty, from the others', starting
+// with `x` = its XCD and `empty` = 0; false when all are empty.  The XCDs'
+// eighths are equal in number, not in work: without the second part the
+// first XCDs to finish waited for a third of the dense-target tile kernel's
+// time (7.7e6-ion needle).  (Another queue is read before its counter is
+// added to: every wavefront passes every queue at the end, and atomics on one
+// address take about 16 ns each.)
+__device__ __forceinline__ bool next_batch(uint32_t* queue, uint32_t n, uint32_t lg, uint32_t batch, int& x,
+                                           int& empty, uint32_t* i0, uint32_t* i1) {
+    for (; empty < kXcd; ++empty, x = x + 1 < kXcd ? x + 1 : 0) {
+        const uint32_t first = (uint32_t)((uint64_t)n * (uint64_t)x / kXcd);
+        const uint32_t own = ((uint32_t)((uint64_t)n * (uint64_t)(x + 1) / kXcd) - first) << lg;
+        uint32_t* q = queue + x * kWorkStride;
+        uint32_t c = 0;
+        if (lane_id() == 0) {
+            if (empty == 0 || __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < own)
+                c = atomicAdd(q, batch);
+            else
+                c = own;
+        }
+        c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+        if (c < own) {
+            *i0 = c;
+            *i1 = own - c > batch ? c + batch : own;
+            return true;
+        }
+    }
+    return false;
+}
+
 // Ascending sort of buf[0..c) by one wavefront; c <= kKnnCap.  Up to 64
 // keys: each lane takes one key and counts the smaller ones (equal ones by
 // position), broadcast lane by lane (no LDS round trips); beyond: a bitonic
@@ -310,9 +343,8 @@ __device__ __forceinline__ int kth_bin_fp32(float d2, int kb_nbins, double kb_in
 
 // 64 targets per wavefront, one per lane: the neighbour records within R of
 // the targets' bounding box are staged through LDS in chunks, and every lane
-// scans them for its own target, keeping its KMAX smallest kNN keys (FP32
-// squared distance, index) in registers.  Used when targets are dense, so
-// that the 64 targets of a tile are close together.
+// scans them for its own target.  Used when targets are dense, so that the
+// 64 targets of a tile are close together.
 constexpr int kStage = 512;   // records per staging chunk (16 B each)
 
 template <int KMAX>
@@ -320,44 +352,24 @@ struct TopK {
     uint64_t key[KMAX > 0 ? KMAX : 1];
 };
 
-// Returns this lane's number of kNN keys with d2 <= Rk^2 (0 when KMAX == 0).
-template <int FLAGS, int KMAX>
-__device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, bool valid, float px, float py,
-                                         float pz, uint32_t i, float Rk, float4* stage, TopK<KMAX>& top,
-                                         uint32_t& hits) {
-    constexpr bool RDF = (FLAGS & (kRdfLds | kRdfGlobal)) != 0;
+// RDF only, with any number of records.
+template <int FLAGS>
+__device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, bool valid, float px, float py, float pz,
+                                         uint32_t i, float4* stage, uint32_t& hits) {
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
     constexpr bool SELF = (FLAGS & kSelf) != 0;
-    const int l = lane_id();
-#pragma unroll
-    for (int m = 0; m < (KMAX > 0 ? KMAX : 1); ++m) top.key[m] = ~0ull;
     const bool fin = valid && isfinite(px) && isfinite(py) && isfinite(pz);
-    float x0 = fin ? px : INFINITY, y0 = fin ? py : INFINITY, z0 = fin ? pz : INFINITY;
-    float x1 = fin ? px : -INFINITY, y1 = fin ? py : -INFINITY, z1 = fin ? pz : -INFINITY;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        x0 = fminf(x0, __shfl_xor(x0, d, kWave));
-        y0 = fminf(y0, __shfl_xor(y0, d, kWave));
-        z0 = fminf(z0, __shfl_xor(z0, d, kWave));
-        x1 = fmaxf(x1, __shfl_xor(x1, d, kWave));
-        y1 = fmaxf(y1, __shfl_xor(y1, d, kWave));
-        z1 = fmaxf(z1, __shfl_xor(z1, d, kWave));
-    }
     if (!__any(fin)) return;
-    const float rk2 = Rk * Rk;
-    float R = 0.0f;
-    if (RDF) R = T.r_enum;
-    if (KMAX > 0) R = fmaxf(R, Rk * 1.000001f);
-
+    const float x0 = wave_min_f(fin ? px : INFINITY), x1 = wave_max_f(fin ? px : -INFINITY);
+    const float y0 = wave_min_f(fin ? py : INFINITY), y1 = wave_max_f(fin ? py : -INFINITY);
+    const float z0 = wave_min_f(fin ? pz : INFINITY), z1 = wave_max_f(fin ? pz : -INFINITY);
     auto scan = [&](int m) {
         wave_sync();
         for (int j = 0; j < m; ++j) {
             const float4 c = stage[j];
             const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;
             const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-            const uint32_t cj = __builtin_bit_cast(uint32_t, c.w);
-            const bool me = fin && (!SELF || cj != i);
-            if (RDF && me && d2 < T.thr2) {
+            if (fin && (!SELF || __builtin_bit_cast(uint32_t, c.w) != i) && d2 < T.thr2) {
                 const float t = __builtin_amdgcn_sqrtf(d2) * T.inv_w;
                 int b = (int)t;
                 const float fr = t - (float)b;
@@ -369,26 +381,11 @@ __device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, b
                     ++hits;
                 }
             }
-            if (KMAX > 0) {
-                const uint64_t key = ((uint64_t)__builtin_bit_cast(uint32_t, d2) << 32) | (uint64_t)cj;
-                if (me && d2 <= rk2 && key < top.key[KMAX - 1]) {
-                    // insert, keeping the keys ascending
-                    uint64_t x = key;
-#pragma unroll
-                    for (int q = 0; q < KMAX; ++q) {
-                        const uint64_t lo = x < top.key[q] ? x : top.key[q];
-                        const uint64_t hi = x < top.key[q] ? top.key[q] : x;
-                        top.key[q] = lo;
-                        x = hi;
-                    }
-                }
-            }
         }
         wave_sync();
     };
-
     int m = 0;   // staged records
-    enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, R, [&](bool v, float4 c) {
+    enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, T.r_enum, [&](bool v, float4 c) {
         const uint64_t bal = __ballot(v);
         const int nn = __popcll(bal);
         if (m + nn > kStage) {
@@ -397,12 +394,11 @@ __device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, b
         }
         if (v) stage[m + __popcll(bal & lanemask_lt())] = c;
         m += nn;
-    }, KMAX > 0);
+    });
     if (m > 0) scan(m);
-    (void)l;
 }
 
-// As run_tile for kNN keys, with the records of a tile in the stage at once:
+// RDF and kNN keys, with the records of a tile in the stage at once:
 // the scan keeps KMAX + 2 values per lane, each the squared distance's bits
 // with the lowest kSlotBits replaced by the record's place in the stage, as
 // floats in ascending order (one median per place); afterwards the KMAX + 2
@@ -410,10 +406,10 @@ __device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, b
 // unless a record left out could tie: its value, so its distance rounded
 // down, is at least the last one kept.  Keeping the 64-bit keys themselves in
 // order cost a 64-bit comparison and four selects per place and candidate
-// (7.5e6 dense targets, k = 10: 2.64 ms, now 2.54, most of it the k-th histogram's atomics).
+// (7.5e6 dense targets, k = 10: 2.64 ms, now 1.56 with the tiles cut at regions).
 // Returns false, with nothing counted, when the stage cannot hold the tile's
-// records (the caller runs run_tile); *unsure: this lane's rows may miss a
-// tie and have to be searched again.
+// records (the caller leaves its targets to the one-by-one pass); *unsure:
+// this lane's rows may miss a tie and have to be searched again.
 constexpr int kSlotBits = 9;
 static_assert((1 << kSlotBits) == kStage, "a stage place per slot");
 
@@ -452,8 +448,10 @@ __device__ __forceinline__ bool run_tile_packed(const GridPlan& P, const PairTas
     float kept[S];
 #pragma unroll
     for (int q = 0; q < S; ++q) kept[q] = none;
+    float4 next = stage[0];
     for (int j = 0; j < m; ++j) {
-        const float4 c = stage[j];
+        const float4 c = next;
+        next = stage[j + 1 < m ? j + 1 : j];
         const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;
         const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
         const bool me = fin && (!SELF || __builtin_bit_cast(uint32_t, c.w) != i);
@@ -636,8 +634,10 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
 
     auto scan = [&](int m) {
         wave_sync();
+        float4 next = stage[0];
         for (int j = 0; j < m; ++j) {
-            const float4 c = stage[j];
+            const float4 c = next;
+            next = stage[j + 1 < m ? j + 1 : j];
             const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;
             const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
             const uint32_t cj = __builtin_bit_cast(uint32_t, c.w);

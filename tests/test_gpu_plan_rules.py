@@ -108,3 +108,35 @@ def test_counting_sort_sizes(orc, n):
         assert np.allclose(gd, dist, rtol=1e-6, atol=0)
         assert np.array_equal(g.knn_hist.cpu().numpy().astype(np.uint64), h)
         assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, A, B, 0.25, 2.0, 100))
+
+
+@pytest.mark.parametrize("blob", [300, 511, 512, 513, 3000])
+def test_tiles_with_many_candidates(orc, blob):
+    """Dense targets around a tight ball of `blob` neighbours: tiles just inside and beyond what a stage of 512
+    records holds (beyond, their targets are left to the one-by-one pass with RDF and kNN), against the oracle."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    print(f"case tile candidates blob={blob}", flush=True)
+    rng = np.random.default_rng(blob)
+    n = 120_000
+    L = 16.0
+    xyz = (rng.random((n, 3)) * L).astype(np.float32)
+    lab = (rng.random(n) < 0.002).astype(np.uint8)
+    xyz[:blob] = (L / 2 + 0.2 * rng.standard_normal((blob, 3))).astype(np.float32)
+    lab[:blob] = 1
+    d = np.full(n, 5.0, np.float32)
+    cloud = aptstat.Cloud(*(torch.from_numpy(v).cuda() for v in (xyz, lab, d)))
+    for k in (3, 10, 16):
+        aptstat.set_tuning(tile_policy=2)
+        try:
+            g = aptstat.knn_rdf(cloud, 0, 1, 1.0, k, r_max=2.0, n_bins=100, kb_nbins=500)
+        finally:
+            aptstat.set_tuning()
+        t, dist, nid, h = orc.knn(xyz, lab, d, 0, 1, 1.0, k, kb_rmax=5.0, kb_nbins=500)
+        tid, gd, gn = (v.cpu().numpy() for v in g.trimmed())
+        assert np.array_equal(tid, t) and np.array_equal(gn, nid)
+        assert np.allclose(gd, dist, rtol=1e-6, atol=0)
+        assert np.array_equal(g.knn_hist.cpu().numpy().astype(np.uint64), h)
+        assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, 0, 1, 1.0, 2.0, 100))
