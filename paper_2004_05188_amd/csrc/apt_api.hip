@@ -147,16 +147,21 @@ constexpr size_t kMaxLds = 64u * 1024u;
 // ------------------------------------------------------------ sizing --
 constexpr int kCountTile = 4096;
 
-constexpr int kMaxCountBlocks = 2048;
-static int count_blocks(int64_t n) {
-    int64_t g = (n + kCountTile - 1) / kCountTile;
-    if (g < 1) g = 1;
-    if (g > kMaxCountBlocks) g = kMaxCountBlocks;
-    return (int)g;
+// The chunks of the counting and compacting kernels: whole tiles of 4096
+// ions; clouds with fewer than 512 such tiles are spread over up to 512
+// workgroups in steps of 256 ions (12 000 ions on 3 workgroups of 4096 took
+// k_count 9 and k_compact 21 us, each ion's dependent loads one after the
+// other; on 47 of 256 they take 4 and 11).
+constexpr int kMaxCountBlocks = 2048, kSpreadBlocks = 512;
+static int64_t count_chunk(int64_t n) {
+    const bool spread = n < (int64_t)kSpreadBlocks * kCountTile;
+    const int64_t step = spread ? kBlock : kCountTile, most = spread ? kSpreadBlocks : kMaxCountBlocks;
+    const int64_t c = (n + most - 1) / most;
+    return std::max<int64_t>((c + step - 1) / step * step, step);
 }
-static int64_t count_chunk(int64_t n, int G) {
-    int64_t c = (n + G - 1) / G;
-    return (c + kCountTile - 1) / kCountTile * kCountTile;
+static int count_blocks(int64_t n) {
+    const int64_t c = count_chunk(n);
+    return (int)std::max<int64_t>((n + c - 1) / c, 1);
 }
 static uint32_t cell_cap_for(int64_t n) {
     int64_t c = n / 2;
@@ -435,7 +440,7 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
                               int sel_union = 0, const InitArgs* init = nullptr) {
     const int64_t n = cl->n;
     const int G = count_blocks(n);
-    const int64_t chunk = count_chunk(n, G);
+    const int64_t chunk = count_chunk(n);
     const int cus = device_info().cus;
     // (the smoothed RDF adds in the order of the records, which has to be the
     // same from run to run: it passes no `init` and keeps the stable sort)
@@ -572,6 +577,16 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     pp.r_enum = do_rdf ? rb->r_max : 0.0f;
     pp.h_shrink = 0.7f;
     pp.rdf_kernel = tu.rdf_kernel;
+    // kernels that the plan cannot choose for a cloud of this size are not
+    // launched (about 4 us each, even to exit at once)
+    if (pp.tile_policy == 0) {
+        // (one species against every ion: as many targets as neighbours only
+        // if there is no other species)
+        if (cl->n < (do_knn ? kTileMinKnn : kTileMinRdf) || (q.neighbor == APT_ANY && q.target != APT_ANY))
+            pp.no_tiles = 1;
+        if (cl->n < (do_knn ? kNbrMinKnn : kNbrMinRdf)) pp.no_nbr = 1;
+        if (pp.no_tiles && pp.no_nbr) pp.tile_policy = 1;
+    }
     {
         TraceSpan span("binning", st);
         if ((s = run_binning(cl, q, pp, w, status, st, nullptr, 0, &ia)) != APT_OK) return s;
@@ -662,7 +677,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     pa.n_targets = do_knn ? n_targets : nullptr;
     pa.status = status;
     const size_t lds = pair_lds_bytes(do_rdf, do_knn, n_bins, in_lds);
-    if (pp.tile_policy != 1 && do_rdf) {
+    if (pp.tile_policy != 1 && do_rdf && !pp.no_nbr) {
         // the RDF neighbour-major when the plan chooses mode 3 (exits otherwise)
         TraceSpan span("nbr", st);
         const bool self = pa.self_possible != 0;
@@ -680,7 +695,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
             else self ? go2(k_rdf_tgt<kRdfGlobal | kSelf>) : go2(k_rdf_tgt<kRdfGlobal>);
         }
     }
-    if (pp.tile_policy != 1) {
+    if (pp.tile_policy != 1 && (do_knn || !pp.no_tiles)) {
         // 64 targets per wavefront when the plan chooses it (exits otherwise)
         TraceSpan span("tile", st);
         const bool self = pa.self_possible != 0;
@@ -821,7 +836,7 @@ static apt_status run_batched(const apt_cloud* cl, const apt_query* pairs, int32
         TraceSpan span("binning", st);
         const PlainWs& pw = w.plain;
         const int G = count_blocks(n);
-        const int64_t chunk = count_chunk(n, G);
+        const int64_t chunk = count_chunk(n);
         CountArgs ca{cl->xyz, cl->lab, nullptr, n, chunk, APT_ANY, APT_ANY, 0.0f, nullptr, pw.part_cnt, pw.part_bbox,
                      pw.part_nf};
         hipLaunchKernelGGL(k_count, dim3(G), dim3(kBlock), 0, st, ca);
@@ -1783,7 +1798,7 @@ apt_status apt_count_targets(const apt_cloud* cloud, apt_query q, int64_t* n_tar
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
     const int G = count_blocks(cloud->n);
-    CountArgs ca{cloud->xyz, cloud->lab, cloud->d_bnd, cloud->n, count_chunk(cloud->n, G), q.target, q.neighbor,
+    CountArgs ca{cloud->xyz, cloud->lab, cloud->d_bnd, cloud->n, count_chunk(cloud->n), q.target, q.neighbor,
                  q.d_srf, nullptr, w.part_cnt, w.part_bbox, w.part_nf};
     hipLaunchKernelGGL(k_count, dim3(G), dim3(kBlock), 0, st, ca);
     PlanParams pp{1.0f, 4.0f, 0, cell_cap_for(cloud->n), 1, 0.0f};

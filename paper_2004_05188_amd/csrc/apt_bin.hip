@@ -217,8 +217,8 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
         const double v64 = 64.0 * vol / (double)(totT > 0 ? totT : 1);
         const double side = cbrt(v64) + 2.0 * R;
         const double cand = rho * side * side * side;
-        P.tile_mode = (pp.k <= 16 && totT >= totB && totT >= (pp.k > 0 ? 1u << 18 : 4096u) && v64 <= R * R * R &&
-                       cand <= (pp.k > 0 ? 200.0 : 100.0)) ? 1 : 0;
+        P.tile_mode = (!pp.no_tiles && pp.k <= 16 && totT >= totB && totT >= (pp.k > 0 ? kTileMinKnn : kTileMinRdf) &&
+                       v64 <= R * R * R && cand <= (pp.k > 0 ? 200.0 : 100.0)) ? 1 : 0;
         // neighbours so dense that 64 of them span well under r_max: the RDF
         // runs neighbour-major (64 records per wavefront against every target
         // within reach), and the kNN, whose radius is then well below r_max,
@@ -235,9 +235,9 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
         // with 200 neighbours 0.53 / 0.44)
         const double a64 = cbrt(64.0 / rho);
         const bool even = 2ull * totT >= totB;
-        if (!P.tile_mode && pp.k <= 16 && pp.r_enum > 0.0f &&
+        if (!P.tile_mode && !pp.no_nbr && pp.k <= 16 && pp.r_enum > 0.0f &&
             a64 <= (even && totT >= (1u << 18) ? 1.15 : 1.0) * (double)pp.r_enum &&
-            totT >= (even && pp.k == 0 ? 1u << 17 : 1u << 18) &&
+            totT >= (even && pp.k == 0 ? kNbrMinRdf : kNbrMinKnn) &&
             (pp.k == 0 || rk_raw <= 0.5 * (double)pp.r_enum))
             P.tile_mode = 3;
     }

@@ -66,7 +66,15 @@ struct PlanParams {
     // > 0: the counting sort's counters per list, which bound the target keys
     // (0: the radix sort, whose passes do)
     uint32_t key_cap = 0;
+    // the automatic choice leaves out tile mode 1, mode 3 (their kernels are
+    // not launched)
+    int32_t no_tiles = 0, no_nbr = 0;
 };
+
+// Fewest targets for the automatic choice of tile mode 1 and of mode 3,
+// without and with a kNN (k_plan has the measurements).
+constexpr uint32_t kTileMinRdf = 4096, kTileMinKnn = 1u << 18;
+constexpr uint32_t kNbrMinRdf = 1u << 17, kNbrMinKnn = 1u << 18;
 
 // ---------------------------------------------------------------- waves --
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
