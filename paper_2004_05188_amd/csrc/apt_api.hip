@@ -1194,7 +1194,6 @@ static apt_status run_sdm(const apt_cloud* cl, apt_query q, float R, int32_t n_v
 constexpr size_t kSmoothPart = (size_t)1 << 21;
 struct SmoothWs {
     PlainWs plain;
-    double* E;
     double* part;
     size_t bytes;
 };
@@ -1202,7 +1201,6 @@ static SmoothWs carve_smooth(void* base, int64_t n) {
     SmoothWs w;
     w.plain = carve_plain(base, n);
     Carve c{base ? reinterpret_cast<char*>(base) + w.plain.bytes : nullptr};
-    w.E = c.take<double>(kSmoothMaxBins + 1);
     w.part = c.take<double>(kSmoothPart);
     w.bytes = w.plain.bytes + c.off;
     return w;
@@ -1238,7 +1236,6 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
 
     InitArgs ia{status, nullptr, 0, nullptr, 0, nullptr, nullptr};
     hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, st, ia);
-    hipLaunchKernelGGL(k_smooth_edges, dim3(16), dim3(256), 0, st, w.E, rb.r_max, rb.n_bins);
     if (bwd && cl->n > 0) hipLaunchKernelGGL(k_fill_f32, dim3(cus * 4), dim3(256), 0, st, grad_xyz, 3 * cl->n);
 
     const apt_tuning tu = tuning();
@@ -1269,13 +1266,17 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
     sa.d_srf = q.d_srf;
     sa.uni = bwd ? 1 : 0;
     sa.n_bins = rb.n_bins;
-    sa.hcap = (int)fmin(64.0, floor((double)kSmoothTerms / (mw + 1.0)));
+    // (narrow windows need few buffered terms, so more wavefronts fit the LDS)
+    const bool table = rb.n_bins <= kSmoothTableBins;
+    sa.narrow = table && mw + 1.0 <= 32.0;
+    sa.n_terms = sa.narrow ? kWave : kSmoothTerms;
+    sa.hcap = sa.narrow ? kWave : (int)fmin(64.0, floor((double)kSmoothTerms / (mw + 1.0)));
     sa.r_pre = r_pre;
     sa.sigma = sig;
     sa.cut = cut;
     sa.w6 = w6;
     sa.inv_width = rb.n_bins / (double)rb.r_max;
-    sa.E = w.E;
+    sa.r_max = (double)rb.r_max;
     sa.grad_h = grad_h;
     sa.part = w.part;
     sa.grad_xyz = grad_xyz;
@@ -1284,18 +1285,20 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
         if (W > kSmoothWaves) W = kSmoothWaves;
         sa.W = W;
         TraceSpan span("smooth", st);
-        hipLaunchKernelGGL(k_smooth_fwd, dim3(W), dim3(kWave), smooth_lds_bytes(true, rb.n_bins), st, sa);
-        SmoothReduceArgs ra{w.part, W, rb.n_bins, h};
-        hipLaunchKernelGGL(k_smooth_reduce, dim3((rb.n_bins + kWave - 1) / kWave), dim3(kWave * kReduceGroups), 0,
-                           st, ra);
+        const size_t lds = smooth_lds_bytes(true, rb.n_bins, sa.n_terms);
+        hipLaunchKernelGGL(table ? k_smooth_fwd<true> : k_smooth_fwd<false>, dim3(W), dim3(kWave), lds, st, sa);
+        SmoothReduceArgs ra{w.plain.plan, w.part, W, rb.n_bins, h};
+        hipLaunchKernelGGL(k_smooth_reduce, dim3((rb.n_bins + kReduceBins - 1) / kReduceBins),
+                           dim3(kReduceBins * kReduceGroups), 0, st, ra);
     } else {
         sa.W = kSmoothWaves;
         TraceSpan span("smooth", st);
-        hipLaunchKernelGGL(k_smooth_bwd, dim3(kSmoothWaves), dim3(kWave), smooth_lds_bytes(false, rb.n_bins), st,
+        const size_t lds = smooth_lds_bytes(false, rb.n_bins, sa.n_terms);
+        hipLaunchKernelGGL(table ? k_smooth_bwd<true> : k_smooth_bwd<false>, dim3(kSmoothWaves), dim3(kWave), lds, st,
                            sa);
         if (grad_s) {
-            SmoothReduceArgs ra{w.part, kSmoothWaves, 1, grad_s};
-            hipLaunchKernelGGL(k_smooth_reduce, dim3(1), dim3(kWave * kReduceGroups), 0, st, ra);
+            SmoothReduceArgs ra{w.plain.plan, w.part, kSmoothWaves, 1, grad_s};
+            hipLaunchKernelGGL(k_smooth_reduce, dim3(1), dim3(kReduceBins * kReduceGroups), 0, st, ra);
         }
     }
     return hip_check("smoothed RDF launch");

@@ -14,9 +14,8 @@
 //  * forward: one wavefront per target; its pairs are collected, then the
 //    Gaussian tail at each (pair, bin edge) is computed on its own lane, and
 //    the bin terms (differences of adjacent edges) are added pair by pair to
-//    the wavefront's FP64 LDS histogram; a reduction kernel sums the
-//    per-wavefront rows in a fixed order (consecutive row ranges in row
-//    order, then the range sums in range order);
+//    the wavefront's FP64 LDS histograms; a reduction kernel sums the
+//    per-wavefront rows in a fixed order;
 //  * adjoint: pair lists are recomputed, not stored.  Every ion that takes
 //    part in a pair (target or neighbour) gathers the derivative of L with
 //    respect to its own position over its pairs in both roles, so no two
@@ -28,15 +27,16 @@
 
 namespace apt {
 
-size_t smooth_lds_bytes(bool fwd, int n_bins) {
-    size_t b = (size_t)kSmoothTerms * 8u + (size_t)kWave * (5u * 8u + 4u);
-    if (fwd) b += (size_t)n_bins * 8u;
+// Dynamic LDS of a workgroup: the terms of a flush, the buffered pairs and,
+// for up to kSmoothTableBins bins, the bin edges with (forward) two copies of
+// the histogram or (adjoint) dL/dh; beyond, one copy of the histogram.
+size_t smooth_lds_bytes(bool fwd, int n_bins, int n_terms) {
+    const bool table = n_bins <= kSmoothTableBins;
+    size_t b = (size_t)n_terms * 8u + (size_t)kWave * (fwd ? 8u : 5u * 8u + 4u);
+    if (fwd) b += (size_t)n_bins * (table ? 16u : 8u);
+    else if (table) b += (size_t)n_bins * 8u;
+    if (table) b += ((size_t)n_bins + 1u) * 8u;
     return b;
-}
-
-__global__ void k_smooth_edges(double* E, float r_max, int n_bins) {
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b <= n_bins; b += gridDim.x * blockDim.x)
-        E[b] = ((double)b * (double)r_max) / (double)n_bins;
 }
 
 __global__ void k_fill_f32(float* p, int64_t n) {
@@ -44,21 +44,65 @@ __global__ void k_fill_f32(float* p, int64_t n) {
         p[i] = 0.0f;
 }
 
+// Coefficients of the tail below: (1 + 2x) exp(x^2) erfc(x) as a polynomial
+// in y = (x - 3.75) / (x + 3.75), from the function's Chebyshev expansion on
+// y in [-1, 1] in 80-digit arithmetic (its next coefficients are below 1e-16),
+// after M. M. Shepherd and J. G. Laframboise, Math. Comp. 36 (1981) 249.
+constexpr int kTailTerms = 23;
+__device__ constexpr double kTail[kTailTerms] = {
+    1.2375126308378275, -0.14024059858554525, 0.0035854154854790257, 0.08227673848999506,
+    -0.10880393014244462, 0.09230432116428125, -0.05869339857664934, 0.028362277372111139,
+    -0.0097465796832652621, 0.0017556261651970652, 0.00029371437804495801, -0.00029015535246077655,
+    5.1646529741774162e-05, 2.2387565714911816e-05, -1.1438048033346894e-05, -9.7926257073035231e-07,
+    1.7419821586224816e-06, -5.0844653786873023e-08, -2.4857126248016745e-07, 1.8790823223700481e-08,
+    3.1979266716668042e-08, -1.9551358868985616e-09, -2.6231073471334759e-09};
+
+// The tail of the normal distribution beyond |t|: 0.5 erfc(|t| / sqrt 2),
+// within about 5e-16 of its value for all t (exp(-t^2/2) takes the rounding of
+// t^2/2 into account).  One path for all lanes, about 80 FP64 instructions;
+// erfc() has several, and the lanes of a wavefront, at the edges of one
+// pair's window, took all of them; through |t| / sqrt 2 it was off by up to
+// 4e-14 in the far tail.
+__device__ __forceinline__ double smooth_tail(double t) {
+    const double x = fabs(t) * M_SQRT1_2;
+    const double y = (x - 3.75) / (x + 3.75);
+    double p = kTail[kTailTerms - 1];
+#pragma unroll
+    for (int q = kTailTerms - 2; q >= 0; --q) p = fma(p, y, kTail[q]);
+    const double h = 0.5 * t, z = h * t, ze = fma(h, t, -z);
+    const double e = 0.5 * exp(-z) * (p / fma(2.0, x, 1.0));
+    return fma(-e, ze, e);
+}
+
+// Edge b of the bins, in FP64.
+__device__ __forceinline__ double smooth_edge(const SmoothArgs& a, int b) {
+    return ((double)b * a.r_max) / (double)a.n_bins;
+}
+
 // Bins [b0, b1] that meet (D - 6 sigma, D + 6 sigma); D < r_max + 6 sigma
 // guarantees that the range is not empty.
-__device__ __forceinline__ void smooth_window(const SmoothArgs& a, double D, int* b0, int* b1) {
+template <class EDGE>
+__device__ __forceinline__ void smooth_window(const SmoothArgs& a, EDGE&& edge, double D, int* b0, int* b1) {
     const int nb = a.n_bins;
     const double lo = D - a.w6, hi = D + a.w6;
     int g = (int)floor(lo * a.inv_width);
     g = g < 0 ? 0 : (g > nb - 1 ? nb - 1 : g);
-    while (g > 0 && a.E[g] > lo) --g;
-    while (g < nb - 1 && !(a.E[g + 1] > lo)) ++g;
+    while (g > 0 && edge(g) > lo) --g;
+    while (g < nb - 1 && !(edge(g + 1) > lo)) ++g;
     int h = (int)floor(hi * a.inv_width);
     h = h < 0 ? 0 : (h > nb - 1 ? nb - 1 : h);
-    while (h < nb - 1 && a.E[h + 1] < hi) ++h;
-    while (h > 0 && !(a.E[h] < hi)) --h;
+    while (h < nb - 1 && edge(h + 1) < hi) ++h;
+    while (h > 0 && !(edge(h) < hi)) --h;
     *b0 = g;
     *b1 = h;
+}
+
+// Bin mass from the signed tails at its edges (negative below D): both edges
+// above D, both below, or D inside the bin (an edge exactly at D falls to the
+// last case with the same value).
+__device__ __forceinline__ double smooth_mass(double slo, double shi) {
+    const double vlo = fabs(slo), vhi = fabs(shi);
+    return slo > 0.0 ? vlo - vhi : (shi < 0.0 ? vhi - vlo : (1.0 - vhi) - vlo);
 }
 
 __device__ __forceinline__ bool smooth_is_target(const SmoothArgs& a, uint32_t i) {
@@ -69,27 +113,45 @@ __device__ __forceinline__ bool smooth_is_nbr(const SmoothArgs& a, uint32_t i) {
     return a.B == APT_ANY || a.lab[i] == a.B;
 }
 
-template <bool BWD>
+// Bound by latency: a chain of dependent steps per ion and flush, and few
+// wavefronts per SIMD beside it, limited by LDS.  So the edges (TABLE) and
+// dL/dh are read from LDS, not memory, the forward keeps only what it needs
+// of a pair, and where windows have at most 32 edges (`narrow`) each half of
+// the wavefront takes a pair of its own, its terms never leave the registers
+// and its bins go to a histogram of the half's own: 64 pairs per flush instead
+// of 34, no search for a term's pair, and no pair waits for the one before.
+// 1e6 ions, 200 bins, sigma 0.02 nm: 216 -> 127 us forward, 135 -> 110 us
+// adjoint.
+template <bool BWD, bool TABLE>
 __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
+    constexpr bool PAIRS2 = !BWD && TABLE;
     extern __shared__ __align__(16) uint8_t smem[];
-    double* s_term = reinterpret_cast<double*>(smem);   // [kSmoothTerms] per-(pair, bin) terms
-    double* s_D = s_term + kSmoothTerms;                // [64] buffered pairs: distance,
-    double* s_dx = s_D + kWave;                         //   scaled displacement (candidate - ion),
+    double* s_term = reinterpret_cast<double*>(smem);   // [n_terms] per-(pair, edge) terms
+    double* s_D = s_term + a.n_terms;                   // [64] buffered pairs: distance,
+    double* s_dx = s_D + kWave;                         //   adjoint: scaled displacement (candidate - ion),
     double* s_dy = s_dx + kWave;
     double* s_dz = s_dy + kWave;
     double* s_zz = s_dz + kWave;                        //   unscaled z difference,
     int* s_mul = reinterpret_cast<int*>(s_zz + kWave);  //   roles: count | (ion is the target) << 8
-    double* s_hist = reinterpret_cast<double*>(s_mul + kWave);   // forward: [n_bins]
+    // forward: histogram, [2][n_bins] with TABLE; adjoint with TABLE: dL/dh
+    double* s_hist = BWD ? reinterpret_cast<double*>(s_mul + kWave) : s_D + kWave;
+    double* s_E = s_hist + (size_t)a.n_bins * (PAIRS2 ? 2 : 1);
+    auto edge = [&](int b) { return TABLE ? s_E[b] : smooth_edge(a, b); };
 
     const GridPlan P = *a.plan;
     const int l = lane_id();
     const double s = a.zscale ? *a.zscale : 1.0;
     const float rp = a.r_pre + P.eps;
     const float rp2 = rp * rp;
-    if (!BWD) {
-        for (int b = l; b < a.n_bins; b += kWave) s_hist[b] = 0.0;
-        wave_sync();
+    if (blockIdx.x >= P.nT) return;      // (k_smooth_reduce reads the rows of the first nT)
+    if (!BWD)
+        for (int b = l; b < a.n_bins * (PAIRS2 ? 2 : 1); b += kWave) s_hist[b] = 0.0;
+    if (TABLE) {
+        for (int b = l; b <= a.n_bins; b += kWave) s_E[b] = smooth_edge(a, b);
+        if (BWD)
+            for (int b = l; b < a.n_bins; b += kWave) s_hist[b] = a.grad_h[b];
     }
+    wave_sync();
     double gs = 0.0;   // adjoint: this lane's share of dL/ds
 
     for (uint32_t t = blockIdx.x; t < P.nT; t += (uint32_t)a.W) {
@@ -111,9 +173,68 @@ __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
             int b0 = 0, mh = 0, me = 0;
             if (l < nh) {
                 int b1;
-                smooth_window(a, s_D[l], &b0, &b1);
+                smooth_window(a, edge, s_D[l], &b0, &b1);
                 mh = b1 - b0 + 1;
                 me = mh + 1;
+            }
+            // the adjoint's share of pair l, given its dL/dD
+            auto gather = [&](double g) {
+                const double D = s_D[l];
+                if (D != 0.0) {
+                    const int mul = s_mul[l];
+                    const double cnt = (double)(mul & 0xff);
+                    gx -= cnt * (g * (s_dx[l] / D));
+                    gy -= cnt * (g * (s_dy[l] / D));
+                    gz -= cnt * ((g * (s_dz[l] / D)) * s);
+                    if (mul >> 8) {
+                        const double zz = s_zz[l];
+                        gs += g * s * zz * zz / D;
+                    }
+                }
+            };
+            if (TABLE && a.narrow) {
+                // every window has at most 32 edges: half h of the wavefront
+                // takes the edges of one pair, two pairs each per step.
+                // Forward: its bins go to the half's own histogram (a
+                // wavefront's LDS accesses happen in program order); adjoint:
+                // their sum is the pair's dL/dD
+                const int half = l >> 5, ln = l & 31;
+                double* hist = s_hist + (BWD ? 0 : (size_t)half * (size_t)a.n_bins);
+                for (int h0 = 0; h0 < nh; h0 += 4) {
+                    double u[2];
+                    int bin[2], cnt[2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const int h = h0 + 2 * k + half, hc = h < nh ? h : 0;
+                        bin[k] = __shfl(b0, hc, kWave) + ln;
+                        const int edges = __shfl(me, hc, kWave);
+                        cnt[k] = h < nh ? edges - 1 : 0;      // bins of the window
+                        const double t = (edge(ln < edges ? bin[k] : bin[k] - ln) - s_D[hc]) / a.sigma;
+                        if (BWD) {
+                            u[k] = exp(-0.5 * t * t) / sqrt(2.0 * M_PI);
+                        } else {
+                            const double v = smooth_tail(t);
+                            u[k] = t >= 0.0 ? v : -v;
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const double next = __shfl_down(u[k], 1, kWave);   // the bin's upper edge
+                        if (!BWD) {
+                            if (ln < cnt[k]) hist[bin[k]] += smooth_mass(u[k], next);
+                        } else {
+                            double g = ln < cnt[k] ? hist[bin[k]] * (-(next - u[k]) / a.sigma) : 0.0;
+#pragma unroll
+                            for (int d = 16; d >= 1; d >>= 1) g += __shfl_xor(g, d, kWave);
+                            if (ln == 0 && cnt[k] > 0) s_term[h0 + 2 * k + half] = g;
+                        }
+                    }
+                }
+                wave_sync();
+                if (BWD && l < nh) gather(s_term[l]);
+                wave_sync();
+                nh = 0;
+                return;
             }
             const uint32_t inc = wave_incl_scan((uint32_t)me);
             const uint32_t tot = readlane(inc, kWave - 1);
@@ -132,10 +253,10 @@ __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
                     }
                 }
                 if (h >= 0) {
-                    const double t = (a.E[ev] - s_D[h]) / a.sigma;
+                    const double t = (edge(ev) - s_D[h]) / a.sigma;
                     if (!BWD) {
-                        // the tail 0.5 erfc(|t| / sqrt 2) > 0, negated when t < 0
-                        const double u = 0.5 * erfc(fabs(t) / M_SQRT2);
+                        // the tail beyond |t|, negated when t < 0
+                        const double u = smooth_tail(t);
                         s_term[v] = t >= 0.0 ? u : -u;
                     } else {
                         s_term[v] = exp(-0.5 * t * t) / sqrt(2.0 * M_PI);
@@ -144,38 +265,35 @@ __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
             }
             wave_sync();
             if (!BWD) {
-                // pair by pair (windows of different pairs overlap)
-                for (int h = 0; h < nh; ++h) {
-                    const uint32_t o = readlane(off, h);
-                    const int ln = readlane(mh, h), bb = readlane(b0, h);
-                    for (int q = l; q < ln; q += kWave) {
-                        // bin mass from the tails at its edges: both edges above
-                        // D, both below, or D inside the bin (an edge exactly at
-                        // D falls to the last case with the same value)
-                        const double slo = s_term[o + q], shi = s_term[o + q + 1];
-                        const double vlo = fabs(slo), vhi = fabs(shi);
-                        s_hist[bb + q] += slo > 0.0 ? vlo - vhi : (shi < 0.0 ? vhi - vlo : (1.0 - vhi) - vlo);
+                auto mass = [&](uint32_t o) { return smooth_mass(s_term[o], s_term[o + 1]); };
+                if (PAIRS2) {
+                    // two pairs at a time, pair by pair within a half (the
+                    // wavefront's LDS accesses happen in program order)
+                    const int half = l >> 5, ln32 = l & 31;
+                    double* hist = s_hist + (size_t)half * (size_t)a.n_bins;
+                    for (int h0 = 0; h0 < nh; h0 += 2) {
+                        const int h = h0 + half < nh ? h0 + half : h0;
+                        const uint32_t o = (uint32_t)__shfl((int)off, h, kWave);
+                        const int bb = __shfl(b0, h, kWave);
+                        const int ln = h0 + half < nh ? __shfl(mh, h, kWave) : 0;
+                        for (int q = ln32; q < ln; q += 32) hist[bb + q] += mass(o + (uint32_t)q);
                     }
-                    wave_sync();
+                } else {
+                    // pair by pair (windows of different pairs overlap)
+                    for (int h = 0; h < nh; ++h) {
+                        const uint32_t o = readlane(off, h);
+                        const int ln = readlane(mh, h), bb = readlane(b0, h);
+                        for (int q = l; q < ln; q += kWave) s_hist[bb + q] += mass(o + (uint32_t)q);
+                        wave_sync();
+                    }
                 }
             } else if (l < nh) {
                 double g = 0.0;
                 for (int q = 0; q < mh; ++q) {
                     const double plo = s_term[off + (uint32_t)q], phi = s_term[off + (uint32_t)q + 1];
-                    g += a.grad_h[b0 + q] * (-(phi - plo) / a.sigma);
+                    g += (TABLE ? s_hist[b0 + q] : a.grad_h[b0 + q]) * (-(phi - plo) / a.sigma);
                 }
-                const double D = s_D[l];
-                if (D != 0.0) {
-                    const int mul = s_mul[l];
-                    const double cnt = (double)(mul & 0xff);
-                    gx -= cnt * (g * (s_dx[l] / D));
-                    gy -= cnt * (g * (s_dy[l] / D));
-                    gz -= cnt * ((g * (s_dz[l] / D)) * s);
-                    if (mul >> 8) {
-                        const double zz = s_zz[l];
-                        gs += g * s * zz * zz / D;
-                    }
-                }
+                gather(g);
             }
             wave_sync();
             nh = 0;
@@ -248,7 +366,7 @@ __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
     if (!BWD) {
         wave_sync();
         double* row = a.part + (size_t)blockIdx.x * (size_t)a.n_bins;
-        for (int b = l; b < a.n_bins; b += kWave) row[b] = s_hist[b];
+        for (int b = l; b < a.n_bins; b += kWave) row[b] = PAIRS2 ? s_hist[b] + s_hist[a.n_bins + b] : s_hist[b];
     } else {
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) gs += __shfl_xor(gs, d, kWave);
@@ -256,18 +374,32 @@ __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
     }
 }
 
-__global__ __launch_bounds__(kWave) void k_smooth_fwd(SmoothArgs a) { smooth_body<false>(a); }
-__global__ __launch_bounds__(kWave) void k_smooth_bwd(SmoothArgs a) { smooth_body<true>(a); }
+// (three wavefronts per SIMD without spills are faster than four: 129 / 137 us)
+template <bool TABLE>
+__global__ __launch_bounds__(kWave, 3) void k_smooth_fwd(SmoothArgs a) {
+    smooth_body<false, TABLE>(a);
+}
+template <bool TABLE>
+__global__ __launch_bounds__(kWave, 4) void k_smooth_bwd(SmoothArgs a) {
+    smooth_body<true, TABLE>(a);
+}
+template __global__ void k_smooth_fwd<false>(SmoothArgs);
+template __global__ void k_smooth_fwd<true>(SmoothArgs);
+template __global__ void k_smooth_bwd<false>(SmoothArgs);
+template __global__ void k_smooth_bwd<true>(SmoothArgs);
 
-// out[b] = sum over the W per-wavefront rows of part[w][b], in a fixed
-// order: kReduceGroups consecutive row ranges, each summed in row order,
-// then the range sums in range order (the same result on every run).
-// Workgroup: 64 bins x kReduceGroups ranges; grid: ceil(n_bins / 64).
-__global__ __launch_bounds__(kWave * kReduceGroups) void k_smooth_reduce(SmoothReduceArgs a) {
-    __shared__ double s_p[kReduceGroups][kWave];
-    const int tb = threadIdx.x % kWave, g = threadIdx.x / kWave;
-    const int b = blockIdx.x * kWave + tb;
-    const int w0 = (int)((int64_t)a.W * g / kReduceGroups), w1 = (int)((int64_t)a.W * (g + 1) / kReduceGroups);
+// out[b] = sum over the first min(W, nT) per-wavefront rows of part[w][b], in
+// a fixed order (the same result on every run): kReduceGroups consecutive row
+// ranges, each summed in row order, then the range sums pairwise.  Workgroup:
+// kReduceBins bins x kReduceGroups ranges, so that 200 bins fill 50 workgroups
+// of 256 ranges each (64 bins x 16 ranges were four, 62 us).
+__global__ __launch_bounds__(kReduceBins * kReduceGroups) void k_smooth_reduce(SmoothReduceArgs a) {
+    __shared__ double s_p[kReduceGroups][kReduceBins];
+    const int tb = threadIdx.x % kReduceBins, g = threadIdx.x / kReduceBins;
+    const int b = blockIdx.x * kReduceBins + tb;
+    const uint32_t nT = a.plan->nT;
+    const int64_t W = nT < (uint32_t)a.W ? (int64_t)nT : (int64_t)a.W;
+    const int w0 = (int)(W * g / kReduceGroups), w1 = (int)(W * (g + 1) / kReduceGroups);
     double acc = 0.0;
     if (b < a.n_bins) {
         const double* col = a.part + (size_t)b;
@@ -282,12 +414,11 @@ __global__ __launch_bounds__(kWave * kReduceGroups) void k_smooth_reduce(SmoothR
         for (; w < w1; ++w) acc += col[(size_t)w * (size_t)a.n_bins];
     }
     s_p[g][tb] = acc;
-    __syncthreads();
-    if (g == 0 && b < a.n_bins) {
-        double t = 0.0;
-        for (int q = 0; q < kReduceGroups; ++q) t += s_p[q][tb];
-        a.out[b] = t;
+    for (int step = 1; step < kReduceGroups; step *= 2) {
+        __syncthreads();
+        if (g % (2 * step) == 0) s_p[g][tb] += s_p[g + step][tb];
     }
+    if (g == 0 && b < a.n_bins) a.out[b] = s_p[0][tb];
 }
 
 }  // namespace apt

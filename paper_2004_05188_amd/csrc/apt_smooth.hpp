@@ -12,7 +12,8 @@ namespace apt {
 constexpr int kSmoothTerms = 1024;     // window edge values buffered per wavefront
 constexpr int kSmoothMaxBins = 4096;   // forward histogram held in LDS
 constexpr int kSmoothWaves = 8192;     // wavefronts of the launch (forward: at most this many)
-constexpr int kReduceGroups = 16;      // row ranges of the fixed-order reduction
+constexpr int kReduceBins = 4, kReduceGroups = 256;   // bins and row ranges of a workgroup of the fixed-order reduction
+constexpr int kSmoothTableBins = 1024; // bins whose edges and second histogram are held in LDS
 
 struct SmoothArgs {
     const GridPlan* plan;
@@ -34,24 +35,28 @@ struct SmoothArgs {
     double cut;                  // r_max + 6 sigma
     double w6;                   // 6 sigma
     double inv_width;            // n_bins / r_max
-    const double* E;             // [n_bins + 1] bin edges
+    double r_max;                // edge b of the bins: (b * r_max) / n_bins
+    int32_t narrow;              // no window has more than 32 edges: a half-wavefront per pair
+    int32_t n_terms;             // terms a flush holds (at most kSmoothTerms)
     const double* grad_h;        // adjoint: dL/dh [n_bins]
     double* part;                // forward: [W][n_bins]; adjoint: [W] partial dL/ds
     float* grad_xyz;             // adjoint: [n][3]
 };
 
 struct SmoothReduceArgs {
+    const GridPlan* plan;
     const double* part;
     int32_t W;
     int32_t n_bins;              // forward: bins; adjoint: 1
     double* out;
 };
 
-__global__ void k_smooth_edges(double* E, float r_max, int n_bins);
+template <bool TABLE>
 __global__ void k_smooth_fwd(SmoothArgs a);
+template <bool TABLE>
 __global__ void k_smooth_bwd(SmoothArgs a);
 __global__ void k_smooth_reduce(SmoothReduceArgs a);
 __global__ void k_fill_f32(float* p, int64_t n);
-size_t smooth_lds_bytes(bool fwd, int n_bins);
+size_t smooth_lds_bytes(bool fwd, int n_bins, int n_terms);
 
 }  // namespace apt

@@ -101,6 +101,24 @@ PROBLEMS = [
 ]
 
 
+# the widest windows of half a wavefront (32 edges) and one bin more, and the last bin count with tables in LDS and
+# one more
+@pytest.mark.parametrize("n_bins,sigma", [(200, 0.0239), (200, 0.0243), (1024, 0.004), (1025, 0.004), (7, 0.3)])
+def test_windows_and_tables_at_their_limits(gpu, orc, synth, n_bins, sigma):
+    _say(f"smooth limits n_bins={n_bins} sigma={sigma}")
+    xyz, lab, d = _box(synth, 20_000, 9.0, 21)
+    cloud = _cloud(gpu, xyz, lab, d)
+    h, st = gpu_fwd(gpu, cloud, SC, SC, 0.3, 2.0, n_bins, sigma, 1.02)
+    ref = orc.smooth_fwd(xyz, lab, d, SC, SC, 0.3, 2.0, n_bins, sigma, 1.02)
+    assert st == 0
+    assert_fwd_close(h, ref)
+    gh = np.random.default_rng(n_bins).standard_normal(n_bins)
+    gx, gs = gpu_bwd(gpu, cloud, SC, SC, 0.3, 2.0, n_bins, sigma, gh, 1.02)
+    ogx, ogs = orc.smooth_bwd(xyz, lab, d, SC, SC, 0.3, 2.0, n_bins, sigma, 1.02, gh)
+    assert_grad_close(gx, ogx)
+    assert abs(gs - ogs) <= 1e-9 * abs(ogs)
+
+
 @pytest.mark.parametrize("s", [1.0, 1.05])
 @pytest.mark.parametrize("prob", PROBLEMS, ids=[p[0] for p in PROBLEMS])
 def test_smooth_forward_and_adjoint_match_oracle(gpu, orc, synth, prob, s):
