@@ -169,8 +169,11 @@ static uint32_t cell_cap_for(int64_t n) {
     if (c > 0xFFFFFF00ll) c = 0xFFFFFF00ll;
     return (uint32_t)c;
 }
-static int sort_passes_max(uint32_t cap) {
-    return sort_passes_for(cap - 1u);
+// The large downsweep's tiles and digits beyond 2^25 ions, the small one's below.
+static bool sort_large(int64_t n) { return n > ((int64_t)1 << 25); }
+static int sort_digit_bits(int64_t n) { return sort_large(n) ? kDsLargeBits : kDsSmallBits; }
+static int sort_passes_max(uint32_t cap, int64_t n) {
+    return sort_passes_for(cap - 1u, sort_digit_bits(n));
 }
 constexpr int kSortBlocks = 1024;   // most workgroups of a radix pass (the counts matrix is sized for it)
 // Workgroups of a radix pass over at most n keys: fewer, fuller ones for
@@ -181,10 +184,12 @@ static int sort_blocks(int64_t n) { return n <= ((int64_t)1 << 25) ? 512 : kSort
 // One radix pass of the sorts in `ss` (grid: their workgroups) over a cloud
 // of n ions: upsweep, scan, and the downsweep whose tile suits the size.
 static void launch_sort_pass(SortSet& ss, int grid, int64_t n, hipStream_t st) {
-    const bool large = n > ((int64_t)1 << 25);
+    const bool large = sort_large(n);
     ss.tile = large ? kDsLargeBlock * kDsLargeItems : kDsSmallBlock * kDsSmallItems;
-    hipLaunchKernelGGL(k_rs_upsweep, dim3(grid), dim3(kBlock), 0, st, ss);
-    hipLaunchKernelGGL(k_rs_scan, dim3(kRadix * ss.n), dim3(kBlock), 0, st, ss);
+    ss.radix = 1 << sort_digit_bits(n);
+    if (large) hipLaunchKernelGGL(k_rs_upsweep<kDsLargeBits>, dim3(grid), dim3(kBlock), 0, st, ss);
+    else hipLaunchKernelGGL(k_rs_upsweep<kDsSmallBits>, dim3(grid), dim3(kBlock), 0, st, ss);
+    hipLaunchKernelGGL(k_rs_scan, dim3(ss.radix * ss.n), dim3(kBlock), 0, st, ss);
     if (large) hipLaunchKernelGGL(k_rs_downsweep_large, dim3(grid), dim3(kDsLargeBlock), 0, st, ss);
     else hipLaunchKernelGGL(k_rs_downsweep_small, dim3(grid), dim3(kDsSmallBlock), 0, st, ss);
 }
@@ -230,7 +235,7 @@ static PlainWs carve_plain(void* base, int64_t n) {
     w.part_off = c.take<uint32_t>(2 * kMaxCountBlocks);
     w.E2 = c.take<double>(APT_MAX_BINS + 1);
     w.KE2 = c.take<double>(APT_MAX_BINS + 1);
-    w.rs_counts = c.take<uint32_t>(2 * 256 * kSortBlocks);   // [sort][256][G]
+    w.rs_counts = c.take<uint32_t>(2 * 256 * kSortBlocks);   // [sort][256][G] (sort_scratch)
     w.rs_totals = c.take<uint32_t>(2 * 256);
     w.tid = c.take<uint32_t>(N);
     w.bsel = c.take<uint32_t>(N);
@@ -249,11 +254,30 @@ static PlainWs carve_plain(void* base, int64_t n) {
     w.bpos = c.take<float4>(N);
     w.cell_start = c.take<uint32_t>((size_t)cell_cap_for(n) + 1);
     w.strag = c.take<uint32_t>(N);
-    w.strag_count = c.take<uint32_t>(64 + 2 * kXcd * kWorkStride);   // [0], [3] stragglers, [1..2] occupied cells, [64..] work queues
+    w.strag_count = c.take<uint32_t>(64);   // [0], [3] stragglers, [1..2] occupied cells
     w.t_cell_start = c.take<uint32_t>((size_t)cell_cap_for(n) + 1);
     w.bytes = c.off;
     return w;
 }
+
+// The radix sorts' digit counts and totals: sort 0 (targets) and 1.  Small
+// digits have arrays of their own; the large sorts' 512 digits take the
+// straggler list, which the pair kernels use later (4 B per ion, more than
+// 2^25 of them).
+struct SortScratch {
+    uint32_t *counts, *totals;
+};
+static SortScratch sort_scratch(const PlainWs& w, int64_t n, int sort) {
+    if (!sort_large(n)) return {w.rs_counts + (size_t)sort * 256 * kSortBlocks, w.rs_totals + sort * 256};
+    const size_t radix = (size_t)1 << kDsLargeBits;
+    return {w.strag + 2 * radix + (size_t)sort * radix * kSortBlocks, w.strag + (size_t)sort * radix};
+}
+
+// The pair kernels' work queues, zeroed by the binning's first kernel: in the
+// part of rs_counts that no sort uses (sort 0 has at most kSortBlocks / 2
+// workgroups).
+static uint32_t* work_queues(const PlainWs& w) { return w.rs_counts + (size_t)256 * (kSortBlocks / 2); }
+static_assert(256 * (kSortBlocks / 2) >= 2 * kXcd * kWorkStride, "room for the queues");
 
 // Workspace of the label permutation for n ions and up to r replicates.
 struct PermWs {
@@ -447,6 +471,7 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
     const bool every = q.target == APT_ANY || q.neighbor == APT_ANY;
     const bool counting = init && n <= (every ? kCountSortMax / 2 : kCountSortMax);
     PlanParams pp = plan;
+    pp.digit_bits = sort_digit_bits(n);
     if (counting) {
         // a counter per cell and list, in the radix sort's value arrays
         pp.cell_cap = (uint32_t)std::min<int64_t>(pp.cell_cap, std::max<int64_t>(n, 1));
@@ -494,19 +519,20 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
     // both sorts share each pass's launches; target keys never need more
     // bytes than cell ids (the plan falls back to cell order when its
     // block-raster keys would)
-    const int passes = sort_passes_max(pp.cell_cap);
+    const int passes = sort_passes_max(pp.cell_cap, n);
     const int Gk = cus * 8;
     // the target sort on half the workgroups: targets are usually the rarer
     // species (on the needle's queries binning −2 to −5.5 %; a query whose
     // targets are the majority species bins ≈ 5 % slower)
     const int Gs = sort_blocks(n), GsT = Gs / 2;
+    const SortScratch xT = sort_scratch(w, n, 0), xB = sort_scratch(w, n, 1);
     for (int p = 0; p < passes; ++p) {
         SortSet ss{};
-        ss.s[0] = SortArgs{w.plan, 1, p, GsT, {w.K[0], w.K[1]}, {w.V[0], w.V[1]}, w.rs_counts, w.rs_totals};
+        ss.s[0] = SortArgs{w.plan, 1, p, GsT, {w.K[0], w.K[1]}, {w.V[0], w.V[1]}, xT.counts, xT.totals};
         // the neighbours' 16-byte records travel with their keys: no random
         // position reads after the sort
         ss.s[1] = SortArgs{w.plan, 0, p, Gs, {w.KB[0], w.KB[1]}, {nullptr, nullptr},
-                           w.rs_counts + (size_t)256 * kSortBlocks, w.rs_totals + 256, {w.bpos, w.brec2}};
+                           xB.counts, xB.totals, {w.bpos, w.brec2}};
         ss.n = 2;
         launch_sort_pass(ss, GsT + Gs, n, st);
     }
@@ -560,7 +586,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
                 knn_hist ? kb->n_bins + 1 : 0, n_targets, w.strag_count,
                 do_rdf ? w.E2 : nullptr, do_rdf ? rb->r_max : 0.0f, do_rdf ? rb->n_bins : 0,
                 knn_hist ? w.KE2 : nullptr, knn_hist ? kb->r_max : 0.0f, knn_hist ? kb->n_bins : 0};
-    ia.work_q = w.strag_count + 64;
+    ia.work_q = work_queues(w);
     // (zeroed and filled by the binning's first kernel)
 
     const apt_tuning tu = tuning();
@@ -605,7 +631,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
             ca.t_id = w.t_id;
             ca.bpos = w.bpos;
             ca.t_cell_start = w.t_cell_start;
-            ca.work_q = w.strag_count + 64;
+            ca.work_q = work_queues(w);
             ca.r_enum = (float)((double)rb->r_max * (1.0 + 4e-5));
             ca.hist = cand;
             ca.n_bins = 1;
@@ -671,7 +697,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     pa.strag = w.strag;
     pa.strag_count = w.strag_count;
     pa.t_cell_start = w.t_cell_start;
-    pa.work_q = w.strag_count + 64;
+    pa.work_q = work_queues(w);
     // the kNN radii from the occupied cells that the binning counted
     pa.occ = do_knn ? w.strag_count + 1 : nullptr;
     pa.n_targets = do_knn ? n_targets : nullptr;
@@ -841,16 +867,18 @@ static apt_status run_batched(const apt_cloud* cl, const apt_query* pairs, int32
                      pw.part_nf};
         hipLaunchKernelGGL(k_count, dim3(G), dim3(kBlock), 0, st, ca);
         PlanParams pp{rb.r_max * bt.cell_frac, 4.0f, k, cell_cap_for(n), 1, rb.r_max};
+        pp.digit_bits = sort_digit_bits(n);
+        const SortScratch xs = sort_scratch(pw, n, 1);
         PlanArgs pa{G, pw.part_cnt, pw.part_bbox, pw.part_nf, pw.part_off, pp, nullptr, pw.plan, status};
         hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, st, pa);
         const int Gk = cus * 8;
         const int Gs = sort_blocks(n);
         KeyArgs kk{pw.plan, cl->xyz, nullptr, nullptr, 0, 0, pw.K[0], pw.V[0]};
         hipLaunchKernelGGL(k_keys, dim3(Gk), dim3(kBlock), 0, st, kk);
-        for (int p = 0; p < sort_passes_max(pp.cell_cap); ++p) {
+        for (int p = 0; p < sort_passes_max(pp.cell_cap, n); ++p) {
             SortSet ss{};
-            ss.s[0] = SortArgs{pw.plan, 0, p, Gs, {pw.K[0], pw.K[1]}, {pw.V[0], pw.V[1]}, pw.rs_counts,
-                               pw.rs_totals};
+            ss.s[0] = SortArgs{pw.plan, 0, p, Gs, {pw.K[0], pw.K[1]}, {pw.V[0], pw.V[1]}, xs.counts,
+                               xs.totals};
             ss.n = 1;
             launch_sort_pass(ss, Gs, n, st);
         }

@@ -279,7 +279,7 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
             // (both counts are at most cell_cap here: exact in u64)
             const double c1 = cells_of(h), c2 = cells_of(h2);
             if (c2 <= (double)pp.cell_cap &&
-                sort_passes_for((uint64_t)c2 - 1u) == sort_passes_for((uint64_t)c1 - 1u))
+                sort_passes_for((uint64_t)c2 - 1u, pp.digit_bits) == sort_passes_for((uint64_t)c1 - 1u, pp.digit_bits))
                 h = h2;
         }
     }
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
     P.n_cells = (uint32_t)ncell;
     P.nT = totT;
     P.nB = totB;
-    const uint32_t passes = (uint32_t)sort_passes_for(P.n_cells - 1u);
+    const uint32_t passes = (uint32_t)sort_passes_for(P.n_cells - 1u, pp.digit_bits);
     P.passes = passes;
     P.bits = key_bits(P.n_cells - 1u);
     // targets in block-raster order when its keys fit 32 bits and need no
@@ -303,14 +303,14 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
         const uint64_t nbx = ((uint64_t)P.dim[0] + 7) / 8, nby = ((uint64_t)P.dim[1] + 7) / 8,
                        nbz = ((uint64_t)P.dim[2] + 7) / 8;
         const uint64_t kmax = nbx * nby * nbz * 512u - 1u;
-        const int cap_passes = sort_passes_for(pp.cell_cap - 1u);
+        const int cap_passes = sort_passes_for(pp.cell_cap - 1u, pp.digit_bits);
         // (mode 3 looks targets up by cell: plain cell order)
         if (P.tile_mode != 3 && kmax <= 0xFFFFFFFFull &&
-            (pp.key_cap ? kmax < pp.key_cap : sort_passes_for(kmax) <= cap_passes)) {
+            (pp.key_cap ? kmax < pp.key_cap : sort_passes_for(kmax, pp.digit_bits) <= cap_passes)) {
             P.tblock = 8;
             P.nbx = (int32_t)nbx;
             P.nby = (int32_t)nby;
-            P.passes_T = (uint32_t)sort_passes_for(kmax);
+            P.passes_T = (uint32_t)sort_passes_for(kmax, pp.digit_bits);
             P.bits_T = key_bits(kmax);
         } else {
             P.tblock = 1;
@@ -474,7 +474,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(KeyArgs a) {
 }
 
 // ------------------------------------------------------------------------
-// 5. LSD radix sort of (cell id, value) pairs, kDigitBits per pass, stable.
+// 5. LSD radix sort of (cell id, value) pairs, stable.
 //    Block b sorts its chunk tile by tile; digits of a tile are ranked
 //    inside each wavefront with ballots, then placed through LDS so that
 //    the global writes of one digit are contiguous.
@@ -519,7 +519,9 @@ __device__ __forceinline__ void rs_chunk(uint32_t n, int G, uint32_t tile, uint3
     *chunk = (c + tile - 1u) / tile * tile;
 }
 
+template <int BITS>
 __global__ __launch_bounds__(kBlock) void k_rs_upsweep(SortSet set) {
+    constexpr int kRadix = 1 << BITS;
     // sort 0 takes the first s[0].G workgroups, sort 1 the next s[1].G
     const uint32_t g0 = (uint32_t)set.s[0].G;
     const int q = blockIdx.x < g0 ? 0 : 1;
@@ -564,17 +566,20 @@ __global__ __launch_bounds__(kBlock) void k_rs_upsweep(SortSet set) {
     }
 }
 
+template __global__ void k_rs_upsweep<kDsSmallBits>(SortSet);
+template __global__ void k_rs_upsweep<kDsLargeBits>(SortSet);
+
 // Row scan of the digit counts: workgroup d turns counts[d][0..G) into
 // exclusive prefixes within the row and writes the row total to totals[d].
-// The downsweep adds the digit bases (a scan of the kRadix totals).
+// The downsweep adds the digit bases (a scan of the digits' totals).
 __global__ __launch_bounds__(kBlock) void k_rs_scan(SortSet set) {
-    const int q = blockIdx.x / kRadix;
+    const int q = blockIdx.x / set.radix;
     if (q >= set.n) return;
     const SortArgs a = sort_of(set, q);
     const GridPlan P = *a.plan;
     if (!rs_active(P, a)) return;
     __shared__ uint32_t s_w[kWavesPerBlock];
-    const int d = blockIdx.x - q * kRadix, t = threadIdx.x, w = t / kWave, l = lane_id();
+    const int d = blockIdx.x - q * set.radix, t = threadIdx.x, w = t / kWave, l = lane_id();
     const int G = a.G;
     const int per = (G + kBlock - 1) / kBlock;    // G <= 4096: at most 16 per thread
     uint32_t v[16];
@@ -599,9 +604,15 @@ __global__ __launch_bounds__(kBlock) void k_rs_scan(SortSet set) {
     if (t == kBlock - 1) a.totals[d] = run;
 }
 
+template <int V>
+struct Int {
+    static constexpr int value = V;
+};
+
 // LDS of one downsweep workgroup of BLOCK threads, ITEMS keys each
-template <int BLOCK, int ITEMS>
+template <int BLOCK, int ITEMS, int BITS>
 struct DownLds {
+    static constexpr int kRadix = 1 << BITS;
     uint32_t key[BLOCK * ITEMS];
     float4 pay[BLOCK * ITEMS];           // values (as u32) or records
     uint32_t wcnt[BLOCK / kWave][kRadix];
@@ -617,12 +628,14 @@ struct DownLds {
 // next tile's keys are loaded while this one is ranked and written; the
 // payloads are loaded at the start of their own tile and wait in registers
 // through the ranking (loading them a tile ahead too took the registers of
-// three more keys per thread and was no faster).
-template <class PAY, int BLOCK, int ITEMS>
+// three more keys per thread and was no faster).  WIDTH: bits that the digits
+// of this pass have at most (a ballot each).
+template <class PAY, int WIDTH, int BLOCK, int ITEMS, int BITS>
 __device__ __forceinline__ void downsweep_tiles(uint64_t beg, uint64_t end, uint32_t shift, uint32_t mask,
                                                 const uint32_t* __restrict__ kin, uint32_t* __restrict__ kout,
                                                 const PAY* __restrict__ pin, PAY* __restrict__ pout,
-                                                DownLds<BLOCK, ITEMS>& S) {
+                                                DownLds<BLOCK, ITEMS, BITS>& S) {
+    constexpr int kRadix = 1 << BITS;
     constexpr int kRsItems = ITEMS, kDsBlock = BLOCK, kDsWaves = BLOCK / kWave, kRsTile = BLOCK * ITEMS;
     const int t = threadIdx.x, w = t / kWave, l = lane_id();
     PAY* s_pay = reinterpret_cast<PAY*>(S.pay);
@@ -655,7 +668,7 @@ __device__ __forceinline__ void downsweep_tiles(uint64_t beg, uint64_t end, uint
             const uint32_t d = (key[j] >> shift) & mask;
             uint64_t peers = __ballot(ok[j]);
 #pragma unroll
-            for (int bit = 0; bit < kDigitBits; ++bit) {
+            for (int bit = 0; bit < WIDTH; ++bit) {
                 const uint64_t b = __ballot((d >> bit) & 1u);
                 peers &= ((d >> bit) & 1u) ? b : ~b;
             }
@@ -716,8 +729,9 @@ __device__ __forceinline__ void downsweep_tiles(uint64_t beg, uint64_t end, uint
     }
 }
 
-template <int BLOCK, int ITEMS>
+template <int BLOCK, int ITEMS, int BITS>
 __device__ __forceinline__ void downsweep_body(const SortSet& set) {
+    constexpr int kRadix = 1 << BITS;
     // sort 0 takes the first s[0].G workgroups, sort 1 the next s[1].G
     const uint32_t g0 = (uint32_t)set.s[0].G;
     const int q = blockIdx.x < g0 ? 0 : 1;
@@ -734,7 +748,7 @@ __device__ __forceinline__ void downsweep_body(const SortSet& set) {
     pass_digit(a.count_is_T ? P.bits_T : P.bits, a.count_is_T ? P.passes_T : P.passes, (uint32_t)a.pass, &shift,
                &mask);
 
-    __shared__ DownLds<BLOCK, ITEMS> S;
+    __shared__ DownLds<BLOCK, ITEMS, BITS> S;
 
     uint32_t chunk;
     rs_chunk(n, a.G, (uint32_t)(BLOCK * ITEMS), &chunk);
@@ -753,25 +767,32 @@ __device__ __forceinline__ void downsweep_body(const SortSet& set) {
         if (t < kRadix) S.run[t] = base + a.counts[(size_t)t * a.G + bid];
     }
     __syncthreads();
-    if (a.rec[0]) {
-        const int passes = a.count_is_T ? (int)P.passes_T : (int)P.passes;
-        downsweep_tiles<float4>(beg, end, shift, mask, kin, kout, rec_after(a.rec[0], a.rec[1], passes, a.pass - 1),
-                                rec_after(a.rec[0], a.rec[1], passes, a.pass), S);
-    } else {
-        downsweep_tiles<uint32_t>(beg, end, shift, mask, kin, kout, pick2(a.vals[0], a.vals[1], (uint32_t)a.pass),
-                                  pick2(a.vals[0], a.vals[1], (uint32_t)a.pass + 1u), S);
-    }
+    auto tiles = [&](auto width) {
+        constexpr int W = decltype(width)::value;
+        if (a.rec[0]) {
+            const int passes = a.count_is_T ? (int)P.passes_T : (int)P.passes;
+            downsweep_tiles<float4, W>(beg, end, shift, mask, kin, kout, rec_after(a.rec[0], a.rec[1], passes, a.pass - 1),
+                                       rec_after(a.rec[0], a.rec[1], passes, a.pass), S);
+        } else {
+            downsweep_tiles<uint32_t, W>(beg, end, shift, mask, kin, kout,
+                                         pick2(a.vals[0], a.vals[1], (uint32_t)a.pass),
+                                         pick2(a.vals[0], a.vals[1], (uint32_t)a.pass + 1u), S);
+        }
+    };
+    if (BITS > 8 && mask > 255u) tiles(Int<BITS>{});
+    else if (BITS > 7 && mask > 127u) tiles(Int<8>{});
+    else tiles(Int<7>{});
 }
 
 // (each kernel runs only with the tile its upsweep cut the chunks for)
 __global__ __launch_bounds__(kDsLargeBlock) void k_rs_downsweep_large(SortSet set) {
     if (set.tile != kDsLargeBlock * kDsLargeItems) return;
-    downsweep_body<kDsLargeBlock, kDsLargeItems>(set);
+    downsweep_body<kDsLargeBlock, kDsLargeItems, kDsLargeBits>(set);
 }
 
 __global__ __launch_bounds__(kDsSmallBlock) void k_rs_downsweep_small(SortSet set) {
     if (set.tile != kDsSmallBlock * kDsSmallItems) return;
-    downsweep_body<kDsSmallBlock, kDsSmallItems>(set);
+    downsweep_body<kDsSmallBlock, kDsSmallItems, kDsSmallBits>(set);
 }
 
 // *sum += the workgroup's total of v, with one atomic per workgroup (atomics

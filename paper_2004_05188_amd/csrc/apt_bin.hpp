@@ -5,25 +5,26 @@
 namespace apt {
 
 // LSD radix sort of cell ids and target keys: the fewest passes of at most
-// kDigitBits each, the key's bits split evenly over them.  A narrower digit
-// has fewer values, so each tile's run of one digit is longer and leaves as
-// a longer contiguous write (2e9 ions, 29-bit cell ids, tiles of 256 x 11
-// keys: passes of 8, 7, 7, 7 bits bin in 124 ms, of 8, 8, 8, 5 bits in 128
-// ms; five passes of 6 bits were slower still).
-constexpr int kDigitBits = 8;
-constexpr int kRadix = 1 << kDigitBits;
-static_assert(kRadix <= kBlock, "one thread per digit in the sort's scans");
-
-// Downsweep tiles: 512 threads x 14 keys for large sorts (with 16-byte
-// records, 151 KB of LDS: one workgroup per CU), 256 x 8 for small ones,
-// whose few tiles per workgroup then still fill two workgroups per CU.  The
-// longer a tile, the longer each digit's run in it and the write that
-// carries the run (2e9 ions, 28-bit cell ids in four 7-bit passes: binning
-// 117 ms with tiles of 256 x 11 keys, 105 ms with 512 x 11, 103 ms with
-// 512 x 14; the 7.7e6-ion needle bins 0.85 ms per step with 512 x 14 and
-// 0.75 ms with 256 x 8).
-constexpr int kDsLargeBlock = 512, kDsLargeItems = 14;
-constexpr int kDsSmallBlock = 256, kDsSmallItems = 8;
+// `digit_bits` bits each, the key's bits split evenly over them (2e9 ions,
+// 29-bit cell ids, tiles of 256 x 11 keys: passes of 8, 7, 7, 7 bits bin in
+// 124 ms, of 8, 8, 8, 5 bits in 128 ms).
+//
+// Downsweep tiles and digits: 512 threads x 13 keys and up to 9 bits for
+// large sorts (with 16-byte records, 156 KB of LDS: one workgroup per CU),
+// 256 x 8 and up to 8 bits for small ones, whose few tiles per workgroup then
+// still fill two workgroups per CU.  A tile leaves each digit's records as one
+// run, and the next tile of the workgroup continues it; with one workgroup
+// per CU the lines that are open for 512 digits are 2 MB of an XCD's 4 MB of
+// L2, so a short run's line is still there for the next (4e8 ions, 25-bit cell
+// ids: four passes of 7 and 6 bits with 512 x 14 keys took 15.3 ms and moved
+// 1.04 times the algorithmic writes, three of 9, 8 and 8 bits take 14.8 ms at
+// 1.15, 1.07 and 1.02 times; with two or three workgroups per CU and tiles of 2048 keys
+// a pass of 8 bits was slower than one of 7.  The 7.7e6-ion needle bins 0.85
+// ms per step with 512 x 14 and 0.75 ms with 256 x 8).
+constexpr int kDsLargeBlock = 512, kDsLargeItems = 13, kDsLargeBits = 9;
+constexpr int kDsSmallBlock = 256, kDsSmallItems = 8, kDsSmallBits = 8;
+static_assert((1 << kDsLargeBits) <= kDsLargeBlock && (1 << kDsSmallBits) <= kDsSmallBlock,
+              "one thread per digit in the downsweep's scans");
 
 // bits of max_key (0 for 0)
 __host__ __device__ inline uint32_t key_bits(uint64_t max_key) {
@@ -33,9 +34,9 @@ __host__ __device__ inline uint32_t key_bits(uint64_t max_key) {
 }
 
 // passes that sort keys in [0, max_key]
-__host__ __device__ inline int sort_passes_for(uint64_t max_key) {
+__host__ __device__ inline int sort_passes_for(uint64_t max_key, int digit_bits) {
     const uint32_t b = key_bits(max_key);
-    return b == 0 ? 1 : (int)((b + kDigitBits - 1) / kDigitBits);
+    return b == 0 ? 1 : (int)((b + (uint32_t)digit_bits - 1u) / (uint32_t)digit_bits);
 }
 
 // the digit of pass `pass` over keys of `bits` bits sorted in `passes`
@@ -215,8 +216,8 @@ struct SortArgs {
     int32_t G;
     uint32_t* keys[2];
     uint32_t* vals[2];
-    uint32_t* counts;       // [256][G]
-    uint32_t* totals;       // [256]
+    uint32_t* counts;       // [digits][G]
+    uint32_t* totals;       // [digits]
     // records instead of values (rec[0] non-NULL): the 16-byte neighbour
     // records travel with their keys; the buffers alternate so that the
     // last active pass writes rec[0] (rec_after)
@@ -230,12 +231,13 @@ __host__ __device__ inline float4* rec_after(float4* rec0, float4* rec1, int pas
 }
 
 // One radix pass of up to two independent sorts in the same launches: sort
-// 0 takes the first s[0].G workgroups, sort 1 the next s[1].G (the scan: 256
+// 0 takes the first s[0].G workgroups, sort 1 the next s[1].G (the scan: radix
 // each).
 struct SortSet {
     SortArgs s[2];
     int32_t n;
     int32_t tile;   // keys per downsweep tile (the passes' chunks are whole tiles)
+    int32_t radix;  // digit values at most (the scan has a workgroup for each)
 };
 
 struct OrderArgs {
@@ -321,7 +323,8 @@ __global__ void k_count(CountArgs a);
 __global__ void k_plan(PlanArgs a);
 __global__ void k_compact(CompactArgs a);
 __global__ void k_keys(KeyArgs a);
-__global__ void k_rs_upsweep(SortSet a);
+template <int BITS>
+__global__ void k_rs_upsweep(SortSet a);           // digits of at most BITS bits
 __global__ void k_rs_scan(SortSet a);
 __global__ void k_rs_downsweep_large(SortSet a);   // kDsLargeBlock threads
 __global__ void k_rs_downsweep_small(SortSet a);   // kDsSmallBlock threads

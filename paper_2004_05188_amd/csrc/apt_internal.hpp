@@ -66,6 +66,7 @@ struct PlanParams {
     // > 0: the counting sort's counters per list, which bound the target keys
     // (0: the radix sort, whose passes do)
     uint32_t key_cap = 0;
+    int32_t digit_bits = 8;     // of a radix pass, at most
     // the automatic choice leaves out tile mode 1, mode 3 (their kernels are
     // not launched)
     int32_t no_tiles = 0, no_nbr = 0;
