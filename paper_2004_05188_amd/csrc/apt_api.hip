@@ -603,6 +603,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     pp.r_enum = do_rdf ? rb->r_max : 0.0f;
     pp.h_shrink = 0.7f;
     pp.rdf_kernel = tu.rdf_kernel;
+    pp.same_species = q.target == q.neighbor;
     // kernels that the plan cannot choose for a cloud of this size are not
     // launched (about 4 us each, even to exit at once)
     if (pp.tile_policy == 0) {
@@ -655,6 +656,9 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     pa.self_possible = q.target == APT_ANY || q.neighbor == APT_ANY || q.target == q.neighbor;
     pa.lab = cl->lab;
     pa.nbr_species = q.neighbor;
+    pa.d_bnd = cl->d_bnd;
+    pa.d_srf = q.d_srf;
+    pa.elig = reinterpret_cast<uint8_t*>(w.K[0]);   // (the target sort's keys, no longer needed)
     int n_bins = 1;
     bool in_lds = false;
     if (do_rdf) {
@@ -710,7 +714,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
         const size_t nl = nbr_lds_bytes(n_bins, in_lds);
         auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(resident_grid(kern, nl)), dim3(kBlock), nl, st, pa); };
         if (self)
-            hipLaunchKernelGGL(k_nbr_self, dim3(std::max(1, device_info().cus * 2)), dim3(kBlock), 0, st, pa);
+            hipLaunchKernelGGL(k_nbr_prep, dim3(std::max(1, device_info().cus * 2)), dim3(kBlock), 0, st, pa);
         if (in_lds) go(k_rdf_nbr<kRdfLds>);
         else go(k_rdf_nbr<kRdfGlobal>);
         if (tu.rdf_kernel == 2) {

@@ -332,6 +332,11 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
     P.rk_tile = pp.k > 0 ? (float)fmin((P.tile_mode == 3 ? 1.3 : 1.6) / 1.15 * (double)P.rk0, (double)P.r_all)
                          : 0.0f;
     P.rdf_nbr = (P.tile_mode == 3 && pp.rdf_kernel != 2) ? 1 : 0;
+    // one species against itself: each unordered pair of neighbours once,
+    // counted for each of its ends that is a target, is half the work of every
+    // neighbour against every target when all are targets, and as much when
+    // half are
+    P.nbr_sym = (P.rdf_nbr && pp.same_species && 5ull * totT >= 3ull * totB) ? 1 : 0;
     *a.plan = P;
     if (s_nf[0] && a.status) atomicOr(a.status, APT_STATUS_NONFINITE);
 }

@@ -44,6 +44,7 @@ struct GridPlan {
                         // neighbours, kNN radius well below r_max)
     float rk_tile;      // kNN radius certified by the tile pass
     int32_t rdf_nbr;    // mode 3: the RDF runs neighbour-major (k_rdf_nbr), else one target per wavefront
+    int32_t nbr_sym;    // ... over unordered pairs of neighbours, of which the targets are most
 };
 
 // Host-chosen parameters of the plan.
@@ -67,6 +68,7 @@ struct PlanParams {
     // (0: the radix sort, whose passes do)
     uint32_t key_cap = 0;
     int32_t digit_bits = 8;     // of a radix pass, at most
+    int32_t same_species = 0;   // targets and neighbours are the same species: every target is a neighbour
     // the automatic choice leaves out tile mode 1, mode 3 (their kernels are
     // not launched)
     int32_t no_tiles = 0, no_nbr = 0;

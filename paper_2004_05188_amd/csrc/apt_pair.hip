@@ -413,15 +413,18 @@ size_t nbr_lds_bytes(int n_bins, bool hist_in_lds) {
     return b + (size_t)kWavesPerBlock * kNbrList * sizeof(float4);
 }
 
-// (at most 64 VGPRs: eight wavefronts per SIMD)
-template <int FLAGS>
-__global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
+//
+// SYM (one species against itself, most of it targets): a chunk meets the
+// records after it instead of every target, and a pair counts once for each
+// end that is a target, so each unordered pair is evaluated once: half the
+// evaluations when all are targets (1e6 ions, every ion against every ion:
+// the call 1.83 -> 0.99 ms, 0.90 of it this kernel).  The chunk's own pairs
+// are taken first.
+template <int FLAGS, bool SYM>
+__device__ __forceinline__ void rdf_nbr_body(const PairArgs& a, const GridPlan& P, uint8_t* smem) {
     constexpr bool COUNT = (FLAGS & kCountEvals) != 0;
     constexpr bool LDS_HIST = !COUNT && (FLAGS & kRdfLds) != 0;
-    const GridPlan P = *a.plan;
-    if (P.tile_mode != 3 || !P.rdf_nbr) return;
     unsigned long long evals = 0;   // COUNT: pair evaluations (records x staged targets)
-    extern __shared__ __align__(16) uint8_t smem[];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int l = lane_id();
     uint32_t* hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
@@ -443,7 +446,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     // cloud with fewer chunks than that splits each chunk's targets into
     // `split` items: 1e6 ions, every ion against every ion, are 15 600 chunks,
     // which in batches of 16 kept 977 of 8192 wavefronts busy (the call 8.71 ms,
-    // now 2.01 ms).  2^32 - 1 neighbours are 6.7e7 items at most.
+    // 2.01 ms in these).  2^32 - 1 neighbours are 6.7e7 items at most.
     const uint32_t n_own = (n_chunks + kXcd - 1) / kXcd;          // of an XCD
     const uint32_t n_waves = gridDim.x / kXcd * kWavesPerBlock;   // of an XCD
     uint32_t lg_split = 0;
@@ -455,7 +458,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     const float thr2 = a.thr2, inv_w = a.inv_w, lo_b = a.delta_b, hi_b = 1.0f - a.delta_b;
     const float half_band = 0.5f - a.delta_b;   // |fract - 1/2| beyond it: within delta_b of an edge
     uint32_t since_flush = 0;
-    const uint32_t flush_at = 0xFFFFFFFFu - (uint32_t)(kWave * kNbrList);
+    const uint32_t flush_at = 0xFFFFFFFFu - (uint32_t)(4 * kWave * kNbrList);
 
     int x = blockIdx.x % kXcd, empty = 0;
     uint32_t ib, ie;
@@ -468,6 +471,45 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
         const bool valid = j < nB;
         const float4 rec = a.bpos[valid ? j : nB - 1];
         const bool fin0 = valid && isfinite(rec.x) && isfinite(rec.y) && isfinite(rec.z);
+        const uint32_t mine = SYM && fin0 ? a.elig[j] : 0u;   // this lane's record is a target
+        // one pair of this lane's record, at squared distance d2 < thr2
+        auto count = [&](float tx, float ty, float tz, float d2, uint32_t weight) {
+            const float tt = __builtin_amdgcn_sqrtf(d2) * inv_w;
+            int b = (int)tt;
+            if (LDS_HIST) {
+                // b == n_bins (beyond r_max) lands in the spare counter
+                if (__builtin_expect(fabsf(__builtin_amdgcn_fractf(tt) - 0.5f) > half_band, 0))
+                    b = exact_bin(exact_D2(tx, ty, tz, rec.x, rec.y, rec.z), a.E2, a.n_bins, a.inv_w64);
+                atomicAdd(&hist_l[b], weight);
+            } else {
+                const float fr = tt - (float)b;
+                if (__builtin_expect(fr < lo_b || fr > hi_b, 0))
+                    b = exact_bin(exact_D2(tx, ty, tz, rec.x, rec.y, rec.z), a.E2, a.n_bins, a.inv_w64);
+                if (b < a.n_bins && weight) atomicAdd((unsigned long long*)&a.hist[b], (unsigned long long)weight);
+            }
+        };
+        auto counted = [&](uint32_t most) {   // counts added since the last call, at most
+            since_flush += most;
+            if (since_flush >= flush_at) {
+                flush_hist(hist_l, a.hist, a.n_bins);
+                since_flush = 0;
+            }
+        };
+        if (SYM && part == 0u) {
+            // the pairs within the chunk: lane t's record against the lanes before it
+            if (COUNT) evals += (unsigned long long)(kWave * (kWave - 1));
+            else for (int t = 1; t < kWave; ++t) {
+                const float tx = readlane(rec.x, t), ty = readlane(rec.y, t), tz = readlane(rec.z, t);
+                const uint32_t both = mine + readlane(mine, t);
+                const float dx = rec.x - tx, dy = rec.y - ty, dz = rec.z - tz;
+                const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                if (fin0 && l < t && c * (uint32_t)kWave + (uint32_t)t < nB && d2 < thr2) count(tx, ty, tz, d2, both);
+            }
+            if (LDS_HIST) {
+                wave_sync();
+                counted(2u * kWave * kWave);
+            }
+        }
         // a run of 64 records may end one cell row and start the next, far
         // apart in x: each row's part is evaluated with its own bounding box
         const uint32_t crow = fin0 ? (uint32_t)cell_axis(P, 2, rec.z) * (uint32_t)P.dim[1] +
@@ -506,32 +548,13 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
                     const float dx = rec.x - T.x, dy = rec.y - T.y, dz = rec.z - T.z;
                     const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
                     // (a target's pair with its own record lands in bin 0
-                    // here and is taken off by k_nbr_self)
-                    if (fin && d2 < thr2) {
-                        const float tt = __builtin_amdgcn_sqrtf(d2) * inv_w;
-                        int b = (int)tt;
-                        if (LDS_HIST) {
-                            // b == n_bins (beyond r_max) lands in the spare counter
-                            if (__builtin_expect(fabsf(__builtin_amdgcn_fractf(tt) - 0.5f) > half_band, 0))
-                                b = exact_bin(exact_D2(T.x, T.y, T.z, rec.x, rec.y, rec.z), a.E2, a.n_bins, a.inv_w64);
-                            atomicAdd(&hist_l[b], 1u);
-                        } else {
-                            const float fr = tt - (float)b;
-                            if (__builtin_expect(fr < lo_b || fr > hi_b, 0))
-                                b = exact_bin(exact_D2(T.x, T.y, T.z, rec.x, rec.y, rec.z), a.E2, a.n_bins, a.inv_w64);
-                            if (b < a.n_bins) atomicAdd((unsigned long long*)&a.hist[b], 1ull);
-                        }
-                    }
+                    // here and is taken off by k_nbr_prep)
+                    if (fin && d2 < thr2)
+                        count(T.x, T.y, T.z, d2, SYM ? mine + __builtin_bit_cast(uint32_t, T.w) : 1u);
                 }
                 wave_sync();
-                if (LDS_HIST) {
-                    // at most cnt * 64 counts were added
-                    since_flush += (uint32_t)cnt * n_rec;
-                    if (since_flush >= flush_at) {
-                        flush_hist(hist_l, a.hist, a.n_bins);
-                        since_flush = 0;
-                    }
-                }
+                // (at most cnt * 64 pairs)
+                if (LDS_HIST) counted((uint32_t)cnt * n_rec * (SYM ? 2u : 1u));
             };
 
             // target rows that the box grown by Re meets, each trimmed in x
@@ -544,7 +567,14 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
                 const int r = rb + l;
                 uint32_t st = 0, len = 0;
                 if (r < nrows)
-                    row_span(P, a.t_cell_start, cy0 + r % ny, cz0 + r / ny, x0, y0, z0, x1, y1, z1, R2, st, len);
+                    row_span(P, SYM ? a.cell_start : a.t_cell_start, cy0 + r % ny, cz0 + r / ny, x0, y0, z0, x1, y1, z1,
+                             R2, st, len);
+                if (SYM) {
+                    // the records after the chunk
+                    const uint32_t last = c * (uint32_t)kWave + 63u, cut = last >= st ? last - st + 1u : 0u;
+                    st += cut < len ? cut : len;
+                    len -= cut < len ? cut : len;
+                }
                 const uint32_t inc = wave_incl_scan(len);
                 const uint32_t all = readlane(inc, kWave - 1);
                 const uint32_t offr = inc - len;
@@ -567,11 +597,20 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
                     const uint32_t base = (uint32_t)__shfl((int)(st - offr), row, kWave);
                     bool keep = v < tot;
                     float tx = 0.0f, ty = 0.0f, tz = 0.0f;
+                    uint32_t its = 0;
                     if (keep) {
                         const uint32_t q = base + v;
-                        tx = a.tx[q];
-                        ty = a.ty[q];
-                        tz = a.tz[q];
+                        if (SYM) {
+                            const float4 o = a.bpos[q];
+                            its = a.elig[q];
+                            tx = o.x;
+                            ty = o.y;
+                            tz = o.z;
+                        } else {
+                            tx = a.tx[q];
+                            ty = a.ty[q];
+                            tz = a.tz[q];
+                        }
                         // exact cull against the records' box (a pair within
                         // r_max lies within r_max of the box)
                         const float ex = fmaxf(0.0f, fmaxf(x0 - tx, tx - x1));
@@ -580,7 +619,8 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
                         keep = isfinite(tx) && isfinite(ty) && isfinite(tz) && ex * ex + ey * ey + ez * ez <= R2;
                     }
                     const uint64_t m = __ballot(keep);
-                    if (keep) list[cnt + __popcll(m & lanemask_lt())] = make_float4(tx, ty, tz, 0.0f);
+                    if (keep) list[cnt + __popcll(m & lanemask_lt())] =
+                        make_float4(tx, ty, tz, __builtin_bit_cast(float, its));
                     cnt += __popcll(m);
                     if (cnt > kNbrList - kWave) {
                         run(cnt);
@@ -596,12 +636,27 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     if (COUNT && l == 0 && evals) atomicAdd((unsigned long long*)a.hist, evals);
 }
 
+// (at most 64 VGPRs: eight wavefronts per SIMD)
+template <int FLAGS>
+__global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    const GridPlan P = *a.plan;
+    if (P.tile_mode != 3 || !P.rdf_nbr) return;
+    if (P.nbr_sym) rdf_nbr_body<FLAGS, true>(a, P, smem);
+    else rdf_nbr_body<FLAGS, false>(a, P, smem);
+}
+
 template __global__ void k_rdf_nbr<kRdfLds>(PairArgs);
 template __global__ void k_rdf_nbr<kRdfGlobal>(PairArgs);
 
-__global__ __launch_bounds__(kBlock) void k_nbr_self(PairArgs a) {
+__global__ __launch_bounds__(kBlock) void k_nbr_prep(PairArgs a) {
     const GridPlan P = *a.plan;
     if (P.tile_mode != 3 || !P.rdf_nbr) return;
+    if (P.nbr_sym) {
+        for (uint64_t j = blockIdx.x * kBlock + threadIdx.x; j < P.nB; j += gridDim.x * kBlock)
+            a.elig[j] = a.d_bnd == nullptr || a.d_bnd[__builtin_bit_cast(uint32_t, a.bpos[j].w)] >= a.d_srf;
+        return;
+    }
     uint32_t cnt = 0;
     for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < P.nT; q += gridDim.x * kBlock) {
         if (!(isfinite(a.tx[q]) && isfinite(a.ty[q]) && isfinite(a.tz[q]))) continue;

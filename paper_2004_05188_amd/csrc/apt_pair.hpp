@@ -19,6 +19,9 @@ struct PairArgs {
     int32_t self_possible;       // a target may also be a neighbour
     const uint8_t* lab;          // [n] species labels
     int32_t nbr_species;         // species of the neighbours (or APT_ANY)
+    const float* d_bnd;          // [n] or NULL, and the targets' least value (k_nbr_prep)
+    float d_srf;
+    uint8_t* elig;               // [nB] by record: 1 if it is a target too (k_nbr_prep, when the plan says nbr_sym)
     // RDF
     int32_t n_bins;
     float r_enum;                // enumeration radius covering every counted pair
@@ -78,12 +81,13 @@ size_t tile_lds_bytes(bool rdf, int n_bins);
 // chose mode 3.
 template <int FLAGS>
 __global__ void k_rdf_nbr(PairArgs a);
-// With targets that may be neighbours the neighbour-major kernel also counts
-// each such target against its own record (distance 0, bin 0) instead of
-// testing identities per pair: this kernel takes those counts off bin 0
-// (every target with a finite position whose species is a neighbour's).
-// Exits unless the plan chose mode 3 with the neighbour-major RDF.
-__global__ void k_nbr_self(PairArgs a);
+// Before it, when targets may be neighbours.  The kernel counts each such
+// target against its own record (distance 0, bin 0) instead of testing
+// identities per pair: this one takes those counts off bin 0 (every target
+// with a finite position whose species is a neighbour's).  Where the plan
+// says nbr_sym, it writes instead which records are targets.  Exits unless the
+// plan chose mode 3 with the neighbour-major RDF.
+__global__ void k_nbr_prep(PairArgs a);
 // Mode 3 with the RDF one target per wavefront (tuning rdf_kernel 2): RDF
 // of every target, eight wavefronts per SIMD; exits otherwise.
 template <int FLAGS>

@@ -140,3 +140,42 @@ def test_tiles_with_many_candidates(orc, blob):
         assert np.allclose(gd, dist, rtol=1e-6, atol=0)
         assert np.array_equal(g.knn_hist.cpu().numpy().astype(np.uint64), h)
         assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, 0, 1, 1.0, 2.0, 100))
+
+
+@pytest.mark.parametrize("n,A,d_srf,n_bins,k", [
+    (1 << 18, 1, 0.0, 200, 0), ((1 << 18) + 37, ANY, 0.0, 4000, 0),   # all targets; counters in LDS and global
+    (2_000, ANY, 0.1, 200, 0), ((1 << 18) + 1, 1, 0.38, 200, 0), ((1 << 18) + 1, 1, 0.42, 200, 0),   # either side of three targets in five
+    ((1 << 19) + 4100, ANY, 0.38, 200, 4), ((1 << 20) + 63, ANY, 0.3, 200, 0),   # chunks split less
+])
+def test_unordered_pairs_of_one_species(n, A, d_srf, n_bins, k):
+    """One species against itself with the neighbour-major RDF (each unordered pair once, weighted by its ends that
+    are targets), against one target per wavefront: with ions in the same place, a cell of many chunks, positions
+    that are not finite and a last chunk that is not full."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    print(f"case unordered pairs n={n} A={A} d_srf={d_srf} n_bins={n_bins} k={k}", flush=True)
+    xyz, lab, _ = _box(torch, n, 0.9, n)
+    g = torch.Generator("cuda").manual_seed(3)
+    xyz[:700] = xyz[700] + 0.05 * torch.rand((700, 3), generator=g, device="cuda")
+    xyz[1000:1100] = xyz[1100:1200]
+    xyz[1500] = float("nan")
+    xyz[1501, 1] = float("inf")
+    d = torch.rand(n, generator=g, device="cuda")
+    cloud = aptstat.Cloud(xyz, lab, d)
+    ws = aptstat.Workspace()
+
+    def hist():
+        if k:
+            return aptstat.knn_rdf(cloud, A, A, d_srf, k, r_max=1.2, n_bins=n_bins, ws=ws).rdf_hist.cpu().numpy()
+        return aptstat.rdf(cloud, A, A, d_srf, 1.2, n_bins, ws=ws).cpu().numpy()
+
+    try:
+        out = []
+        for policy in (4, 1):
+            aptstat.set_tuning(tile_policy=policy)
+            out.append(hist())
+    finally:
+        aptstat.set_tuning()
+    assert np.array_equal(out[0], out[1]) and out[0].sum() > 0
