@@ -347,6 +347,17 @@ __device__ __forceinline__ int kth_bin_fp32(float d2, int kb_nbins, double kb_in
 // 64 targets of a tile are close together.
 constexpr int kStage = 512;   // records per staging chunk (16 B each)
 
+// Whether a record can lie within R of the box (R2 = (R + eps)^2).  The rows
+// that enumerate_box trims end at whole cells, a third or more of whose records
+// lie farther: tested once per record of a tile, by one lane, they are never
+// scanned by 64 (KCULL).
+__device__ __forceinline__ bool box_near(float4 c, float x0, float y0, float z0, float x1, float y1, float z1, float R2) {
+    const float ex = fmaxf(0.0f, fmaxf(x0 - c.x, c.x - x1));
+    const float ey = fmaxf(0.0f, fmaxf(y0 - c.y, c.y - y1));
+    const float ez = fmaxf(0.0f, fmaxf(z0 - c.z, c.z - z1));
+    return ex * ex + ey * ey + ez * ez <= R2;
+}
+
 template <int KMAX>
 struct TopK {
     uint64_t key[KMAX > 0 ? KMAX : 1];
@@ -385,7 +396,9 @@ __device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, b
         wave_sync();
     };
     int m = 0;   // staged records
+    const float Re = T.r_enum + P.eps, Re2 = Re * Re;
     enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, T.r_enum, [&](bool v, float4 c) {
+        v = v && box_near(c, x0, y0, z0, x1, y1, z1, Re2);
         const uint64_t bal = __ballot(v);
         const int nn = __popcll(bal);
         if (m + nn > kStage) {
@@ -406,7 +419,7 @@ __device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, b
 // unless a record left out could tie: its value, so its distance rounded
 // down, is at least the last one kept.  Keeping the 64-bit keys themselves in
 // order cost a 64-bit comparison and four selects per place and candidate
-// (7.5e6 dense targets, k = 10: 2.64 ms, now 1.56 with the tiles cut at regions).
+// (7.5e6 dense targets, k = 10: 2.64 ms against 1.56).
 // Returns false, with nothing counted, when the stage cannot hold the tile's
 // records (the caller leaves its targets to the one-by-one pass); *unsure:
 // this lane's rows may miss a tie and have to be searched again.
@@ -434,7 +447,9 @@ __device__ __forceinline__ bool run_tile_packed(const GridPlan& P, const PairTas
     const float z0 = wave_min_f(fin ? pz : INFINITY), z1 = wave_max_f(fin ? pz : -INFINITY);
     const float R = RDF ? fmaxf(T.r_enum, Rk * 1.000001f) : Rk * 1.000001f;
     int m = 0;
+    const float Re = R + P.eps, Re2 = Re * Re;
     enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, R, [&](bool v, float4 c) {
+        v = v && box_near(c, x0, y0, z0, x1, y1, z1, Re2);
         const uint64_t bal = __ballot(v);
         const int nn = __popcll(bal);
         if (v && m + nn <= kStage) stage[m + __popcll(bal & lanemask_lt())] = c;
@@ -666,8 +681,10 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
     };
     int m = 0;              // records in the stage
     bool once = true;       // it holds all of the tile's
-    auto stage_one = [&](auto&& sc) {
-        return [&, sc](bool v, float4 c) {
+    auto stage_one = [&](auto&& sc, float Rs) {
+        const float Re = Rs + P.eps, Re2 = Re * Re;
+        return [&, sc, Re2](bool v, float4 c) {
+            v = v && box_near(c, x0, y0, z0, x1, y1, z1, Re2);
             const uint64_t bal = __ballot(v);
             const int nn = __popcll(bal);
             if (m + nn > kStage) {
@@ -679,7 +696,7 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
             m += nn;
         };
     };
-    enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, R, stage_one(scan), true);
+    enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, R, stage_one(scan, R), true);
     if (m > 0) scan(m);
 
     // the k-th distance and how many of the k nearest lie strictly nearer
@@ -730,7 +747,8 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
             wave_sync();
         };
         m = 0;
-        enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, sqrtf(tmax) * 1.000001f, stage_one(scan2));
+        const float Rt = sqrtf(tmax) * 1.000001f;
+        enumerate_box(P, T.cell_start, T.bpos, x0, y0, z0, x1, y1, z1, Rt, stage_one(scan2, Rt));
         if (m > 0) scan2(m);
     }
     settled = settled && jk != 0xFFFFFFFFu;
