@@ -611,7 +611,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
         // if there is no other species)
         if (cl->n < (do_knn ? kTileMinKnn : kTileMinRdf) || (q.neighbor == APT_ANY && q.target != APT_ANY))
             pp.no_tiles = 1;
-        if (cl->n < (do_knn ? kNbrMinKnn : kNbrMinRdf)) pp.no_nbr = 1;
+        if (!do_rdf || cl->n < (do_knn ? kNbrMinKnn : kNbrMinRdf)) pp.no_nbr = 1;
         if (pp.no_tiles && pp.no_nbr) pp.tile_policy = 1;
     }
     {
@@ -673,7 +673,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
         double delta = fmax(1e-6, 2e-6 * rmax);
         double delta_b = fmax(delta / w_bin, 4e-6 * n_bins);
         if (delta_b > 0.25) delta_b = 0.25;
-        pa.delta_b = (float)delta_b;
+        pa.half_band = 0.5f - (float)delta_b;
         pa.inv_w = (float)(n_bins / rmax);
         pa.inv_w64 = n_bins / rmax;
         pa.thr2 = (float)((rmax * (1.0 + 2e-5)) * (rmax * (1.0 + 2e-5)));
@@ -707,13 +707,33 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     pa.n_targets = do_knn ? n_targets : nullptr;
     pa.status = status;
     const size_t lds = pair_lds_bytes(do_rdf, do_knn, n_bins, in_lds);
-    if (pp.tile_policy != 1 && do_rdf && !pp.no_nbr) {
+    const int km = !do_knn ? 0 : k <= 4 ? 4 : k <= 10 ? 10 : 16;
+    // one target per lane: the kNN of mode 3 (before the RDF kernel, for which
+    // it prepares), or with the RDF of mode 2, which only the tuning chooses
+    const bool lane_rdf = do_rdf && pp.tile_policy == 3;
+    if (pp.tile_policy != 1 && (lane_rdf || (do_knn && !pp.no_nbr && pp.tile_policy != 2))) {
+        TraceSpan span("lane", st);
+        const bool self = pa.self_possible != 0;
+        const size_t tl = tile_lds_bytes(lane_rdf, n_bins);
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(resident_grid(kern, tl)), dim3(kBlock), tl, st, pa); };
+        if (lane_rdf) {
+            if (km == 0) self ? go(k_pair_lane<kRdfLds | kSelf, 0>) : go(k_pair_lane<kRdfLds, 0>);
+            else if (km == 4) self ? go(k_pair_lane<kRdfLds | kSelf, 4>) : go(k_pair_lane<kRdfLds, 4>);
+            else if (km == 10) self ? go(k_pair_lane<kRdfLds | kSelf, 10>) : go(k_pair_lane<kRdfLds, 10>);
+            else self ? go(k_pair_lane<kRdfLds | kSelf, 16>) : go(k_pair_lane<kRdfLds, 16>);
+        } else {
+            if (km == 4) self ? go(k_pair_lane<kSelf, 4>) : go(k_pair_lane<0, 4>);
+            else if (km == 10) self ? go(k_pair_lane<kSelf, 10>) : go(k_pair_lane<0, 10>);
+            else self ? go(k_pair_lane<kSelf, 16>) : go(k_pair_lane<0, 16>);
+        }
+    }
+    if (pp.tile_policy != 1 && do_rdf && !pp.no_nbr && pp.tile_policy != 3) {
         // the RDF neighbour-major when the plan chooses mode 3 (exits otherwise)
         TraceSpan span("nbr", st);
         const bool self = pa.self_possible != 0;
         const size_t nl = nbr_lds_bytes(n_bins, in_lds);
         auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(resident_grid(kern, nl)), dim3(kBlock), nl, st, pa); };
-        if (self)
+        if (self && !do_knn)
             hipLaunchKernelGGL(k_nbr_prep, dim3(std::max(1, device_info().cus * 2)), dim3(kBlock), 0, st, pa);
         if (in_lds) go(k_rdf_nbr<kRdfLds>);
         else go(k_rdf_nbr<kRdfGlobal>);
@@ -725,13 +745,12 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
             else self ? go2(k_rdf_tgt<kRdfGlobal | kSelf>) : go2(k_rdf_tgt<kRdfGlobal>);
         }
     }
-    if (pp.tile_policy != 1 && (do_knn || !pp.no_tiles)) {
+    if (pp.tile_policy != 1 && !pp.no_tiles && tu.tile_policy < 3) {
         // 64 targets per wavefront when the plan chooses it (exits otherwise)
         TraceSpan span("tile", st);
         const bool self = pa.self_possible != 0;
         const size_t tl = tile_lds_bytes(do_rdf, n_bins);
         auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(resident_grid(kern, tl)), dim3(kBlock), tl, st, pa); };
-        const int km = !do_knn ? 0 : k <= 4 ? 4 : k <= 10 ? 10 : 16;
         if (do_rdf) {
             if (km == 0) self ? go(k_pair_tile<kRdfLds | kSelf, 0>) : go(k_pair_tile<kRdfLds, 0>);
             else if (km == 4) self ? go(k_pair_tile<kRdfLds | kSelf, 4>) : go(k_pair_tile<kRdfLds, 4>);
@@ -967,7 +986,7 @@ static apt_status run_batched(const apt_cloud* cl, const apt_query* pairs, int32
         ba.r_enum = (float)((double)rb.r_max * (1.0 + 4e-5));
         ba.thr2 = (float)(((double)rb.r_max * (1.0 + 2e-5)) * ((double)rb.r_max * (1.0 + 2e-5)));
         ba.inv_w = (float)(rb.n_bins / (double)rb.r_max);
-        ba.delta_b = (float)delta_b;
+        ba.half_band = 0.5f - (float)delta_b;
         ba.inv_w64 = rb.n_bins / (double)rb.r_max;
         ba.E2 = w.plain.E2;
         ba.rdf_hist = rdf_hist;

@@ -17,7 +17,7 @@
 namespace apt {
 
 size_t batched_lds_bytes(int n_bins) {
-    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u;
+    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u;
     b = (b + 15) & ~size_t(15);
     return b + (size_t)kWavesPerBlock * kKnnCap * 8u;
 }
@@ -25,7 +25,7 @@ size_t batched_lds_bytes(int n_bins) {
 // tiles: histogram + staging buffer (which later holds a straggler's kNN keys)
 size_t batched_tile_lds_bytes(int n_bins) {
     static_assert(kStage * sizeof(float4) >= kKnnCap * sizeof(uint64_t), "key buffer inside the stage");
-    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u;
+    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u;
     b = (b + 15) & ~size_t(15);
     return b + (size_t)kWavesPerBlock * kStage * sizeof(float4);
 }
@@ -286,17 +286,16 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
     T.r_enum = a.r_enum;
     T.thr2 = a.thr2;
     T.inv_w = a.inv_w;
-    T.lo_b = a.delta_b;
-    T.hi_b = 1.0f - a.delta_b;
+    T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
     T.k = a.k;
     T.rknn = INFINITY;
     T.rknn2 = INFINITY;
-    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u + 15) & ~size_t(15);
+    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u + 15) & ~size_t(15);
     T.kbuf = reinterpret_cast<uint64_t*>(smem + off) + (size_t)w * kKnnCap;
-    for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
+    for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
 
     const int RP = a.R * a.n_pairs;
@@ -304,6 +303,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
     const double vol = batch_volume(a, P);
     int cur = -1;                     // (replicate, pair) of the LDS histogram contents
     uint32_t since_flush = 0;
+    const uint32_t flush_at = flush_limit((uint64_t)a.n);
     uint64_t seg_a0 = 0;
     const float* d_bnd = a.d_bnd;
     float d_srf = 0.0f;
@@ -347,8 +347,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
             const float px = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, rec.x)));
             const float py = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, rec.y)));
             const float pz = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, rec.z)));
-            uint32_t hits = 0;
-            const int found = run_target<kRdfLds | kSelf, true>(P, T, px, py, pz, i, hits);
+            uint32_t steps = 0;
+            const int found = run_target<kRdfLds | kSelf, true>(P, T, px, py, pz, i, steps);
             if (a.knn_hist && l == 0) {
                 const int b = kth_bin(found, a.k, T.kbuf, a.xyz, px, py, pz, a.KE2, a.kb_nbins, a.kb_inv_w64);
                 atomicAdd((unsigned long long*)&a.knn_hist[((size_t)(a.rep0 + r) * a.n_pairs + p) *
@@ -356,8 +356,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
                           1ull);
             }
             wave_sync();
-            since_flush += wave_sum(hits);
-            if (since_flush >= 0x7FFFFFFFu - (uint32_t)min((uint64_t)a.n, (uint64_t)0x7FFFFFFFu)) {
+            since_flush += steps * kWave;
+            if (since_flush >= flush_at) {
                 flush_hist(T.hist_l, T.hist_g, a.n_bins);
                 since_flush = 0;
             }
@@ -386,22 +386,30 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
     T.r_enum = a.r_enum;
     T.thr2 = a.thr2;
     T.inv_w = a.inv_w;
-    T.lo_b = a.delta_b;
-    T.hi_b = 1.0f - a.delta_b;
+    T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
     T.k = a.k;
     T.rknn = INFINITY;
     T.rknn2 = INFINITY;
-    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u + 15) & ~size_t(15);
+    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u + 15) & ~size_t(15);
     float4* stage = reinterpret_cast<float4*>(smem + off) + (size_t)w * kStage;
     T.kbuf = reinterpret_cast<uint64_t*>(stage);      // used only after the tile pass
-    for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
+    for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
 
     int cur = -1;
+    // u32 LDS counters: flushed before a further scan (kStage records of 64
+    // lanes) could overflow them
     uint32_t since_flush = 0;
+    auto counted = [&](uint32_t most) {
+        since_flush += most;
+        if (since_flush >= 0xFFFFFFFFu - (uint32_t)(kStage * kWave)) {
+            flush_hist(T.hist_l, T.hist_g, a.n_bins);
+            since_flush = 0;
+        }
+    };
     uint64_t seg_a0 = 0, seg_len = 0;
     float d_srf = 0.0f, Rk = 0.0f;
     int rp = 0;
@@ -448,7 +456,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
             pz = rec.z;
             valid0 = a.d_bnd == nullptr || a.d_bnd[i] >= d_srf;
         }
-        uint32_t hits = 0;
         // (cell order: a tile that runs over the end of a row of cells is
         // taken a row at a time, or its box would span the specimen)
         const uint32_t row = isfinite(py + pz) ? (uint32_t)cell_axis(P, 2, pz) * (uint32_t)P.dim[1] +
@@ -458,7 +465,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
         while (todo) {
         const bool valid = valid0 && row == readlane(row, __builtin_ctzll(todo));
         todo &= ~__ballot(valid);
-        const uint64_t kth = run_tile_kth<kRdfLds | kSelf, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, hits,
+        const uint64_t kth = run_tile_kth<kRdfLds | kSelf, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, counted,
                                                                  a.knn_hist ? a.kb_nbins : 0, a.kb_inv_w64);
         const bool fin = isfinite(px) && isfinite(py) && isfinite(pz);
         const bool certified = valid && (kth != ~0ull || !fin);
@@ -478,20 +485,15 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
             const float tx = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, px), ln));
             const float ty = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, py), ln));
             const float tz = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pz), ln));
-            uint32_t h2 = 0;
+            uint32_t steps = 0;
             wave_sync();
-            const int found = run_target<kSelf, true>(P, T, tx, ty, tz, ti, h2, false);
+            const int found = run_target<kSelf, true>(P, T, tx, ty, tz, ti, steps, false);
             if (kh && l == 0) {
                 const int b = kth_bin(found, a.k, T.kbuf, a.xyz, tx, ty, tz, a.KE2, a.kb_nbins, a.kb_inv_w64);
                 atomicAdd((unsigned long long*)&kh[b], 1ull);
             }
             wave_sync();
         }
-        }
-        since_flush += wave_sum(hits);
-        if (since_flush >= 0x7FFFFFFFu - (uint32_t)min((uint64_t)a.n * kWave, (uint64_t)0x7FFFFFFFu)) {
-            flush_hist(T.hist_l, T.hist_g, a.n_bins);
-            since_flush = 0;
         }
     }
     }

@@ -58,7 +58,7 @@ struct BatchPairArgs {
     float tile_reach;         // certified kNN reach of a tile, times the Poisson mean k-th distance
     // RDF
     int32_t n_bins;
-    float r_enum, thr2, inv_w, delta_b;
+    float r_enum, thr2, inv_w, half_band;
     double inv_w64;
     const double* E2;
     uint64_t* rdf_hist;       // [n_rep][n_pairs][n_bins]

@@ -27,7 +27,7 @@ namespace apt {
 
 size_t pair_lds_bytes(bool rdf, bool knn, int n_bins, bool hist_in_lds) {
     size_t b = 0;
-    if (rdf && hist_in_lds) b += (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u;
+    if (rdf && hist_in_lds) b += (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u;
     b = (b + 15) & ~size_t(15);
     if (knn) b += (size_t)kWavesPerBlock * kKnnCap * 8u;
     return b;
@@ -82,8 +82,8 @@ __device__ __forceinline__ void pair_items(const PairArgs& a, const GridPlan& P,
             n_py = a.ty[q];
             n_pz = a.tz[q];
         }
-        uint32_t hits = 0;
-        const int found = run_target<FLAGS, KNN>(P, T, px, py, pz, i, hits, rdf_on);
+        uint32_t steps = 0;
+        const int found = run_target<FLAGS, KNN>(P, T, px, py, pz, i, steps, rdf_on);
         if (KNN) {
             if ((int64_t)rank < a.capacity) {
                 if (l == 0) a.target_id[rank] = (int64_t)i;
@@ -107,7 +107,7 @@ __device__ __forceinline__ void pair_items(const PairArgs& a, const GridPlan& P,
         }
         if (LDS_HIST) {
             // u32 LDS counters: flush before a further target could overflow them
-            since_flush += wave_sum(hits);
+            since_flush += steps * kWave;
             if (since_flush >= flush_at) {
                 flush_hist(T.hist_l, a.hist, a.n_bins);
                 since_flush = 0;
@@ -139,11 +139,10 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
     T.r_enum = a.r_enum;
     T.thr2 = a.thr2;
     T.inv_w = a.inv_w;
-    T.lo_b = a.delta_b;
-    T.hi_b = 1.0f - a.delta_b;
+    T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
     T.hist_g = a.hist;
     T.k = a.k;
     T.rk0 = P.rk0;
@@ -151,16 +150,16 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
     T.rknn2 = a.rknn2;
     T.kbuf = nullptr;
     if (LDS_HIST)
-        for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
+        for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
     if (KNN) {
-        size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u : 0;
+        size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u : 0;
         off = (off + 15) & ~size_t(15);
         T.kbuf = reinterpret_cast<uint64_t*>(smem + off) + (size_t)w * kKnnCap;
     }
     wave_sync();
 
-    uint32_t since_flush = 0;      // hits counted into hist_l since its last flush (wave total)
-    const uint32_t flush_at = P.nB >= 0x7FFFFFFFu ? 0u : 0xFFFFFFFFu - P.nB;
+    uint32_t since_flush = 0;      // counts in hist_l since its last flush, at most
+    const uint32_t flush_at = flush_limit(P.nB);
     // In a tile mode the tile pass (mode 3: the neighbour-major kernel) counted
     // the RDF and left the targets whose kNN it could not certify in a list;
     // tiles with too many candidates in another, which needs both.
@@ -168,7 +167,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
     if (KNN || P.tile_mode == 0)
         for (int list = P.tile_mode != 0; list <= (P.tile_mode == 1 ? 2 : P.tile_mode != 0); ++list)
             pair_items<FLAGS, KNN>(a, P, T, list, list != 1, since_flush, flush_at);
-    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins + 1), a.hist, a.n_bins);
 }
 
 // Mode 3 with the RDF one target per wavefront (tuning): the RDF of every
@@ -190,11 +189,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_tgt(PairArgs a) {
     T.r_enum = a.r_enum;
     T.thr2 = a.thr2;
     T.inv_w = a.inv_w;
-    T.lo_b = a.delta_b;
-    T.hi_b = 1.0f - a.delta_b;
+    T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
     T.hist_g = a.hist;
     T.k = 0;
     T.rk0 = 0.0f;
@@ -202,12 +200,12 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_tgt(PairArgs a) {
     T.rknn2 = INFINITY;
     T.kbuf = nullptr;
     if (LDS_HIST)
-        for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
+        for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
     uint32_t since_flush = 0;
-    const uint32_t flush_at = P.nB >= 0x7FFFFFFFu ? 0u : 0xFFFFFFFFu - P.nB;
+    const uint32_t flush_at = flush_limit(P.nB);
     pair_items<FLAGS, false>(a, P, T, 0, true, since_flush, flush_at);
-    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins + 1), a.hist, a.n_bins);
 }
 
 template __global__ void k_rdf_tgt<kRdfLds>(PairArgs);
@@ -249,19 +247,39 @@ __global__ __launch_bounds__(kBlock) void k_count_candidates(const GridPlan* pla
 }
 
 size_t tile_lds_bytes(bool rdf, int n_bins) {
-    size_t b = rdf ? (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u : 0;
+    size_t b = rdf ? (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u : 0;
     b = (b + 15) & ~size_t(15);
     return b + (size_t)kWavesPerBlock * kStage * sizeof(float4);
 }
 
-// (at most 128 VGPRs: four wavefronts per SIMD against three, for a few spills)
-template <int FLAGS, int KMAX>
-__global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
+// Before the neighbour-major RDF (k_nbr_prep).
+__device__ __forceinline__ void nbr_prep(const PairArgs& a, const GridPlan& P) {
+    if (P.nbr_sym) {
+        for (uint64_t j = blockIdx.x * kBlock + threadIdx.x; j < P.nB; j += gridDim.x * kBlock)
+            a.elig[j] = a.d_bnd == nullptr || a.d_bnd[__builtin_bit_cast(uint32_t, a.bpos[j].w)] >= a.d_srf;
+        return;
+    }
+    uint32_t cnt = 0;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < P.nT; q += gridDim.x * kBlock) {
+        if (!(isfinite(a.tx[q]) && isfinite(a.ty[q]) && isfinite(a.tz[q]))) continue;
+        if (a.nbr_species == APT_ANY || (int)a.lab[a.t_id[q]] == a.nbr_species) ++cnt;
+    }
+    // (one atomic per workgroup: they run one after the other)
+    __shared__ uint32_t s_cnt;
+    if (threadIdx.x == 0) s_cnt = 0;
+    __syncthreads();
+    cnt = wave_sum(cnt);
+    if (lane_id() == 0 && cnt) atomicAdd(&s_cnt, cnt);
+    __syncthreads();
+    // (u64 arithmetic modulo 2^64: the order of this and the kernel's adds
+    // does not matter)
+    if (threadIdx.x == 0 && s_cnt) atomicAdd((unsigned long long*)a.hist, 0ull - (unsigned long long)s_cnt);
+}
+// LANE: one target per lane (mode 2, and mode 3, whose RDF is counted by
+// another kernel, without RDF flags), else tiles through the stage.
+template <int FLAGS, int KMAX, bool LANE>
+__device__ __forceinline__ void pair_tile_body(const PairArgs& a, const GridPlan& P, uint8_t* smem) {
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
-    GridPlan P = *a.plan;
-    if (!P.tile_mode || (P.tile_mode == 3 && KMAX == 0)) return;
-    refine_radii(P, a.occ, a.k);
-    extern __shared__ __align__(16) uint8_t smem[];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int l = lane_id();
     PairTask T;
@@ -271,27 +289,38 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
     T.r_enum = a.r_enum;
     T.thr2 = a.thr2;
     T.inv_w = a.inv_w;
-    T.lo_b = a.delta_b;
-    T.hi_b = 1.0f - a.delta_b;
+    T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
     T.hist_g = a.hist;
     T.k = a.k;
     T.kbuf = nullptr;
-    size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u : 0;
+    size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u : 0;
     off = (off + 15) & ~size_t(15);
     float4* stage = reinterpret_cast<float4*>(smem + off) + (size_t)w * kStage;
     if (LDS_HIST)
-        for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
+        for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
     const float Rk = KMAX > 0 ? fminf(P.rk_tile, a.rknn) : 0.0f;
 
     // work queues over tiles (cell order), an eighth per XCD
     const uint32_t n_tiles = (P.nT + kWave - 1) / kWave;
     constexpr uint32_t kBatch = 4;
+    // u32 LDS counters: flushed before a further tile (at most 64 parts, each a
+    // stage of records against 64 lanes; run_lane: every record) could overflow
+    // them; run_tile scans any number of stages, and flushes between two
     uint32_t since_flush = 0;
-    const uint32_t flush_at = P.nB >= 0x7FFFFFFFu / kWave ? 0u : 0xFFFFFFFFu - P.nB * kWave;
+    const uint32_t flush_at = !LANE                               ? 0xFFFFFFFFu - (uint32_t)(kWave * kStage * kWave)
+                              : P.nB >= 0x7FFFFFFFu / kWave ? 0u : 0xFFFFFFFFu - P.nB * kWave;
+    auto counted = [&](uint32_t most) {
+        if (!LDS_HIST) return;
+        since_flush += most;
+        if (since_flush >= flush_at) {
+            flush_hist(T.hist_l, a.hist, a.n_bins);
+            since_flush = 0;
+        }
+    };
     int x = blockIdx.x % kXcd, empty = 0;
     uint32_t gb, ge;
     while (next_batch(a.work_q + kXcd * kWorkStride, n_tiles, 0, kBatch, x, empty, &gb, &ge)) {
@@ -308,23 +337,24 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
             py = a.ty[slot];
             pz = a.tz[slot];
         }
-        uint32_t hits = 0;
         // a tile that runs from one region of the order into the next is
         // taken a region at a time: its box, and with it the candidates of
         // every lane, would span both (a few such tiles, with thousands of
         // candidates from one side of the specimen to the other, ran on for a
         // third of the launch after all others)
-        const uint32_t region = P.tile_mode == 1 && isfinite(px + py + pz) ? target_region(P, px, py, pz) : 0u;
+        const uint32_t region = !LANE && isfinite(px + py + pz) ? target_region(P, px, py, pz) : 0u;
         uint64_t todo = __ballot(valid0);
         while (todo) {
         const bool valid = valid0 && region == readlane(region, __builtin_ctzll(todo));
         todo &= ~__ballot(valid);
         TopK<KMAX> top;
         bool unsure = false;
-        // mode 3: the kNN only (the one-per-wavefront pass counts the RDF)
-        if (P.tile_mode >= 2) run_lane<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, top, hits, P.tile_mode == 2);
-        else if constexpr (KMAX > 0) {
-            if (!run_tile_packed<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, top, hits, &unsure)) {
+        if constexpr (LANE) {
+            uint32_t hits = 0;
+            run_lane<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, top, hits);
+            if (LDS_HIST) since_flush += wave_sum(hits);
+        } else if constexpr (KMAX > 0) {
+            if (!run_tile_packed<FLAGS, KMAX>(P, T, valid, px, py, pz, i, Rk, a.k, stage, top, &unsure)) {
                 // too many candidates: RDF and kNN one target at a time (the
                 // list's other end)
                 const uint64_t m = __ballot(valid);
@@ -334,8 +364,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
                 if (valid) a.strag[P.nT - 1u - (base + (uint32_t)__popcll(m & lanemask_lt()))] = slot;
                 continue;
             }
+            since_flush += (uint32_t)(kStage * kWave);
         } else {
-            run_tile<FLAGS>(P, T, valid, px, py, pz, i, stage, hits);
+            run_tile<FLAGS>(P, T, valid, px, py, pz, i, stage, counted);
         }
         if (KMAX > 0) {
             // certified: k keys within Rk, or the radius already is r_knn_max
@@ -381,16 +412,32 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
             }
         }
         }
-        if (LDS_HIST) {
-            since_flush += wave_sum(hits);
-            if (since_flush >= flush_at) {
-                flush_hist(T.hist_l, a.hist, a.n_bins);
-                since_flush = 0;
-            }
-        }
+        counted(0u);
     }
     }
-    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins + 1), a.hist, a.n_bins);
+}
+
+// (at most 128 VGPRs: four wavefronts per SIMD against three.  The two are
+// kernels of their own: with both passes in one, their registers spilled, and
+// the tiles of 7.5e6 dense targets, k = 10, took 1.32 ms instead of 1.28)
+template <int FLAGS, int KMAX>
+__global__ __launch_bounds__(kBlock, 4) void k_pair_tile(PairArgs a) {
+    GridPlan P = *a.plan;
+    if (P.tile_mode != 1) return;
+    refine_radii(P, a.occ, a.k);
+    extern __shared__ __align__(16) uint8_t smem[];
+    pair_tile_body<FLAGS, KMAX, false>(a, P, smem);
+}
+
+template <int FLAGS, int KMAX>
+__global__ __launch_bounds__(kBlock, 4) void k_pair_lane(PairArgs a) {
+    GridPlan P = *a.plan;
+    if (P.tile_mode < 2) return;
+    if (P.rdf_nbr && a.hist && a.self_possible) nbr_prep(a, P);
+    refine_radii(P, a.occ, a.k);
+    extern __shared__ __align__(16) uint8_t smem[];
+    pair_tile_body<FLAGS, KMAX, true>(a, P, smem);
 }
 
 // ---------------------------------------------------- neighbour-major RDF --
@@ -455,8 +502,7 @@ __device__ __forceinline__ void rdf_nbr_body(const PairArgs& a, const GridPlan& 
     const uint32_t batch = per_wave < 1u ? 1u : per_wave > 16u ? 16u : per_wave;
     const float Re = a.r_enum + P.eps;
     const float R2 = Re * Re;
-    const float thr2 = a.thr2, inv_w = a.inv_w, lo_b = a.delta_b, hi_b = 1.0f - a.delta_b;
-    const float half_band = 0.5f - a.delta_b;   // |fract - 1/2| beyond it: within delta_b of an edge
+    const float thr2 = a.thr2, inv_w = a.inv_w, half_band = a.half_band;
     uint32_t since_flush = 0;
     const uint32_t flush_at = 0xFFFFFFFFu - (uint32_t)(4 * kWave * kNbrList);
 
@@ -476,17 +522,11 @@ __device__ __forceinline__ void rdf_nbr_body(const PairArgs& a, const GridPlan& 
         auto count = [&](float tx, float ty, float tz, float d2, uint32_t weight) {
             const float tt = __builtin_amdgcn_sqrtf(d2) * inv_w;
             int b = (int)tt;
-            if (LDS_HIST) {
-                // b == n_bins (beyond r_max) lands in the spare counter
-                if (__builtin_expect(fabsf(__builtin_amdgcn_fractf(tt) - 0.5f) > half_band, 0))
-                    b = exact_bin(exact_D2(tx, ty, tz, rec.x, rec.y, rec.z), a.E2, a.n_bins, a.inv_w64);
-                atomicAdd(&hist_l[b], weight);
-            } else {
-                const float fr = tt - (float)b;
-                if (__builtin_expect(fr < lo_b || fr > hi_b, 0))
-                    b = exact_bin(exact_D2(tx, ty, tz, rec.x, rec.y, rec.z), a.E2, a.n_bins, a.inv_w64);
-                if (b < a.n_bins && weight) atomicAdd((unsigned long long*)&a.hist[b], (unsigned long long)weight);
-            }
+            if (__builtin_expect(fabsf(__builtin_amdgcn_fractf(tt) - 0.5f) > half_band, 0))
+                b = exact_bin(exact_D2(tx, ty, tz, rec.x, rec.y, rec.z), a.E2, a.n_bins, a.inv_w64);
+            // (LDS: b == n_bins, beyond r_max, lands in the spare counter)
+            if (LDS_HIST) atomicAdd(&hist_l[b], weight);
+            else if (b < a.n_bins && weight) atomicAdd((unsigned long long*)&a.hist[b], (unsigned long long)weight);
         };
         auto counted = [&](uint32_t most) {   // counts added since the last call, at most
             since_flush += most;
@@ -651,31 +691,14 @@ template __global__ void k_rdf_nbr<kRdfGlobal>(PairArgs);
 
 __global__ __launch_bounds__(kBlock) void k_nbr_prep(PairArgs a) {
     const GridPlan P = *a.plan;
-    if (P.tile_mode != 3 || !P.rdf_nbr) return;
-    if (P.nbr_sym) {
-        for (uint64_t j = blockIdx.x * kBlock + threadIdx.x; j < P.nB; j += gridDim.x * kBlock)
-            a.elig[j] = a.d_bnd == nullptr || a.d_bnd[__builtin_bit_cast(uint32_t, a.bpos[j].w)] >= a.d_srf;
-        return;
-    }
-    uint32_t cnt = 0;
-    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < P.nT; q += gridDim.x * kBlock) {
-        if (!(isfinite(a.tx[q]) && isfinite(a.ty[q]) && isfinite(a.tz[q]))) continue;
-        if (a.nbr_species == APT_ANY || (int)a.lab[a.t_id[q]] == a.nbr_species) ++cnt;
-    }
-    // (one atomic per workgroup: they run one after the other)
-    __shared__ uint32_t s_cnt;
-    if (threadIdx.x == 0) s_cnt = 0;
-    __syncthreads();
-    cnt = wave_sum(cnt);
-    if (lane_id() == 0 && cnt) atomicAdd(&s_cnt, cnt);
-    __syncthreads();
-    // (u64 arithmetic modulo 2^64: the order of this and the kernel's adds
-    // does not matter)
-    if (threadIdx.x == 0 && s_cnt) atomicAdd((unsigned long long*)a.hist, 0ull - (unsigned long long)s_cnt);
+    if (P.tile_mode == 3 && P.rdf_nbr) nbr_prep(a, P);
 }
+
 template __global__ void k_rdf_nbr<kRdfGlobal | kCountEvals>(PairArgs);
 
-#define APT_TILE_INST(F, K) template __global__ void k_pair_tile<F, K>(PairArgs);
+#define APT_TILE_INST(F, K)                                   \
+    template __global__ void k_pair_tile<F, K>(PairArgs);     \
+    template __global__ void k_pair_lane<F, K>(PairArgs);
 APT_TILE_INST(kRdfLds, 0)
 APT_TILE_INST(kRdfLds | kSelf, 0)
 APT_TILE_INST(kRdfLds, 4)

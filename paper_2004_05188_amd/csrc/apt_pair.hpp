@@ -27,7 +27,7 @@ struct PairArgs {
     float r_enum;                // enumeration radius covering every counted pair
     float thr2;                  // FP32 squared-distance cut of the fast path
     float inv_w;                 // n_bins / r_max (FP32)
-    float delta_b;               // near-edge band, in bins
+    float half_band;             // a bin position whose fraction is further than this from 1/2 is too near an edge
     double inv_w64;
     const double* E2;            // [n_bins + 1]
     uint64_t* hist;              // [n_bins]
@@ -70,9 +70,13 @@ __global__ void k_pair(PairArgs a);
 size_t pair_lds_bytes(bool rdf, bool knn, int n_bins, bool hist_in_lds);
 
 // 64 targets per wavefront (apt_pair.hip); KMAX >= k kNN keys per lane, 0 for
-// RDF only.  Exits at once unless the plan chose tile mode.
+// RDF only.  Exits at once unless the plan chose mode 1.
 template <int FLAGS, int KMAX>
 __global__ void k_pair_tile(PairArgs a);
+// One target per lane: the kNN of mode 3 (no RDF flag; does k_nbr_prep's work
+// first), or with the RDF all of mode 2.  Exits in other modes.
+template <int FLAGS, int KMAX>
+__global__ void k_pair_lane(PairArgs a);
 size_t tile_lds_bytes(bool rdf, int n_bins);
 
 // Neighbour-major RDF (mode 3, dense neighbours): each wavefront takes 64

@@ -211,10 +211,10 @@ struct PairTask {
     const uint32_t* cell_start;  // [n_cells + 1] into bpos
     // RDF
     int n_bins;
-    float r_enum, thr2, inv_w, lo_b, hi_b;
+    float r_enum, thr2, inv_w, half_band;
     double inv_w64;
     const double* E2;
-    uint32_t* hist_l;            // per-wavefront LDS histogram (LDS variant)
+    uint32_t* hist_l;            // per-wavefront LDS histogram (LDS variant), n_bins + 1 counters
     uint64_t* hist_g;            // global histogram (global variant)
     // kNN
     int k;
@@ -222,12 +222,27 @@ struct PairTask {
     uint64_t* kbuf;              // per-wavefront LDS key buffer [kKnnCap]
 };
 
+// One pair's RDF count, at FP32 squared distance d2 < thr2: the FP32 bin, or
+// near an edge the FP64 one.  The LDS histogram has one more counter: a pair
+// just beyond r_max (bin n_bins) lands there, uncounted, instead of taking a
+// branch, and nothing is kept of how many were counted (callers bound it by the
+// candidates scanned).
+template <bool LDS_HIST>
+__device__ __forceinline__ void rdf_count(const PairTask& T, float px, float py, float pz, float4 c, float d2) {
+    const float t = __builtin_amdgcn_sqrtf(d2) * T.inv_w;
+    int b = (int)t;
+    if (__builtin_expect(fabsf(__builtin_amdgcn_fractf(t) - 0.5f) > T.half_band, 0))
+        b = exact_bin(exact_D2(px, py, pz, c.x, c.y, c.z), T.E2, T.n_bins, T.inv_w64);
+    if (LDS_HIST) atomicAdd(&T.hist_l[b], 1u);
+    else if (b < T.n_bins) atomicAdd((unsigned long long*)&T.hist_g[b], 1ull);
+}
+
 // RDF counts and kNN keys of one target.  Leaves the sorted keys in kbuf and
-// returns how many of the k nearest were found; adds this lane's RDF counts
-// to `hits`.
+// returns how many of the k nearest were found; adds the RDF's steps of 64
+// candidates to `steps`.
 template <int FLAGS, bool KNN>
 __device__ __forceinline__ int run_target(const GridPlan& P, const PairTask& T, float px, float py, float pz,
-                                          uint32_t i, uint32_t& hits, bool rdf_on = true) {
+                                          uint32_t i, uint32_t& steps, bool rdf_on = true) {
     constexpr bool RDF_T = (FLAGS & (kRdfLds | kRdfGlobal)) != 0;
     const bool RDF = RDF_T && rdf_on;
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
@@ -240,22 +255,11 @@ __device__ __forceinline__ int run_target(const GridPlan& P, const PairTask& T, 
     };
     auto cid = [](float4 c) { return __builtin_bit_cast(uint32_t, c.w); };
 
-    // ---- RDF of one candidate: FP32 bin, FP64 re-decision near an edge
     auto rdf_one = [&](bool valid, float4 c, float d2) {
         bool ok = valid && d2 < T.thr2;
         if (SELF) ok = ok && !(d2 == 0.0f && cid(c) == i);     // the target itself
-        const float t = __builtin_amdgcn_sqrtf(d2) * T.inv_w;
-        int b = (int)t;
-        const float fr = t - (float)b;
-        if (ok) {
-            if (__builtin_expect(fr < T.lo_b || fr > T.hi_b, 0))
-                b = exact_bin(exact_D2(px, py, pz, c.x, c.y, c.z), T.E2, T.n_bins, T.inv_w64);
-            if (b < T.n_bins) {
-                if (LDS_HIST) atomicAdd(&T.hist_l[b], 1u);
-                else atomicAdd((unsigned long long*)&T.hist_g[b], 1ull);
-                ++hits;
-            }
-        }
+        if (ok) rdf_count<LDS_HIST>(T, px, py, pz, c, d2);
+        ++steps;
     };
 
     // ---- kNN: keys of candidates in (rk2_prev, rk2] into the LDS buffer
@@ -363,10 +367,10 @@ struct TopK {
     uint64_t key[KMAX > 0 ? KMAX : 1];
 };
 
-// RDF only, with any number of records.
-template <int FLAGS>
+// RDF only, with any number of records; counted(bound) after each scan.
+template <int FLAGS, class C>
 __device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, bool valid, float px, float py, float pz,
-                                         uint32_t i, float4* stage, uint32_t& hits) {
+                                         uint32_t i, float4* stage, C&& counted) {
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
     constexpr bool SELF = (FLAGS & kSelf) != 0;
     const bool fin = valid && isfinite(px) && isfinite(py) && isfinite(pz);
@@ -380,20 +384,11 @@ __device__ __forceinline__ void run_tile(const GridPlan& P, const PairTask& T, b
             const float4 c = stage[j];
             const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;
             const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-            if (fin && (!SELF || __builtin_bit_cast(uint32_t, c.w) != i) && d2 < T.thr2) {
-                const float t = __builtin_amdgcn_sqrtf(d2) * T.inv_w;
-                int b = (int)t;
-                const float fr = t - (float)b;
-                if (__builtin_expect(fr < T.lo_b || fr > T.hi_b, 0))
-                    b = exact_bin(exact_D2(px, py, pz, c.x, c.y, c.z), T.E2, T.n_bins, T.inv_w64);
-                if (b < T.n_bins) {
-                    if (LDS_HIST) atomicAdd(&T.hist_l[b], 1u);
-                    else atomicAdd((unsigned long long*)&T.hist_g[b], 1ull);
-                    ++hits;
-                }
-            }
+            if (fin && (!SELF || __builtin_bit_cast(uint32_t, c.w) != i) && d2 < T.thr2)
+                rdf_count<LDS_HIST>(T, px, py, pz, c, d2);
         }
         wave_sync();
+        counted((uint32_t)m * kWave);
     };
     int m = 0;   // staged records
     const float Re = T.r_enum + P.eps, Re2 = Re * Re;
@@ -429,7 +424,7 @@ static_assert((1 << kSlotBits) == kStage, "a stage place per slot");
 template <int FLAGS, int KMAX>
 __device__ __forceinline__ bool run_tile_packed(const GridPlan& P, const PairTask& T, bool valid, float px, float py,
                                                 float pz, uint32_t i, float Rk, int k, float4* stage, TopK<KMAX>& top,
-                                                uint32_t& hits, bool* unsure) {
+                                                bool* unsure) {
     constexpr bool RDF = (FLAGS & (kRdfLds | kRdfGlobal)) != 0;
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
     constexpr bool SELF = (FLAGS & kSelf) != 0;
@@ -470,18 +465,7 @@ __device__ __forceinline__ bool run_tile_packed(const GridPlan& P, const PairTas
         const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;
         const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
         const bool me = fin && (!SELF || __builtin_bit_cast(uint32_t, c.w) != i);
-        if (RDF && me && d2 < T.thr2) {
-            const float t = __builtin_amdgcn_sqrtf(d2) * T.inv_w;
-            int b = (int)t;
-            const float fr = t - (float)b;
-            if (__builtin_expect(fr < T.lo_b || fr > T.hi_b, 0))
-                b = exact_bin(exact_D2(px, py, pz, c.x, c.y, c.z), T.E2, T.n_bins, T.inv_w64);
-            if (b < T.n_bins) {
-                if (LDS_HIST) atomicAdd(&T.hist_l[b], 1u);
-                else atomicAdd((unsigned long long*)&T.hist_g[b], 1ull);
-                ++hits;
-            }
-        }
+        if (RDF && me && d2 < T.thr2) rdf_count<LDS_HIST>(T, px, py, pz, c, d2);
         const float x = me && d2 <= rk2 ? u2f((f2u(d2) & ~kSlot) | (uint32_t)j) : none;
         if (__any(x < kept[S - 1])) {
 #pragma unroll
@@ -531,19 +515,18 @@ __device__ __forceinline__ bool run_tile_packed(const GridPlan& P, const PairTas
 // target (rows trimmed to the x-range the sphere reaches, as in
 // enumerate_box) and reads the records one by one, kLaneU of them in flight;
 // no staging, and no lane waits on a shared candidate list.  Same results as
-// run_tile (same candidate set, order-free updates).  With rdf_on false only
+// run_tile (same candidate set, order-free updates).  Without an RDF only
 // the kNN keys within Rk are taken (a small radius when the neighbours are
-// dense: a few dozen records per lane).  Eight records in flight per lane
+// dense: a few dozen records per lane).  Adds this lane's RDF counts to `hits`.
+// Eight records in flight per lane
 // (2e9-ion needle, 1.0 nm cells: 23.4 ms with four, 22.4 with eight, 34
 // with two; sixteen spill).
 constexpr int kLaneU = 8;
 
 template <int FLAGS, int KMAX>
 __device__ __forceinline__ void run_lane(const GridPlan& P, const PairTask& T, bool valid, float px, float py,
-                                         float pz, uint32_t i, float Rk, TopK<KMAX>& top, uint32_t& hits,
-                                         bool rdf_on = true) {
-    constexpr bool RDF_T = (FLAGS & (kRdfLds | kRdfGlobal)) != 0;
-    const bool RDF = RDF_T && rdf_on;
+                                         float pz, uint32_t i, float Rk, TopK<KMAX>& top, uint32_t& hits) {
+    constexpr bool RDF = (FLAGS & (kRdfLds | kRdfGlobal)) != 0;
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
     constexpr bool SELF = (FLAGS & kSelf) != 0;
 #pragma unroll
@@ -577,6 +560,9 @@ __device__ __forceinline__ void run_lane(const GridPlan& P, const PairTask& T, b
         float4 c[kLaneU];
 #pragma unroll
         for (int u = 0; u < kLaneU; ++u) c[u] = T.bpos[j + (uint32_t)u < j1 ? j + (uint32_t)u : j];
+        // (all of them issued before the first is waited for: with the last two
+        // after it the 4e8-ion needle's Sc targets took 5.1 ms, now 4.4)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kLaneU; ++u) {
             if (j + (uint32_t)u >= j1) break;
@@ -585,28 +571,22 @@ __device__ __forceinline__ void run_lane(const GridPlan& P, const PairTask& T, b
             const uint32_t cj = __builtin_bit_cast(uint32_t, c[u].w);
             const bool me = !SELF || cj != i;
             if (RDF && me && d2 < T.thr2) {
-                const float t = __builtin_amdgcn_sqrtf(d2) * T.inv_w;
-                int b = (int)t;
-                const float fr = t - (float)b;
-                if (__builtin_expect(fr < T.lo_b || fr > T.hi_b, 0))
-                    b = exact_bin(exact_D2(px, py, pz, c[u].x, c[u].y, c[u].z), T.E2, T.n_bins, T.inv_w64);
-                if (b < T.n_bins) {
-                    if (LDS_HIST) atomicAdd(&T.hist_l[b], 1u);
-                    else atomicAdd((unsigned long long*)&T.hist_g[b], 1ull);
-                    ++hits;
-                }
+                rdf_count<LDS_HIST>(T, px, py, pz, c[u], d2);
+                ++hits;
             }
             if (KMAX > 0) {
                 const uint64_t key = ((uint64_t)__builtin_bit_cast(uint32_t, d2) << 32) | (uint64_t)cj;
                 if (me && d2 <= rk2 && key < top.key[KMAX - 1]) {
-                    uint64_t x = key;
+                    // (from the last place down: one comparison per place, none
+                    // waiting for another)
+                    bool here = true;   // key < top.key[q]
 #pragma unroll
-                    for (int q = 0; q < KMAX; ++q) {
-                        const uint64_t lo = x < top.key[q] ? x : top.key[q];
-                        const uint64_t hi = x < top.key[q] ? top.key[q] : x;
-                        top.key[q] = lo;
-                        x = hi;
+                    for (int q = KMAX - 1; q > 0; --q) {
+                        const bool before = key < top.key[q - 1];
+                        top.key[q] = before ? top.key[q - 1] : here ? key : top.key[q];
+                        here = before;
                     }
+                    top.key[0] = here ? key : top.key[0];
                 }
             }
         }
@@ -627,10 +607,10 @@ __device__ __forceinline__ void run_lane(const GridPlan& P, const PairTask& T, b
 // k-th key (FP32 d2 bits << 32 | index), or ~0 when it is not settled here:
 // fewer than k neighbours within Rk, or an index needed at a distance that
 // several of the k nearest share (the caller finishes those targets exactly).
-template <int FLAGS, int KMAX>
+template <int FLAGS, int KMAX, class C>
 __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTask& T, bool valid, float px,
                                                  float py, float pz, uint32_t i, float Rk, int k, float4* stage,
-                                                 uint32_t& hits, int kb_nbins, double kb_inv_w64) {
+                                                 C&& counted, int kb_nbins, double kb_inv_w64) {
     constexpr bool RDF = (FLAGS & (kRdfLds | kRdfGlobal)) != 0;
     constexpr bool LDS_HIST = (FLAGS & kRdfLds) != 0;
     constexpr bool SELF = (FLAGS & kSelf) != 0;
@@ -657,18 +637,7 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
             const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
             const uint32_t cj = __builtin_bit_cast(uint32_t, c.w);
             const bool me = fin && (!SELF || cj != i);
-            if (RDF && me && d2 < T.thr2) {
-                const float t = __builtin_amdgcn_sqrtf(d2) * T.inv_w;
-                int b = (int)t;
-                const float fr = t - (float)b;
-                if (__builtin_expect(fr < T.lo_b || fr > T.hi_b, 0))
-                    b = exact_bin(exact_D2(px, py, pz, c.x, c.y, c.z), T.E2, T.n_bins, T.inv_w64);
-                if (b < T.n_bins) {
-                    if (LDS_HIST) atomicAdd(&T.hist_l[b], 1u);
-                    else atomicAdd((unsigned long long*)&T.hist_g[b], 1ull);
-                    ++hits;
-                }
-            }
+            if (RDF && me && d2 < T.thr2) rdf_count<LDS_HIST>(T, px, py, pz, c, d2);
             const bool in = me && d2 <= rk2;
             if (__ballot(in && d2 < top[KMAX - 1])) {
                 const float x = in ? d2 : INFINITY;
@@ -678,6 +647,7 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
             }
         }
         wave_sync();
+        if (RDF) counted((uint32_t)m * kWave);
     };
     int m = 0;              // records in the stage
     bool once = true;       // it holds all of the tile's
@@ -753,6 +723,15 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
     }
     settled = settled && jk != 0xFFFFFFFFu;
     return settled ? (((uint64_t)__builtin_bit_cast(uint32_t, tau) << 32) | (uint64_t)jk) : ~0ull;
+}
+
+// Steps of 64 candidates that one target's RDF can take, in counts, taken off
+// 2^32: the bound at which a wavefront's u32 LDS counters are flushed before
+// another target.  (A step that ends a group of rows may be less than full, one
+// in 64 rows: at most twice nB and 64 more.  Clouds too large for that flush
+// after every target, whose counts are at most nB.)
+__device__ __forceinline__ uint32_t flush_limit(uint64_t nB) {
+    return nB >= 0x3FFFFFFFull ? 0u : 0xFFFFFFFFu - (uint32_t)(2 * nB + kWave);
 }
 
 // Flush a per-wavefront u32 LDS histogram into a global u64 histogram.
