@@ -550,6 +550,16 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
     return hip_check("binning launch");
 }
 
+// The FP32 squared distance below which a pair may count: r_max^2 with a
+// margin above the FP32 distance's error (2e-7 of it).  For LDS histograms
+// (`near_edge`) no more than four fifths of the band around the last edge
+// (delta_b bins, at least 4e-6 n_bins), so that the FP32 position of every pair
+// beyond r_max lies in the band (it errs by 3e-7 n_bins) and is decided in FP64.
+static float rdf_thr2(double r_max, int n_bins, double delta_b, bool near_edge) {
+    const double m = 1.0 + (near_edge ? fmin(2e-5, 0.8 * delta_b / n_bins) : 2e-5);
+    return (float)((r_max * m) * (r_max * m));
+}
+
 // The whole plain path.  rdf_hist / knn outputs may be absent.
 // cand (diagnostic, device u64): bin as the call would, then count the RDF
 // stencil's candidates into *cand instead of running the pair kernels.
@@ -676,7 +686,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
         pa.half_band = 0.5f - (float)delta_b;
         pa.inv_w = (float)(n_bins / rmax);
         pa.inv_w64 = n_bins / rmax;
-        pa.thr2 = (float)((rmax * (1.0 + 2e-5)) * (rmax * (1.0 + 2e-5)));
+        pa.thr2 = rdf_thr2(rmax, n_bins, delta_b, rdf_lds || tile_fits);
         pa.r_enum = (float)(rmax * (1.0 + 4e-5));
         pa.E2 = w.E2;
         pa.hist = rdf_hist;
@@ -984,7 +994,7 @@ static apt_status run_batched(const apt_cloud* cl, const apt_query* pairs, int32
         ba.occ = reinterpret_cast<const uint32_t*>(w.work + 4);
         ba.n_bins = rb.n_bins;
         ba.r_enum = (float)((double)rb.r_max * (1.0 + 4e-5));
-        ba.thr2 = (float)(((double)rb.r_max * (1.0 + 2e-5)) * ((double)rb.r_max * (1.0 + 2e-5)));
+        ba.thr2 = rdf_thr2(rb.r_max, rb.n_bins, delta_b, true);
         ba.inv_w = (float)(rb.n_bins / (double)rb.r_max);
         ba.half_band = 0.5f - (float)delta_b;
         ba.inv_w64 = rb.n_bins / (double)rb.r_max;

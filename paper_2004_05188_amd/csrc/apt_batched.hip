@@ -17,7 +17,7 @@
 namespace apt {
 
 size_t batched_lds_bytes(int n_bins) {
-    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u;
+    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u;
     b = (b + 15) & ~size_t(15);
     return b + (size_t)kWavesPerBlock * kKnnCap * 8u;
 }
@@ -25,7 +25,7 @@ size_t batched_lds_bytes(int n_bins) {
 // tiles: histogram + staging buffer (which later holds a straggler's kNN keys)
 size_t batched_tile_lds_bytes(int n_bins) {
     static_assert(kStage * sizeof(float4) >= kKnnCap * sizeof(uint64_t), "key buffer inside the stage");
-    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u;
+    size_t b = (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u;
     b = (b + 15) & ~size_t(15);
     return b + (size_t)kWavesPerBlock * kStage * sizeof(float4);
 }
@@ -289,13 +289,13 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
     T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
     T.k = a.k;
     T.rknn = INFINITY;
     T.rknn2 = INFINITY;
-    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u + 15) & ~size_t(15);
+    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u + 15) & ~size_t(15);
     T.kbuf = reinterpret_cast<uint64_t*>(smem + off) + (size_t)w * kKnnCap;
-    for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
+    for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
 
     const int RP = a.R * a.n_pairs;
@@ -389,14 +389,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_pair_batched_tile(BatchPairArgs a
     T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
     T.k = a.k;
     T.rknn = INFINITY;
     T.rknn2 = INFINITY;
-    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u + 15) & ~size_t(15);
+    size_t off = ((size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u + 15) & ~size_t(15);
     float4* stage = reinterpret_cast<float4*>(smem + off) + (size_t)w * kStage;
     T.kbuf = reinterpret_cast<uint64_t*>(stage);      // used only after the tile pass
-    for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
+    for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
 
     int cur = -1;

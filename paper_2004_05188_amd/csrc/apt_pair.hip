@@ -27,7 +27,7 @@ namespace apt {
 
 size_t pair_lds_bytes(bool rdf, bool knn, int n_bins, bool hist_in_lds) {
     size_t b = 0;
-    if (rdf && hist_in_lds) b += (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u;
+    if (rdf && hist_in_lds) b += (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u;
     b = (b + 15) & ~size_t(15);
     if (knn) b += (size_t)kWavesPerBlock * kKnnCap * 8u;
     return b;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
     T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
     T.hist_g = a.hist;
     T.k = a.k;
     T.rk0 = P.rk0;
@@ -150,9 +150,9 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
     T.rknn2 = a.rknn2;
     T.kbuf = nullptr;
     if (LDS_HIST)
-        for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
+        for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
     if (KNN) {
-        size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u : 0;
+        size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u : 0;
         off = (off + 15) & ~size_t(15);
         T.kbuf = reinterpret_cast<uint64_t*>(smem + off) + (size_t)w * kKnnCap;
     }
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair(PairArgs a) {
     if (KNN || P.tile_mode == 0)
         for (int list = P.tile_mode != 0; list <= (P.tile_mode == 1 ? 2 : P.tile_mode != 0); ++list)
             pair_items<FLAGS, KNN>(a, P, T, list, list != 1, since_flush, flush_at);
-    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins + 1), a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
 // Mode 3 with the RDF one target per wavefront (tuning): the RDF of every
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_tgt(PairArgs a) {
     T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
     T.hist_g = a.hist;
     T.k = 0;
     T.rk0 = 0.0f;
@@ -200,12 +200,12 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_tgt(PairArgs a) {
     T.rknn2 = INFINITY;
     T.kbuf = nullptr;
     if (LDS_HIST)
-        for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
+        for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
     uint32_t since_flush = 0;
     const uint32_t flush_at = flush_limit(P.nB);
     pair_items<FLAGS, false>(a, P, T, 0, true, since_flush, flush_at);
-    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins + 1), a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
 template __global__ void k_rdf_tgt<kRdfLds>(PairArgs);
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kBlock) void k_count_candidates(const GridPlan* pla
 }
 
 size_t tile_lds_bytes(bool rdf, int n_bins) {
-    size_t b = rdf ? (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins + 1) * 4u : 0;
+    size_t b = rdf ? (size_t)kWavesPerBlock * (size_t)hist_stride(n_bins) * 4u : 0;
     b = (b + 15) & ~size_t(15);
     return b + (size_t)kWavesPerBlock * kStage * sizeof(float4);
 }
@@ -292,15 +292,15 @@ __device__ __forceinline__ void pair_tile_body(const PairArgs& a, const GridPlan
     T.half_band = a.half_band;
     T.inv_w64 = a.inv_w64;
     T.E2 = a.E2;
-    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins + 1);
+    T.hist_l = reinterpret_cast<uint32_t*>(smem) + (size_t)w * hist_stride(a.n_bins);
     T.hist_g = a.hist;
     T.k = a.k;
     T.kbuf = nullptr;
-    size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins + 1) * 4u : 0;
+    size_t off = LDS_HIST ? (size_t)kWavesPerBlock * hist_stride(a.n_bins) * 4u : 0;
     off = (off + 15) & ~size_t(15);
     float4* stage = reinterpret_cast<float4*>(smem + off) + (size_t)w * kStage;
     if (LDS_HIST)
-        for (int b = l; b <= a.n_bins; b += kWave) T.hist_l[b] = 0;
+        for (int b = l; b < a.n_bins; b += kWave) T.hist_l[b] = 0;
     wave_sync();
     const float Rk = KMAX > 0 ? fminf(P.rk_tile, a.rknn) : 0.0f;
 
@@ -415,7 +415,7 @@ __device__ __forceinline__ void pair_tile_body(const PairArgs& a, const GridPlan
         counted(0u);
     }
     }
-    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins + 1), a.hist, a.n_bins);
+    if (LDS_HIST) flush_hist_block(reinterpret_cast<uint32_t*>(smem), hist_stride(a.n_bins), a.hist, a.n_bins);
 }
 
 // (at most 128 VGPRs: four wavefronts per SIMD against three.  The two are

@@ -179,3 +179,40 @@ def test_unordered_pairs_of_one_species(n, A, d_srf, n_bins, k):
     finally:
         aptstat.set_tuning()
     assert np.array_equal(out[0], out[1]) and out[0].sum() > 0
+
+
+@pytest.mark.parametrize("n_bins", [1, 200, 2047, 2048, 3072, 4096, 4097])
+@pytest.mark.parametrize("r_max", [1.0, float(np.nextafter(np.float32(1.0), np.float32(2.0))), 0.75])
+def test_pairs_about_the_last_edge(n_bins, r_max):
+    """Pairs at r_max, a rounding step either side of it and up to 1e-4 beyond, whose FP32 bin may be the one after
+    the last: every pair kernel against the FP64 distances (whole numbers: no tolerance).  The sizes are the largest
+    histograms of each kernel's LDS, and the next."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    print(f"case last edge n_bins={n_bins} r_max={r_max}", flush=True)
+    g = np.mgrid[0:7, 0:7, 0:7].reshape(3, -1).T * 0.25
+    rng = np.random.default_rng(n_bins)
+    far = np.array([20.0, 0.0, 0.0]) + np.arange(40)[:, None] * np.array([0.0, 8.0, 0.0])
+    step = r_max + np.concatenate([np.arange(-10, 10) * 2.0 ** -24, rng.uniform(-1e-4, 1e-4, 20)])
+    xyz = np.concatenate([g, far, far + step[:, None] * np.array([0.0, 0.0, 1.0])]).astype(np.float32)
+    d = np.sqrt(((xyz[:, None].astype(np.float64) - xyz[None].astype(np.float64)) ** 2).sum(-1))
+    d = d[~np.eye(len(xyz), dtype=bool)]
+    r = float(np.float32(r_max))
+    edges = np.arange(n_bins + 1) * r / n_bins
+    b = np.searchsorted(edges, d[d < r], side="right") - 1
+    want = np.bincount(np.minimum(b, n_bins - 1), minlength=n_bins)
+
+    cloud = aptstat.Cloud(torch.from_numpy(xyz).cuda(), torch.zeros(len(xyz), dtype=torch.uint8, device="cuda"),
+                          torch.ones(len(xyz), device="cuda"))
+    ws = aptstat.Workspace()
+    try:
+        for policy in (0, 1, 2, 3, 4):
+            aptstat.set_tuning(tile_policy=policy)
+            got = aptstat.rdf(cloud, ANY, ANY, 0.0, r_max, n_bins, ws=ws).cpu().numpy()
+            assert np.array_equal(got, want), policy
+            got = aptstat.knn_rdf(cloud, ANY, ANY, 0.0, 4, r_max=r_max, n_bins=n_bins, ws=ws).rdf_hist.cpu().numpy()
+            assert np.array_equal(got, want), policy
+    finally:
+        aptstat.set_tuning()
