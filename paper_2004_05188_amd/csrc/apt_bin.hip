@@ -206,19 +206,24 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
         // search reach, so that they share most of their candidates, and when
         // those candidates are few: every lane evaluates all of them, while
         // one target per wavefront spends a fixed ~0.6 ns and a 64-candidate
-        // step per 64.  Box of 1e6 targets at 30 ions/nm^3, r_max 2 nm, tiles
-        // against one target per wavefront (against neighbour-major) in ms:
-        // RDF with 10 neighbours within r_max (44 candidates) 0.50 / 0.69, 30
-        // (133) 0.82 / 0.79, 100 (322) 4.02 / 1.17, 700 26.8 / 3.43 (1.61);
-        // with k = 10 (137) 0.84 / 1.29, (167) 1.31 / 1.70, (322) 5.1 / 2.0,
-        // 33.5 / 4.1 (2.6).  With a kNN also only for 2^18 targets or more,
-        // below which its tiles leave SIMDs empty (2e5 targets: 0.45 / 0.39)
+        // step per 64; and a kNN tile's have to fit the stage (512).  Boxes of
+        // 30 ions/nm^3, tiles / one target per wavefront (/ neighbour-major)
+        // in ms.  RDF, 3e4 targets: 30 candidates 0.090 / 0.093, 60 0.107 /
+        // 0.093; 1e5: 89 0.140 / 0.148, 105 0.153 / 0.131; 3e5: 177 0.217 /
+        // 0.280, 226 0.280 / 0.264; 1e6: 443 0.46 / 1.06 / 0.97, 665 0.60 /
+        // 1.23 / 1.11, 752 0.82 / 1.12 / 0.77.  k = 10, 1e5 targets: 160 0.21
+        // / 0.25, 216 0.25 / 0.20; 3e5: 443 0.45 / 0.65, 665 0.77 / 0.70; 1e6:
+        // 443 0.71 / 2.01 / 1.55, 665 1.87 / 2.15 / 1.72; k = 3 and 16 alike
         const double R = fmax((double)pp.r_enum, 1.6 / 1.15 * rk_raw);
         const double v64 = 64.0 * vol / (double)(totT > 0 ? totT : 1);
         const double side = cbrt(v64) + 2.0 * R;
         const double cand = rho * side * side * side;
+        const double most = pp.k > 0 ? (totT >= (1u << 18) ? 450.0 : 200.0)
+                            : totT >= (1u << 19) ? 600.0
+                            : totT >= (1u << 18) ? 180.0
+                            : totT >= (1u << 16) ? 100.0 : 45.0;
         P.tile_mode = (!pp.no_tiles && pp.k <= 16 && totT >= totB && totT >= (pp.k > 0 ? kTileMinKnn : kTileMinRdf) &&
-                       v64 <= R * R * R && cand <= (pp.k > 0 ? 200.0 : 100.0)) ? 1 : 0;
+                       v64 <= R * R * R && cand <= most) ? 1 : 0;
         // neighbours so dense that 64 of them span well under r_max: the RDF
         // runs neighbour-major (64 records per wavefront against every target
         // within reach), and the kNN, whose radius is then well below r_max,
