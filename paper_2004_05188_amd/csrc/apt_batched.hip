@@ -280,7 +280,7 @@ constexpr uint32_t kTileBatch = 8;    // tiles per batch, at most
 // wavefront gets some (720 tiles of one replicate of 47 000 ions, eight at a
 // time, kept 90 wavefronts busy: the call 1.51 ms, now 0.54).
 __device__ __forceinline__ uint32_t batch_of(uint64_t total, uint32_t most) {
-    const uint64_t per = total / ((uint64_t)gridDim.x * kWavesPerBlock * 2u);
+    const uint64_t per = total / ((uint64_t)gridDim.x * kWavesPerBlock * 8u);
     return per < 1u ? 1u : per < most ? (uint32_t)per : most;
 }
 
