@@ -208,20 +208,20 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
         // one target per wavefront spends a fixed ~0.6 ns and a 64-candidate
         // step per 64; and a kNN tile's have to fit the stage (512).  Boxes of
         // 30 ions/nm^3, tiles / one target per wavefront (/ neighbour-major)
-        // in ms.  RDF, 3e4 targets: 30 candidates 0.090 / 0.093, 60 0.107 /
-        // 0.093; 1e5: 89 0.140 / 0.148, 105 0.153 / 0.131; 3e5: 177 0.217 /
-        // 0.280, 226 0.280 / 0.264; 1e6: 443 0.46 / 1.06 / 0.97, 665 0.60 /
-        // 1.23 / 1.11, 752 0.82 / 1.12 / 0.77.  k = 10, 1e5 targets: 160 0.21
-        // / 0.25, 216 0.25 / 0.20; 3e5: 443 0.45 / 0.65, 665 0.77 / 0.70; 1e6:
-        // 443 0.71 / 2.01 / 1.55, 665 1.87 / 2.15 / 1.72; k = 3 and 16 alike
+        // in ms.  RDF, 3e4 targets: 177 candidates 0.086 / 0.093, 226 0.105 /
+        // 0.097; 1e5: 310 0.122 / 0.143, 376 0.157 / 0.143; 3e5: 665 0.27 /
+        // 0.42 / 0.49, 752 0.36 / 0.38 / 0.36; 1e6: 665 0.56 / 1.23 / 1.12.
+        // k = 10, 3e4 targets: 160 0.106 / 0.119, 239 0.126 / 0.124; 1e5: 271
+        // 0.18 / 0.23, 376 0.23 / 0.24 (k = 16, 434: 0.26 / 0.25); 3e5: 443
+        // 0.31 / 0.66 / 0.67; 1e6: 443 0.71 / 2.01 / 1.55, 665 1.74 / 2.15 /
+        // 1.67; k = 3 and 16 alike
         const double R = fmax((double)pp.r_enum, 1.6 / 1.15 * rk_raw);
         const double v64 = 64.0 * vol / (double)(totT > 0 ? totT : 1);
         const double side = cbrt(v64) + 2.0 * R;
         const double cand = rho * side * side * side;
-        const double most = pp.k > 0 ? (totT >= (1u << 18) ? 450.0 : 200.0)
-                            : totT >= (1u << 19) ? 600.0
-                            : totT >= (1u << 18) ? 180.0
-                            : totT >= (1u << 16) ? 100.0 : 45.0;
+        const double most = totT >= (1u << 18) ? (pp.k > 0 ? 450.0 : 600.0)
+                            : totT >= (1u << 16) ? 300.0
+                            : totT >= (1u << 15) ? 180.0 : 45.0;
         P.tile_mode = (!pp.no_tiles && pp.k <= 16 && totT >= totB && totT >= (pp.k > 0 ? kTileMinKnn : kTileMinRdf) &&
                        v64 <= R * R * R && cand <= most) ? 1 : 0;
         // neighbours so dense that 64 of them span well under r_max: the RDF

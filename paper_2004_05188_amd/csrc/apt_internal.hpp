@@ -76,7 +76,7 @@ struct PlanParams {
 
 // Fewest targets for the automatic choice of tile mode 1 and of mode 3,
 // without and with a kNN (k_plan has the measurements).
-constexpr uint32_t kTileMinRdf = 4096, kTileMinKnn = 1u << 17;
+constexpr uint32_t kTileMinRdf = 4096, kTileMinKnn = 1u << 15;
 constexpr uint32_t kNbrMinRdf = 1u << 17, kNbrMinKnn = 1u << 18;
 
 // ---------------------------------------------------------------- waves --
