@@ -722,7 +722,7 @@ static apt_status run_plain(const apt_cloud* cl, apt_query q, const apt_bins* rb
     // it prepares), or with the RDF of mode 2, which only the tuning chooses
     const bool lane_rdf = do_rdf && pp.tile_policy == 3;
     if (pp.tile_policy != 1 && (lane_rdf || (do_knn && !pp.no_nbr && pp.tile_policy != 2))) {
-        TraceSpan span("lane", st);
+        TraceSpan span("tile", st);
         const bool self = pa.self_possible != 0;
         const size_t tl = tile_lds_bytes(lane_rdf, n_bins);
         auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(resident_grid(kern, tl)), dim3(kBlock), tl, st, pa); };
