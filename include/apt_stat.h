@@ -347,10 +347,11 @@ apt_status apt_count_targets(const apt_cloud* cloud, apt_query q, int64_t* n_tar
  * within the first kNN radius when k > 0 and that is larger, each row
  * trimmed to the x-range the sphere reaches); for the neighbour-major kernel
  * (dense neighbours), the records of each 64-record run times the targets
- * staged for it.  Divided by the in-range pair
- * count it gives the culling ratio of the grid (paper, Supplementary,
- * "Effectiveness of the spatial splitting").  Errors as
- * apt_knn_rdf; k < 0 or candidates NULL return APT_E_ARG.  Workspace as
+ * staged for it; where one species meets itself, a pair is counted for each
+ * of its ends that is a target, though the RDF then evaluates both at once.
+ * Divided by the in-range pair count it gives the culling ratio of the grid
+ * (paper, Supplementary, "Effectiveness of the spatial splitting").  Errors
+ * as apt_knn_rdf; k < 0 or candidates NULL return APT_E_ARG.  Workspace as
  * APT_OP_KNN_RDF. */
 apt_status apt_count_candidates(const apt_cloud* cloud, apt_query q, apt_bins bins, int32_t k,
                                 uint64_t* candidates, int32_t* status, void* ws, size_t ws_bytes, void* stream);

@@ -474,6 +474,7 @@ size_t nbr_lds_bytes(int n_bins, bool hist_in_lds) {
 template <int FLAGS, bool SYM>
 __device__ __forceinline__ void rdf_nbr_body(const PairArgs& a, const GridPlan& P, uint8_t* smem) {
     constexpr bool COUNT = (FLAGS & kCountEvals) != 0;
+    static_assert(!(COUNT && SYM), "the diagnostic gives no cell_start and no elig");
     constexpr bool LDS_HIST = !COUNT && (FLAGS & kRdfLds) != 0;
     unsigned long long evals = 0;   // COUNT: pair evaluations (records x staged targets)
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -541,8 +542,7 @@ __device__ __forceinline__ void rdf_nbr_body(const PairArgs& a, const GridPlan& 
         };
         if (SYM && part == 0u) {
             // the pairs within the chunk: lane t's record against the lanes before it
-            if (COUNT) evals += (unsigned long long)(kWave * (kWave - 1));
-            else for (int t = 1; t < kWave; ++t) {
+            for (int t = 1; t < kWave; ++t) {
                 const float tx = readlane(rec.x, t), ty = readlane(rec.y, t), tz = readlane(rec.z, t);
                 const uint32_t both = mine + readlane(mine, t);
                 const float dx = rec.x - tx, dy = rec.y - ty, dz = rec.z - tz;
@@ -686,8 +686,15 @@ __global__ __launch_bounds__(kBlock, 8) void k_rdf_nbr(PairArgs a) {
     extern __shared__ __align__(16) uint8_t smem[];
     const GridPlan P = *a.plan;
     if (P.tile_mode != 3 || !P.rdf_nbr) return;
-    if (P.nbr_sym) rdf_nbr_body<FLAGS, true>(a, P, smem);
-    else rdf_nbr_body<FLAGS, false>(a, P, smem);
+    // (the diagnostic counts ordered evaluations, and has neither the records'
+    // offsets nor their flags: the unordered form is no part of its instance)
+    if constexpr ((FLAGS & kCountEvals) == 0) {
+        if (P.nbr_sym) {
+            rdf_nbr_body<FLAGS, true>(a, P, smem);
+            return;
+        }
+    }
+    rdf_nbr_body<FLAGS, false>(a, P, smem);
 }
 
 template __global__ void k_rdf_nbr<kRdfLds>(PairArgs);

@@ -216,3 +216,31 @@ def test_pairs_about_the_last_edge(n_bins, r_max):
             assert np.array_equal(got, want), policy
     finally:
         aptstat.set_tuning()
+
+
+@pytest.mark.parametrize("n,policy,d_srf,r_max,k", [
+    ((1 << 17) + 5, 0, 0.0, 2.0, 0), ((1 << 18) + 70, 0, 0.0, 2.0, 10), ((1 << 18) + 70, 0, 0.3, 2.0, 0),
+    (5_000, 4, 0.0, 1.0, 0), (63, 4, 0.0, 1.0, 0),
+])
+def test_candidates_of_one_species_against_itself(n, policy, d_srf, r_max, k):
+    """The diagnostic count where the RDF takes unordered pairs (every ion, or the only species, against itself): the
+    evaluations of ordered pairs, so the same as for that species against every ion, at least the pairs that the RDF
+    counts and at most targets times neighbours."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    print(f"case candidates of one species n={n} policy={policy} d_srf={d_srf} k={k}", flush=True)
+    xyz, _, _ = _box(torch, n, 0.5, n)
+    d = torch.rand(n, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    cloud = aptstat.Cloud(xyz, torch.ones(n, dtype=torch.uint8, device="cuda"), d)
+    ws = aptstat.Workspace()
+    aptstat.set_tuning(tile_policy=policy)
+    try:
+        got = [int(aptstat.count_candidates(cloud, A, B, d_srf, r_max, 200, k=k, ws=ws).item())
+               for A, B in ((ANY, ANY), (1, 1), (1, ANY), (ANY, ANY))]
+        pairs = int(aptstat.rdf(cloud, ANY, ANY, d_srf, r_max, 200, ws=ws).sum())
+    finally:
+        aptstat.set_tuning()
+    assert len(set(got)) == 1, got
+    assert 0 < pairs <= got[0] <= int((d >= d_srf).sum()) * n
