@@ -466,7 +466,7 @@ __device__ __forceinline__ float axis_gap(const TriPlan& T, int c, float p0, flo
 // k), k a slot of the sorted arrays, is called by all 64 lanes per step.
 // (Pieces outside the grid are registered in its outermost cells, nearer to
 // the box than they are: the gaps stay lower bounds.)  Returns whether the
-// rows were the whole grid.
+// box grown by S covers the grid (cells at its corners may still be beyond S).
 template <class F>
 __device__ __forceinline__ bool edge_rows(const TriPlan& T, const uint32_t* __restrict__ tstart, float x0, float y0,
                                           float z0, float x1, float y1, float z1, float S, F&& f) {
@@ -578,7 +578,7 @@ __global__ __launch_bounds__(kWave, 4) void k_edge_dist(EdgeArgs a) {
                 near2 = INFINITY;
             };
             // the centroid nearest to the box's centre, of the rows within R
-            // of the box; true if these were the whole grid
+            // of the box; true if the box grown by R covers the grid
             auto nearest = [&](float R) {
                 const bool whole = edge_rows(T, a.tstart, x0, y0, z0, x1, y1, z1, (R + skip) * 1.00001f + T.slack,
                                              [&](bool ok, uint32_t k) {
@@ -589,12 +589,15 @@ __global__ __launch_bounds__(kWave, 4) void k_edge_dist(EdgeArgs a) {
                 near2 = wave_min_f(near2);
                 return whole;
             };
-            // the whole part first, within a reach that doubles until there
-            // is a piece, all have been seen or the probe's reach is passed
+            // the whole part first, within a reach that doubles until there is
+            // a piece or the probe's reach is passed.  Once the reach spans the
+            // grid along every axis, only the corners are left out (their rows
+            // lie beyond it diagonally): the rest of the probe's reach at once
             centre();
-            for (float R = fminf(2.0f * T.h, a.d_prb);; R = fminf(2.0f * R, a.d_prb)) {
+            for (float R = fminf(2.0f * T.h, a.d_prb);;) {
                 const bool whole = nearest(R);
-                if (near2 < INFINITY || whole || R >= a.d_prb) break;
+                if (near2 < INFINITY || R >= a.d_prb) break;
+                R = whole ? a.d_prb : fminf(2.0f * R, a.d_prb);
             }
             if (!(near2 < INFINITY)) continue;       // nothing within reach of the group
             const float gx = cx, gy = cy, gz = cz, gnear = sqrtf(near2) * 1.00001f + T.slack;

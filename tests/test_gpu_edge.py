@@ -176,3 +176,20 @@ def test_frustum7m_hull(gpu, orc, synth):
     fin = np.isfinite(g) & (d_an > 0)
     assert fin.sum() > 1_000_000
     assert np.all(np.abs(g[fin].astype(np.float64) - d_an[fin]) <= sag + 1e-4)
+
+
+@pytest.mark.parametrize("d_prb", [25.0, 33.0, float("inf")])
+@pytest.mark.parametrize("dims", [(20.0, 20.0, 20.0), (30.0, 20.0, 10.0), (6.0, 40.0, 17.0)])
+def test_triangles_at_the_corners(gpu, orc, dims, d_prb):
+    """One small triangle at a corner, an edge or a face of the ions' box, nothing else: the search's reach spans the
+    box along every axis before it meets the triangle.  Two triangles too, for groups that meet the farther one
+    first."""
+    _say(f"case edge corners {dims} d_prb={d_prb}")
+    rng = np.random.default_rng(5)
+    xyz = (rng.random((700, 3)) * dims).astype(np.float32)
+    small = np.array([[0.0, 0.0, 0.0], [0.05, 0.0, 0.0], [0.0, 0.05, 0.0]])
+    corners = [np.array([i & 1, i >> 1 & 1, i >> 2]) * dims for i in range(8)]
+    places = corners + [np.array([0.5, 1.0, 0.0]) * dims, np.array([0.3, 0.6, 1.0]) * dims]
+    for p in [[c] for c in places] + [[corners[0], corners[7]], [corners[1], places[9]]]:
+        g, _ = check(orc, gpu, xyz, np.stack([small + q for q in p]).astype(np.float32), d_prb, method="brute")
+        assert np.isfinite(d_prb) or np.isfinite(g).all()
