@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_link(ClusterLinkArgs a) {
             if (!valid || j <= i) return;          // each pair once, from its lower index
             const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;
             const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-            if (d2 > a.out2) return;
+            if (!(d2 <= a.out2)) return;           // (NaN too: an ion without a finite position has no links)
             if (d2 > a.in2 && !(exact_D2(px, py, pz, c.x, c.y, c.z) <= a.lim2)) return;
             uf_union(a.parent, i, j);
         });

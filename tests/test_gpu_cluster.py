@@ -142,6 +142,23 @@ def test_size_histogram_around_its_lds_range(gpu, orc, n_size_bins):
     assert c[0] == 5
 
 
+@pytest.mark.parametrize("n,step", [(60, 3), (312, 6), (5000, 50), (5000, 2)])
+def test_ions_with_one_coordinate_not_finite(gpu, orc, n, step):
+    """Every step-th ion without a finite x, y or z (NaN, or an infinity), the others in the same rows of cells: each is
+    a cluster of its own."""
+    _say(f"case cluster one coordinate not finite n={n} step={step}")
+    rng = np.random.default_rng(n + step)
+    xyz = (rng.random((n, 3)) * (n / 30.0) ** (1.0 / 3.0)).astype(np.float32)
+    i = np.arange(1, n, step)
+    xyz[i, rng.integers(0, 3, len(i))] = rng.choice([np.nan, np.nan, np.inf, -np.inf], len(i)).astype(np.float32)
+    lab = rng.integers(0, 2, n).astype(np.uint8)
+    for A in (1, ANY):
+        for d_max in (0.2, 0.4):
+            gl, _ = check(orc, gpu, xyz, lab, None, A, d_max, 1, expect_status=1)
+            own = i[(lab[i] == A) | (A == ANY)]
+            assert np.array_equal(gl[own], own)
+
+
 def test_repeat_determinism(gpu, small_needle):
     xyz, lab, d = small_needle
     a = run_ms(gpu, xyz, lab, d, ANY, 0.3, 2, 1.0)
