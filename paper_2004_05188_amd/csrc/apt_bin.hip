@@ -352,13 +352,37 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
 constexpr int kCompactItems = 16;
 constexpr int kCompactTile = kBlock * kCompactItems;
 
+// The counting sort's counters of list q (0: targets, 1: neighbours): one per
+// key (the targets' in block-raster order, or cells), 2^lg places apart;
+// *places of them in all, at most `cap`.  Atomics on one line of 32 counters
+// run one after the other, about 16 ns each, so the counters of lists with many
+// ions per key lie apart (980 000 targets over 5000 cells, 160 lines: k_compact
+// 121 us; 16 places apart 72).  The scan takes the places between for keys
+// without an ion.
+__device__ __forceinline__ uint32_t cs_spread(const GridPlan& P, int q, uint32_t cap, uint32_t* places) {
+    const uint32_t n = q == 1 || P.tblock == 1
+                           ? P.n_cells
+                           : (uint32_t)P.nbx * (uint32_t)P.nby * (((uint32_t)P.dim[2] + 7u) / 8u) * 512u;
+    const uint32_t ions = q == 1 ? P.nB : P.nT;
+    uint32_t lg = 0;
+    while (lg < 5 && ((uint64_t)n << (lg + 1)) <= cap && ions / 16u > (n << lg)) ++lg;
+    *places = n << lg;
+    return lg;
+}
+
 // The sort keys of the ions one tile of k_compact selected: targets
 // [t0, t1) and neighbours [b0, b1) of the lists (contiguous: the compaction
 // is stable), or every ion of [i0, i1) when the neighbours are all ions.
+// With the counting sort (cnt non-NULL), each ion's rank within its key too.
 __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, uint32_t t1, uint32_t b0, uint32_t b1,
                                               int64_t i0, int64_t i1) {
     const GridPlan P = *a.plan;
     const double sd = a.zscale ? *a.zscale : 1.0;
+    uint32_t lgt = 0, lgb = 0, places;
+    if (a.tcnt) {
+        lgt = cs_spread(P, 0, a.n_keys_max, &places);
+        lgb = cs_spread(P, 1, a.n_keys_max, &places);
+    }
     constexpr int U = 4;   // list entries and positions in flight per thread
     // ion ids of list entries [j0, j0 + U * kBlock) of `list` (NULL: the
     // entries are the ions themselves), their positions, then f(j, id, x, y, z)
@@ -390,14 +414,14 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
         }
     };
     run(a.tid, t0, t1, [&](uint32_t j, uint32_t, float x, float y, float z) {
-        const uint32_t key = target_key(P, x, y, z);
+        const uint32_t key = target_key(P, x, y, z) << lgt;
         a.tkeys[j] = key;
         if (a.tcnt) a.trank[j] = atomicAdd(a.tcnt + key, 1u);
         else a.tvals[j] = j;
     });
     float4* __restrict__ brec = a.bcnt ? a.brec[1] : rec_after(a.brec[0], a.brec[1], (int)P.passes, -1);
     auto bkey = [&](uint32_t j, uint32_t id, float x, float y, float z) {
-        const uint32_t key = cell_id(P, x, y, z);
+        const uint32_t key = cell_id(P, x, y, z) << lgb;
         a.bkeys[j] = key;
         if (a.bcnt) a.brank[j] = atomicAdd(a.bcnt + key, 1u);
         brec[j] = make_float4(x, y, z, __builtin_bit_cast(float, id));
@@ -1026,16 +1050,12 @@ __device__ __forceinline__ void gather(const GatherArgs& a, uint32_t bid, uint32
 // 8. counting sort (small clouds): the counts of each key, made by the
 //    compaction, scanned and used
 // ------------------------------------------------------------------------
-// keys of list q: the targets' keys (block-raster order or cells), the cells
-__device__ __forceinline__ uint32_t cs_keys(const GridPlan& P, int q) {
-    if (q == 1 || P.tblock == 1) return P.n_cells;
-    return (uint32_t)P.nbx * (uint32_t)P.nby * (((uint32_t)P.dim[2] + 7u) / 8u) * 512u;
-}
-
 __global__ __launch_bounds__(kBlock) void k_cs_scan(CountSortArgs a) {
     const GridPlan P = *a.plan;
     const int q = blockIdx.y;
-    const uint32_t n = cs_keys(P, q), base = blockIdx.x * (uint32_t)kCsTile;
+    uint32_t n;
+    (void)cs_spread(P, q, a.n_keys_max, &n);
+    const uint32_t base = blockIdx.x * (uint32_t)kCsTile;
     if (base >= n) return;
     __shared__ uint32_t s_w[kWavesPerBlock], s_d[kWavesPerBlock];
     constexpr uint32_t per = kCsTile / kBlock;
@@ -1073,7 +1093,8 @@ __global__ __launch_bounds__(kBlock) void k_cs_scan(CountSortArgs a) {
 __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
     __shared__ uint32_t s_off[2][kCsTiles], s_w[2][kWavesPerBlock];
     const GridPlan P = *a.plan;
-    const uint32_t nk[2] = {cs_keys(P, 0), cs_keys(P, 1)};
+    uint32_t nk[2];
+    const uint32_t lg[2] = {cs_spread(P, 0, a.n_keys_max, &nk[0]), cs_spread(P, 1, a.n_keys_max, &nk[1])};
     {
         // where each tile starts: the sums of the tiles before it
         const int t = threadIdx.x, w = t / kWave;
@@ -1096,7 +1117,7 @@ __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
     auto start = [&](int q, uint32_t key) { return a.cnt[q][key] + s_off[q][key / kCsTile]; };
     const uint32_t first = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
     for (uint32_t j = first; j < P.nB; j += stride) a.bpos[start(1, a.bkeys[j]) + a.brank[j]] = a.brec[j];
-    for (uint32_t c = first; c <= P.n_cells; c += stride) a.cell_start[c] = c < P.n_cells ? start(1, c) : P.nB;
+    for (uint32_t c = first; c <= P.n_cells; c += stride) a.cell_start[c] = c < P.n_cells ? start(1, c << lg[1]) : P.nB;
     for (uint32_t j = first; j < P.nT; j += stride) {
         const uint32_t id = a.tid[j], p = start(0, a.tkeys[j]) + a.trank[j];
         a.t_rank[p] = j;
@@ -1107,7 +1128,7 @@ __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
     }
     // (mode 3: the targets are in plain cell order)
     if (P.tile_mode == 3 && a.t_cell_start)
-        for (uint32_t c = first; c <= P.n_cells; c += stride) a.t_cell_start[c] = c < P.n_cells ? start(0, c) : P.nT;
+        for (uint32_t c = first; c <= P.n_cells; c += stride) a.t_cell_start[c] = c < P.n_cells ? start(0, c << lg[0]) : P.nT;
 }
 
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a) { gather(a, blockIdx.x, gridDim.x); }

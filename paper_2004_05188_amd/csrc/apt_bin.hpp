@@ -154,6 +154,7 @@ struct CompactArgs {
     uint32_t* bcnt = nullptr;
     uint32_t* trank = nullptr;
     uint32_t* brank = nullptr;
+    uint32_t n_keys_max = 0;   // counters per list
 };
 
 // Counting sort of clouds up to kCountSortMax ions: the compaction counts

@@ -110,6 +110,33 @@ def test_counting_sort_sizes(orc, n):
         assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, A, B, 0.25, 2.0, 100))
 
 
+@pytest.mark.parametrize("few", [0, 1, 2, 40, 1500, 9000])
+@pytest.mark.parametrize("n", [65, 9_000, 131_073])
+def test_counting_sort_with_many_ions_per_key(orc, n, few):
+    """Cells sized for `few` ions of one species that all others share: counters 1 to 32 places apart, for the targets
+    (few neighbours) or the neighbours (few targets), up to the counters that there are; against the oracle."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    few = min(few, n)
+    print(f"case many ions per key n={n} few={few}", flush=True)
+    rng = np.random.default_rng(n + few)
+    xyz = (rng.random((n, 3)) * (n / 30.0) ** (1.0 / 3.0)).astype(np.float32)
+    lab = np.zeros(n, np.uint8)
+    lab[rng.permutation(n)[:few]] = 1
+    d = rng.random(n).astype(np.float32)
+    cloud = aptstat.Cloud(*(torch.from_numpy(v).cuda() for v in (xyz, lab, d)))
+    for A, B in ((0, 1), (1, 0), (1, 1), (ANY, 1)):
+        g = aptstat.knn_rdf(cloud, A, B, 0.25, 3, r_max=0.6, n_bins=50, kb_nbins=100)
+        t, dist, nid, h = orc.knn(xyz, lab, d, A, B, 0.25, 3, kb_rmax=5.0, kb_nbins=100)
+        tid, gd, gn = (v.cpu().numpy() for v in g.trimmed())
+        assert np.array_equal(tid, t) and np.array_equal(gn, nid)
+        assert np.allclose(gd, dist, rtol=1e-6, atol=0)
+        assert np.array_equal(g.knn_hist.cpu().numpy().astype(np.uint64), h)
+        assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, A, B, 0.25, 0.6, 50))
+
+
 @pytest.mark.parametrize("blob", [300, 511, 512, 513, 3000])
 def test_tiles_with_many_candidates(orc, blob):
     """Dense targets around a tight ball of `blob` neighbours: tiles just inside and beyond what a stage of 512
