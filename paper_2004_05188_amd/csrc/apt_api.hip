@@ -452,24 +452,31 @@ __global__ void k_finish(FinishArgs a) {
     if (a.capacity >= 0 && (int64_t)nT > a.capacity && a.status) atomicOr(a.status, APT_STATUS_CAPACITY);
 }
 
+// Whether the binning of n ions is the counting sort (the smoothed RDF's is not).
+static bool counting_sort(int64_t n, apt_query q) {
+    const bool every = q.target == APT_ANY || q.neighbor == APT_ANY;
+    return n <= (every ? kCountSortMax / 2 : kCountSortMax);
+}
+
 // The binning stage shared by the plain entry points.  Leaves in the
 // workspace: plan, tid (eligible targets ascending), order (their ranks in
 // cell order, with rank, index and position), neighbour SoA in cell order
 // and cell_start.
 // zscale (device, may be NULL) scales z before binning; sel_union makes
 // targets and neighbours both the ions that take part in a pair in either
-// role.
+// role; same_ions: they are the same ions, and the counting sort leaves out the
+// targets' order (the neighbour records hold it: a sort of as many ions less,
+// 1e6 ions of one species 120 us of the call's 690).
 static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams& plan, const PlainWs& w,
                               int32_t* status, hipStream_t st, const double* zscale = nullptr,
-                              int sel_union = 0, const InitArgs* init = nullptr) {
+                              int sel_union = 0, const InitArgs* init = nullptr, bool same_ions = false) {
     const int64_t n = cl->n;
     const int G = count_blocks(n);
     const int64_t chunk = count_chunk(n);
     const int cus = device_info().cus;
     // (the smoothed RDF adds in the order of the records, which has to be the
     // same from run to run: it passes no `init` and keeps the stable sort)
-    const bool every = q.target == APT_ANY || q.neighbor == APT_ANY;
-    const bool counting = init && n <= (every ? kCountSortMax / 2 : kCountSortMax);
+    const bool counting = init && counting_sort(n, q);
     PlanParams pp = plan;
     pp.digit_bits = sort_digit_bits(n);
     if (counting) {
@@ -499,6 +506,7 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
                    {w.bpos, w.brec2}};
     const bool occ = pp.k > 0 && !zscale;
     if (counting) {
+        if (same_ions) cm.tkeys = nullptr;
         cm.tcnt = w.V[0];
         cm.bcnt = w.V[1];
         cm.trank = w.K[1];
@@ -507,10 +515,10 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
         hipLaunchKernelGGL(k_compact, dim3(G), dim3(kBlock), 0, st, cm);
         CountSortArgs cs{w.plan, pp.key_cap, {w.V[0], w.V[1]}, {w.rs_counts, w.rs_counts + kCsTiles},
                          {occ ? w.strag_count + 1 : nullptr, occ ? w.strag_count + 2 : nullptr},
-                         w.tid, w.K[0], w.K[1], cl->xyz, w.t_rank, w.t_id, w.tx, w.ty, w.tz, w.t_cell_start,
+                         w.tid, cm.tkeys, w.K[1], cl->xyz, w.t_rank, w.t_id, w.tx, w.ty, w.tz, w.t_cell_start,
                          w.KB[0], w.KB[1], w.brec2, w.bpos, w.cell_start};
         const int tiles = (int)((pp.key_cap + kCsTile - 1) / kCsTile);
-        hipLaunchKernelGGL(k_cs_scan, dim3(tiles, 2), dim3(kBlock), 0, st, cs);
+        hipLaunchKernelGGL(k_cs_scan, dim3(tiles, same_ions ? 1 : 2), dim3(kBlock), 0, st, cs);
         const int gp = (int)std::min<int64_t>(std::max<int64_t>((n + kBlock - 1) / kBlock, 1), cus * 8);
         hipLaunchKernelGGL(k_cs_place, dim3(gp), dim3(kBlock), 0, st, cs);
         return hip_check("binning launch");
@@ -1804,7 +1812,7 @@ apt_status apt_cluster_ms(const apt_cloud* cloud, uint8_t species, float d_max, 
     pp.h_shrink = 0.7f;
     {
         TraceSpan span("binning", st);
-        if ((s = run_binning(&cl, q, pp, w, status, st, nullptr, 0, &ia)) != APT_OK) return s;
+        if ((s = run_binning(&cl, q, pp, w, status, st, nullptr, 0, &ia, true)) != APT_OK) return s;
     }
     if (cl.n == 0) return hip_check("clustering launch");
     const uint32_t n = (uint32_t)cl.n;
@@ -1813,7 +1821,7 @@ apt_status apt_cluster_ms(const apt_cloud* cloud, uint8_t species, float d_max, 
     const int g = (int)std::min<int64_t>(((int64_t)n + kBlock - 1) / kBlock, 8192);
     ClusterLinkArgs la{};
     la.plan = w.plan;
-    la.t_id = w.t_id;
+    la.t_id = counting_sort(cl.n, q) ? nullptr : w.t_id;
     la.tx = w.tx;
     la.ty = w.ty;
     la.tz = w.tz;

@@ -379,7 +379,7 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
     const GridPlan P = *a.plan;
     const double sd = a.zscale ? *a.zscale : 1.0;
     uint32_t lgt = 0, lgb = 0, places;
-    if (a.tcnt) {
+    if (a.bcnt) {
         lgt = cs_spread(P, 0, a.n_keys_max, &places);
         lgb = cs_spread(P, 1, a.n_keys_max, &places);
     }
@@ -413,7 +413,7 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
             }
         }
     };
-    run(a.tid, t0, t1, [&](uint32_t j, uint32_t, float x, float y, float z) {
+    if (a.tkeys) run(a.tid, t0, t1, [&](uint32_t j, uint32_t, float x, float y, float z) {
         const uint32_t key = target_key(P, x, y, z) << lgt;
         a.tkeys[j] = key;
         if (a.tcnt) a.trank[j] = atomicAdd(a.tcnt + key, 1u);
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_compact(CompactArgs a) {
             if (mb[it] & bit) a.bsel[s_base[1][it][w] + __popcll(mb[it] & lanemask_lt())] = (uint32_t)i;
         }
         __syncthreads();   // the tile's list entries are visible to the whole workgroup
-        if (a.tkeys) {
+        if (a.bkeys) {
             const int64_t te = tile + kCompactTile < end ? tile + kCompactTile : end;
             compact_keys(a, s_base[0][0][0], s_run[0], s_base[1][0][0], s_run[1], tile, te);
             __syncthreads();
@@ -1052,7 +1052,7 @@ __device__ __forceinline__ void gather(const GatherArgs& a, uint32_t bid, uint32
 // ------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_cs_scan(CountSortArgs a) {
     const GridPlan P = *a.plan;
-    const int q = blockIdx.y;
+    const int q = a.tkeys ? blockIdx.y : 1;
     uint32_t n;
     (void)cs_spread(P, q, a.n_keys_max, &n);
     const uint32_t base = blockIdx.x * (uint32_t)kCsTile;
@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
         uint32_t v[2], inc[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            v[q] = t < kCsTiles && (uint32_t)t * kCsTile < nk[q] ? a.sums[q][t] : 0u;
+            v[q] = t < kCsTiles && (uint32_t)t * kCsTile < nk[q] && (q == 1 || a.tkeys) ? a.sums[q][t] : 0u;
             inc[q] = wave_incl_scan(v[q]);
             if (lane_id() == kWave - 1) s_w[q][w] = inc[q];
         }
@@ -1118,6 +1118,7 @@ __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
     const uint32_t first = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
     for (uint32_t j = first; j < P.nB; j += stride) a.bpos[start(1, a.bkeys[j]) + a.brank[j]] = a.brec[j];
     for (uint32_t c = first; c <= P.n_cells; c += stride) a.cell_start[c] = c < P.n_cells ? start(1, c << lg[1]) : P.nB;
+    if (!a.tkeys) return;
     for (uint32_t j = first; j < P.nT; j += stride) {
         const uint32_t id = a.tid[j], p = start(0, a.tkeys[j]) + a.trank[j];
         a.t_rank[p] = j;

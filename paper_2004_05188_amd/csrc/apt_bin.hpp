@@ -137,8 +137,8 @@ struct CompactArgs {
     uint32_t* tid;          // [nT]
     uint32_t* bsel;         // [nB] or NULL (neighbours = all ions)
     int32_t sel_union;      // as CountArgs::sel_union
-    // sort keys written with the lists (plan from k_plan; NULL keys: none):
-    // targets (block-raster key, list position), neighbours (cell id and
+    // sort keys written with the lists (plan from k_plan): targets
+    // (block-raster key, list position; tkeys NULL: none), neighbours (cell id and
     // their 16-byte record (x, y, z, ion index) into the record buffer that
     // the sort's passes start from, see SortArgs::rec)
     const GridPlan* plan;
@@ -148,7 +148,7 @@ struct CompactArgs {
     uint32_t* tvals;
     uint32_t* bkeys;
     float4* brec[2];
-    // the counting sort (tcnt non-NULL): each key's count so far is the ion's
+    // the counting sort (bcnt non-NULL): each key's count so far is the ion's
     // rank within its key; the records go to brec[1]
     uint32_t* tcnt = nullptr;
     uint32_t* bcnt = nullptr;
@@ -182,7 +182,7 @@ struct CountSortArgs {
     uint32_t* distinct[2];  // += keys with a count, or NULL
     // targets
     const uint32_t* tid;
-    const uint32_t* tkeys;
+    const uint32_t* tkeys;  // NULL: no target order (the targets are the neighbours)
     const uint32_t* trank;
     const float* xyz;
     uint32_t* t_rank;
@@ -330,7 +330,7 @@ __global__ void k_rs_scan(SortSet a);
 __global__ void k_rs_downsweep_large(SortSet a);   // kDsLargeBlock threads
 __global__ void k_rs_downsweep_small(SortSet a);   // kDsSmallBlock threads
 __global__ void k_gather(GatherArgs a);
-__global__ void k_cs_scan(CountSortArgs a);      // grid (kCsTiles, 2)
+__global__ void k_cs_scan(CountSortArgs a);      // grid (tiles, lists)
 __global__ void k_cs_place(CountSortArgs a);
 // the target order (first g_order workgroups) and the neighbour gather (the
 // rest) in one launch: they read and write disjoint arrays

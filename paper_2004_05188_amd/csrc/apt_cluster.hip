@@ -79,10 +79,11 @@ __global__ __launch_bounds__(kBlock) void k_ms_link(ClusterLinkArgs a) {
     const uint32_t t0 = (uint32_t)((uint64_t)P.nT * (uint64_t)xcd / kXcd);
     const uint32_t t1 = (uint32_t)((uint64_t)P.nT * (uint64_t)(xcd + 1) / kXcd);
     for (uint32_t s = t0 + wx; s < t1; s += wstride) {
-        const uint32_t i = __builtin_amdgcn_readfirstlane(a.t_id[s]);
-        const float px = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.tx[s])));
-        const float py = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.ty[s])));
-        const float pz = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.tz[s])));
+        const float4 own = a.t_id ? make_float4(a.tx[s], a.ty[s], a.tz[s], __builtin_bit_cast(float, a.t_id[s])) : a.bpos[s];
+        const uint32_t i = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(uint32_t, own.w));
+        const float px = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, own.x)));
+        const float py = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, own.y)));
+        const float pz = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, own.z)));
         if (!(isfinite(px) && isfinite(py) && isfinite(pz))) continue;
         enumerate(P, a.cell_start, a.bpos, px, py, pz, a.r_enum, [&](bool valid, float4 c) {
             const uint32_t j = __builtin_bit_cast(uint32_t, c.w);

@@ -8,7 +8,7 @@ namespace apt {
 
 struct ClusterLinkArgs {
     const GridPlan* plan;
-    const uint32_t* t_id;        // [nT] the species' ions in cell order: ion index
+    const uint32_t* t_id;        // [nT] the species' ions in cell order: ion index, or NULL: in that of bpos
     const float* tx;             // ... position
     const float* ty;
     const float* tz;
