@@ -137,6 +137,34 @@ def test_counting_sort_with_many_ions_per_key(orc, n, few):
         assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, A, B, 0.25, 0.6, 50))
 
 
+@pytest.mark.parametrize("n", [64, 700, 30_011])
+@pytest.mark.parametrize("every,axes", [(1, 3), (2, 3), (2, 1), (7, 3)])
+def test_counting_sort_without_finite_positions(orc, n, every, axes):
+    """Every (second, seventh) ion without a finite position, or without a finite x alone: a wavefront's ranks among
+    ions that share a counter, beside finite ones and full wavefronts; against the oracle."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    print(f"case counting sort not finite n={n} every={every} axes={axes}", flush=True)
+    rng = np.random.default_rng(n + every)
+    xyz = (rng.random((n, 3)) * (n / 30.0) ** (1.0 / 3.0)).astype(np.float32)
+    xyz[::every, :axes] = np.nan
+    xyz[0, 0] = -np.inf
+    lab = rng.integers(0, 2, n).astype(np.uint8)
+    d = rng.random(n).astype(np.float32)
+    cloud = aptstat.Cloud(*(torch.from_numpy(v).cuda() for v in (xyz, lab, d)))
+    for A, B in ((ANY, ANY), (1, 0)):
+        g = aptstat.knn_rdf(cloud, A, B, 0.25, 3, r_max=0.6, n_bins=50, kb_nbins=100)
+        t, dist, nid, h = orc.knn(xyz, lab, d, A, B, 0.25, 3, kb_rmax=5.0, kb_nbins=100)
+        tid, gd, gn = (v.cpu().numpy() for v in g.trimmed())
+        assert int(g.status.item()) == aptstat.STATUS_NONFINITE
+        assert np.array_equal(tid, t) and np.array_equal(gn, nid)
+        assert np.allclose(gd, dist, rtol=1e-6, atol=0)
+        assert np.array_equal(g.knn_hist.cpu().numpy().astype(np.uint64), h)
+        assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, A, B, 0.25, 0.6, 50))
+
+
 @pytest.mark.parametrize("blob", [300, 511, 512, 513, 3000])
 def test_tiles_with_many_candidates(orc, blob):
     """Dense targets around a tight ball of `blob` neighbours: tiles just inside and beyond what a stage of 512
