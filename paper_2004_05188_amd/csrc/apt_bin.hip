@@ -394,13 +394,16 @@ __device__ __forceinline__ uint32_t cs_rank(uint32_t* cnt, uint32_t place, bool 
 // The sort keys of the ions one tile of k_compact selected: targets
 // [t0, t1) and neighbours [b0, b1) of the lists (contiguous: the compaction
 // is stable), or every ion of [i0, i1) when the neighbours are all ions.
-// With the counting sort (cnt non-NULL), each ion's rank within its key too.
+// COUNT: for the counting sort, each ion's rank within its key too (a kernel of
+// its own: with both in one, the compaction of 7.7e6 ions, 1 % of them in the
+// lists, took 31.4 us instead of 26.3).
+template <bool COUNT>
 __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, uint32_t t1, uint32_t b0, uint32_t b1,
                                               int64_t i0, int64_t i1) {
     const GridPlan P = *a.plan;
     const double sd = a.zscale ? *a.zscale : 1.0;
     uint32_t lgt = 0, lgb = 0, places;
-    if (a.bcnt) {
+    if (COUNT) {
         lgt = cs_spread(P, 0, a.n_keys_max, &places);
         lgb = cs_spread(P, 1, a.n_keys_max, &places);
     }
@@ -434,17 +437,18 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
             }
         }
     };
-    if (a.tkeys) run(a.tid, t0, t1, [&](uint32_t j, uint32_t, float x, float y, float z) {
+    auto tput = [&](uint32_t j, uint32_t, float x, float y, float z) {
         const uint32_t key = target_key(P, x, y, z) << lgt;
         a.tkeys[j] = key;
-        if (a.tcnt) a.trank[j] = cs_rank(a.tcnt, key, isfinite(x) && isfinite(y) && isfinite(z));
+        if (COUNT) a.trank[j] = cs_rank(a.tcnt, key, isfinite(x) && isfinite(y) && isfinite(z));
         else a.tvals[j] = j;
-    });
-    float4* __restrict__ brec = a.bcnt ? a.brec[1] : rec_after(a.brec[0], a.brec[1], (int)P.passes, -1);
+    };
+    if (!COUNT || a.tkeys) run(a.tid, t0, t1, tput);
+    float4* __restrict__ brec = COUNT ? a.brec[1] : rec_after(a.brec[0], a.brec[1], (int)P.passes, -1);
     auto bkey = [&](uint32_t j, uint32_t id, float x, float y, float z) {
         const uint32_t key = cell_id(P, x, y, z) << lgb;
         a.bkeys[j] = key;
-        if (a.bcnt) a.brank[j] = cs_rank(a.bcnt, key, isfinite(x) && isfinite(y) && isfinite(z));
+        if (COUNT) a.brank[j] = cs_rank(a.bcnt, key, isfinite(x) && isfinite(y) && isfinite(z));
         brec[j] = make_float4(x, y, z, __builtin_bit_cast(float, id));
     };
     if (a.bsel) run(a.bsel, b0, b1, bkey);
@@ -452,6 +456,7 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
 }
 
 // (at most 64 VGPRs: eight wavefronts per SIMD for the streaming reads)
+template <bool COUNT>
 __global__ __launch_bounds__(kBlock, 8) void k_compact(CompactArgs a) {
     __shared__ uint32_t s_cnt[2][kCompactItems][kWavesPerBlock];
     __shared__ uint32_t s_base[2][kCompactItems][kWavesPerBlock];
@@ -504,13 +509,14 @@ __global__ __launch_bounds__(kBlock, 8) void k_compact(CompactArgs a) {
             if (mb[it] & bit) a.bsel[s_base[1][it][w] + __popcll(mb[it] & lanemask_lt())] = (uint32_t)i;
         }
         __syncthreads();   // the tile's list entries are visible to the whole workgroup
-        if (a.bkeys) {
-            const int64_t te = tile + kCompactTile < end ? tile + kCompactTile : end;
-            compact_keys(a, s_base[0][0][0], s_run[0], s_base[1][0][0], s_run[1], tile, te);
-            __syncthreads();
-        }
+        const int64_t te = tile + kCompactTile < end ? tile + kCompactTile : end;
+        compact_keys<COUNT>(a, s_base[0][0][0], s_run[0], s_base[1][0][0], s_run[1], tile, te);
+        __syncthreads();
     }
 }
+
+template __global__ void k_compact<false>(CompactArgs);
+template __global__ void k_compact<true>(CompactArgs);
 
 // ------------------------------------------------------------------------
 // 4. cell keys

@@ -148,7 +148,7 @@ struct CompactArgs {
     uint32_t* tvals;
     uint32_t* bkeys;
     float4* brec[2];
-    // the counting sort (bcnt non-NULL): each key's count so far is the ion's
+    // the counting sort: each key's count so far is the ion's
     // rank within its key; the records go to brec[1]
     uint32_t* tcnt = nullptr;
     uint32_t* bcnt = nullptr;
@@ -322,7 +322,8 @@ __device__ inline void fill_edges(double* E2, float r_max, int n_bins, int t, in
 
 __global__ void k_count(CountArgs a);
 __global__ void k_plan(PlanArgs a);
-__global__ void k_compact(CompactArgs a);
+template <bool COUNT>
+__global__ void k_compact(CompactArgs a);           // COUNT: for the counting sort
 __global__ void k_keys(KeyArgs a);
 template <int BITS>
 __global__ void k_rs_upsweep(SortSet a);           // digits of at most BITS bits
