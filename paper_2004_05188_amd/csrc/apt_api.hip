@@ -1192,14 +1192,21 @@ static apt_status run_sdm(const apt_cloud* cl, apt_query q, float R, int32_t n_v
     (void)hipGetLastError();
     const int64_t nv = (int64_t)n_vox * n_vox * n_vox;
     // the histogram is zeroed by the binning's first kernel, unless that has
-    // too few workgroups for it (16 voxels per thread: 3 workgroups took
-    // 130 us over 160^3 voxels)
-    const bool own_zero = nv > (int64_t)count_blocks(cl->n) * kBlock * 16;
+    // too few workgroups for it (64 voxels per thread; 160^3 voxels on the 79
+    // workgroups of 20 000 ions: 97 us with the launch, 92 without; on 489, a call of
+    // 111 us was 4 us longer with it)
+    const bool own_zero = nv > (int64_t)count_blocks(cl->n) * kBlock * 64;
     if (own_zero) {
         InitArgs za{nullptr, hist, (int32_t)nv};
         hipLaunchKernelGGL(k_init, dim3(device_info().cus * 8), dim3(256), 0, st, za);
     }
-    InitArgs ia{status, own_zero ? nullptr : hist, (int32_t)nv, nullptr, 0, nullptr, w.strag_count};
+    // (the lists' fill counts take the other histogram's edges, which only a kNN
+    // has: the sort uses its own counts until the pairs are enumerated)
+    uint64_t* const used = reinterpret_cast<uint64_t*>(w.KE2);
+    InitArgs ia{status, own_zero ? nullptr : hist, (int32_t)nv, used, kXcd * kSdmRuns, nullptr, w.strag_count};
+    ia.faces = w.E2;
+    ia.face_R = R;
+    ia.n_vox = n_vox;
     const apt_tuning tu = tuning();
     const double Rd = (double)R;
     PlanParams pp;
@@ -1238,16 +1245,15 @@ static apt_status run_sdm(const apt_cloud* cl, apt_query q, float R, int32_t n_v
     a.hist = hist;
     // the lists take the arrays that only the binning needed (the ion lists,
     // both sorts' keys and values, the second record buffer: one contiguous
-    // part of the workspace), their fill counts the sort's digit counts
+    // part of the workspace)
     const size_t room = (size_t)(reinterpret_cast<char*>(w.t_rank) - reinterpret_cast<char*>(w.tid));
     const size_t cap = std::min<size_t>(room / sizeof(uint16_t) / (kXcd * kSdmRuns) / 64 * 64, 0x7FFFFFC0u);
-    a.used = reinterpret_cast<unsigned long long*>(w.rs_counts);
+    a.used = reinterpret_cast<unsigned long long*>(used);
     // (fewer than 64 entries each: the cloud has too few ions for a list)
     a.lg_run = kSdmLgRunMin;
     while (a.lg_run < kSdmLgRunMax && ((int64_t)kSdmRuns << a.lg_run) < nv) ++a.lg_run;
     a.list = nv <= ((int64_t)kSdmRuns << a.lg_run) && cap > 0 ? reinterpret_cast<uint16_t*>(w.tid) : nullptr;
     a.cap = (uint32_t)cap;
-    hipLaunchKernelGGL(k_sdm_faces, dim3(1), dim3(kBlock), 0, st, a, w.E2);
     {
         TraceSpan span("sdm", st);
         hipLaunchKernelGGL(k_sdm, dim3(resident_grid(k_sdm, 0)), dim3(kBlock), 0, st, a);

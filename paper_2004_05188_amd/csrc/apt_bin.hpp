@@ -69,6 +69,9 @@ struct InitArgs {
     uint32_t* work_q = nullptr;   // [2][kXcd] work counters of the pair kernels, kWorkStride apart, or NULL
     uint32_t* zero[2] = {nullptr, nullptr};   // [n_zero] the counting sort's counters, or NULL
     uint32_t n_zero = 0;
+    double* faces = nullptr;      // [n_vox + 1] the voxel faces of [-face_R, face_R], or NULL
+    float face_R = 0.0f;
+    int32_t n_vox = 0;
 };
 
 __device__ inline void fill_edges(double* E2, float r_max, int n_bins, int t, int stride);
@@ -89,6 +92,11 @@ __device__ inline void init_body(const InitArgs& a, int t, int st) {
         for (int b = t; b < a.n1; b += st) a.h1[b] = 0;
     if (a.h2)
         for (int b = t; b < a.n2; b += st) a.h2[b] = 0;
+    if (a.faces) {
+#pragma clang fp contract(off)
+        for (int m = t; m <= a.n_vox; m += st)
+            a.faces[m] = ((double)(2 * m - a.n_vox) * (double)a.face_R) / (double)a.n_vox;
+    }
     if (a.zero[0])
         for (uint32_t b = (uint32_t)t; b < a.n_zero; b += (uint32_t)st) {
             a.zero[0][b] = 0;

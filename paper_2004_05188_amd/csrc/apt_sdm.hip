@@ -28,13 +28,6 @@
 
 namespace apt {
 
-__global__ __launch_bounds__(kBlock) void k_sdm_faces(SdmArgs a, double* F) {
-#pragma clang fp contract(off)
-    for (int m = threadIdx.x; m <= a.n_vox; m += kBlock)
-        F[m] = ((double)(2 * m - a.n_vox) * (double)a.R) / (double)a.n_vox;
-    for (int b = threadIdx.x; b < kXcd * kSdmRuns; b += kBlock) a.used[b] = 0ull;
-}
-
 // voxel of one displacement component: FP32 coordinate, FP64 near a face
 __device__ __forceinline__ int sdm_axis(const SdmArgs& a, float v32, float pi, float pj) {
     const float t = (v32 + a.R) * a.inv_w;
@@ -107,11 +100,25 @@ __device__ __forceinline__ void sdm_targets(const SdmArgs& a, SdmBuf* B) {
     const uint32_t t1 = (uint32_t)((uint64_t)P.nT * (uint64_t)(xcd + 1) / kXcd);
     const uint32_t nv = (uint32_t)a.n_vox;
     int cnt = 0;
+    // the next target is loaded while this one's pairs are counted (not with the
+    // lists, whose kernel has no registers left for it)
+    uint32_t next_i = 0;
+    float next_x = 0.0f, next_y = 0.0f, next_z = 0.0f;
+    auto load = [&](uint32_t s) {
+        if (s >= t1) return;
+        next_i = a.t_id[s];
+        next_x = a.tx[s];
+        next_y = a.ty[s];
+        next_z = a.tz[s];
+    };
+    if (!LIST) load(t0 + wx);
     for (uint32_t s = t0 + wx; s < t1; s += wstride) {
-        const uint32_t i = __builtin_amdgcn_readfirstlane(a.t_id[s]);
-        const float px = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.tx[s])));
-        const float py = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.ty[s])));
-        const float pz = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.tz[s])));
+        if (LIST) load(s);
+        const uint32_t i = __builtin_amdgcn_readfirstlane(next_i);
+        const float px = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, next_x)));
+        const float py = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, next_y)));
+        const float pz = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, next_z)));
+        if (!LIST) load(s + wstride);
         if (!(isfinite(px) && isfinite(py) && isfinite(pz))) continue;
         enumerate(P, a.cell_start, a.bpos, px, py, pz, a.r_enum, [&](bool valid, float4 c) {
             const float dx = c.x - px, dy = c.y - py, dz = c.z - pz;

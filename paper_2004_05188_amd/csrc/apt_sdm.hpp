@@ -42,7 +42,6 @@ struct SdmArgs {
     uint32_t lg_run;
 };
 
-__global__ void k_sdm_faces(SdmArgs a, double* F);
 __global__ void k_sdm(SdmArgs a);               // counts pair by pair
 __global__ void k_sdm_list(SdmArgs a);          // through the lists; k_sdm or k_sdm_list does the work
 __global__ void k_sdm_merge(SdmArgs a);        // kSdmMergeBlock threads; grid (4, kSdmRuns)
