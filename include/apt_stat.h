@@ -366,8 +366,10 @@ apt_status apt_count_candidates(const apt_cloud* cloud, apt_query q, apt_bins bi
  *                wavefront (2, 3 and 4 only when k <= 16 and n_bins <= 2048;
  *                4 also needs k >= 1)
  *   cell_occ     neighbours per grid cell aimed at with one target per
- *                wavefront (default 4)
- *   h_min_frac   smallest cell edge as a fraction of r_max (default 0.5)
+ *                wavefront (default 4); apt_edge_distance: a quarter of the
+ *                ions per cell
+ *   h_min_frac   smallest cell edge as a fraction of r_max (default 0.5);
+ *                apt_edge_distance, which has no r_max, does not use it
  *   tile_occ     neighbours per grid cell aimed at with 64 targets per
  *                wavefront or one per lane (default 1; 0 selects the default)
  *   rdf_kernel   the RDF kernel of the dense-neighbour mode (tile_policy 4 or

@@ -1720,7 +1720,7 @@ apt_status apt_edge_distance(const apt_cloud* cloud, const float* tri, int64_t n
     // 64 consecutive ions are one search group: with about 16 per cell of the
     // bounding box (a needle fills it by half) they span two cells of a row
     pp.h_min = 0.0f;
-    pp.occ = 16.0f;
+    pp.occ = 4.0f * tu.cell_occ;
     pp.tile_occ = tu.tile_occ;
     pp.k = 0;
     pp.cell_cap = cell_cap_for(cl.n);

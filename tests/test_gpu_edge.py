@@ -193,3 +193,15 @@ def test_triangles_at_the_corners(gpu, orc, dims, d_prb):
     for p in [[c] for c in places] + [[corners[0], corners[7]], [corners[1], places[9]]]:
         g, _ = check(orc, gpu, xyz, np.stack([small + q for q in p]).astype(np.float32), d_prb, method="brute")
         assert np.isfinite(d_prb) or np.isfinite(g).all()
+
+
+@pytest.mark.parametrize("cell_occ", [0.1, 1.0, 4.0, 100.0, 1e6])
+def test_tuned_cells(gpu, orc, needle, cell_occ):
+    """cell_occ sets the ions' cells, from more cells than ions to one cell for all: the distances stay the same."""
+    _say(f"case edge cell_occ={cell_occ}")
+    _, xyz, _, mesh = needle
+    gpu[0].set_tuning(cell_occ=cell_occ)
+    try:
+        check(orc, gpu, xyz[:20_000], mesh, 1.5)
+    finally:
+        gpu[0].set_tuning()
