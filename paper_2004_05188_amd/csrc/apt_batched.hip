@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
     const double vol = batch_volume(a, P);
     int cur = -1;                     // (replicate, pair) of the LDS histogram contents
     uint32_t since_flush = 0;
-    const uint32_t flush_at = flush_limit((uint64_t)a.n);
+    const uint32_t flush_at = flush_limit((uint32_t)a.n);
     uint64_t seg_a0 = 0;
     const float* d_bnd = a.d_bnd;
     float d_srf = 0.0f;
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_pair_batched(BatchPairArgs a) {  
                           1ull);
             }
             wave_sync();
-            since_flush += steps * kWave;
+            since_flush += counts_of(steps, (uint32_t)a.n);
             if (since_flush >= flush_at) {
                 flush_hist(T.hist_l, T.hist_g, a.n_bins);
                 since_flush = 0;

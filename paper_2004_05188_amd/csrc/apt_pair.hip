@@ -107,7 +107,7 @@ __device__ __forceinline__ void pair_items(const PairArgs& a, const GridPlan& P,
         }
         if (LDS_HIST) {
             // u32 LDS counters: flush before a further target could overflow them
-            since_flush += steps * kWave;
+            since_flush += counts_of(steps, P.nB);
             if (since_flush >= flush_at) {
                 flush_hist(T.hist_l, a.hist, a.n_bins);
                 since_flush = 0;

@@ -731,14 +731,16 @@ __device__ __forceinline__ uint64_t run_tile_kth(const GridPlan& P, const PairTa
     return settled ? (((uint64_t)__builtin_bit_cast(uint32_t, tau) << 32) | (uint64_t)jk) : ~0ull;
 }
 
-// Steps of 64 candidates that one target's RDF can take, in counts, taken off
-// 2^32: the bound at which a wavefront's u32 LDS counters are flushed before
-// another target.  (A step that ends a group of rows may be less than full, one
-// in 64 rows: at most twice nB and 64 more.  Clouds too large for that flush
-// after every target, whose counts are at most nB.)
-__device__ __forceinline__ uint32_t flush_limit(uint64_t nB) {
-    return nB >= 0x3FFFFFFFull ? 0u : 0xFFFFFFFFu - (uint32_t)(2 * nB + kWave);
+// RDF counts of one target after `steps` steps of 64 candidates, at most: the
+// candidates of full steps, and never more than the nB neighbours (a step that
+// ends a group of 64 rows may be nearly empty, one for each group that holds a
+// record).
+__device__ __forceinline__ uint32_t counts_of(uint32_t steps, uint32_t nB) {
+    return steps < nB / (uint32_t)kWave ? steps * (uint32_t)kWave : nB;
 }
+// The counts from which a wavefront's u32 LDS counters are flushed before
+// another target: below it, that target's nB at most still fit.
+__device__ __forceinline__ uint32_t flush_limit(uint32_t nB) { return 0xFFFFFFFFu - nB; }
 
 // Flush a per-wavefront u32 LDS histogram into a global u64 histogram.
 __device__ __forceinline__ void flush_hist(uint32_t* hist_l, uint64_t* hist_g, int n_bins) {
