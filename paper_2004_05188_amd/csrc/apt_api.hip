@@ -511,9 +511,8 @@ static apt_status run_binning(const apt_cloud* cl, apt_query q, const PlanParams
         cm.bcnt = w.V[1];
         cm.trank = w.K[1];
         cm.brank = w.KB[1];
-        cm.n_keys_max = pp.key_cap;
         hipLaunchKernelGGL(k_compact<true>, dim3(G), dim3(kBlock), 0, st, cm);
-        CountSortArgs cs{w.plan, pp.key_cap, {w.V[0], w.V[1]}, {w.rs_counts, w.rs_counts + kCsTiles},
+        CountSortArgs cs{w.plan, {w.V[0], w.V[1]}, {w.rs_counts, w.rs_counts + kCsTiles},
                          {occ ? w.strag_count + 1 : nullptr, occ ? w.strag_count + 2 : nullptr},
                          w.tid, cm.tkeys, w.K[1], cl->xyz, w.t_rank, w.t_id, w.tx, w.ty, w.tz, w.t_cell_start,
                          w.KB[0], w.KB[1], w.brec2, w.bpos, w.cell_start};

@@ -125,6 +125,13 @@ __device__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t* tmp, uint32_t* to
     return r;
 }
 
+// The counting sort's keys of list q (0: targets, 1: neighbours): the targets'
+// in block-raster order, or cells.
+__device__ __forceinline__ uint32_t cs_keys(const GridPlan& P, int q) {
+    if (q == 1 || P.tblock == 1) return P.n_cells;
+    return (uint32_t)P.nbx * (uint32_t)P.nby * (((uint32_t)P.dim[2] + 7u) / 8u) * 512u;
+}
+
 __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
     __shared__ uint32_t tmp[64];
     __shared__ float s_box[6][16];
@@ -324,6 +331,17 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
             P.bits_T = P.bits;
         }
     }
+    // Counters of lists with many ions per key lie apart, as far as there are
+    // counters: atomics on one line of 32 run one after the other, about 16 ns each
+    // (980 000 targets over 5000 cells, 160 lines: k_compact 121 us; 16 places
+    // apart 72).  The scan takes the places between for keys without an ion.
+    for (int q = 0; q < 2; ++q) {
+        const uint32_t ions = q == 1 ? totB : totT;
+        uint64_t places = cs_keys(P, q);
+        uint32_t lg = 0;
+        for (; lg < 5 && 2u * places <= pp.key_cap && places < ions / 16u; ++lg) places *= 2u;
+        (q ? P.spread[1] : P.spread[0]) = lg;
+    }
     // (x - lo) * inv_h in FP32 misplaces a point by at most ~3 ulps of the
     // extent; cull with a margin well above that
     P.eps = (float)fmin(fmax(1e-5, 8.0 * 5.9604645e-8 * (emax + amax)), 3.0e38);
@@ -351,24 +369,6 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
 // ------------------------------------------------------------------------
 constexpr int kCompactItems = 16;
 constexpr int kCompactTile = kBlock * kCompactItems;
-
-// The counting sort's counters of list q (0: targets, 1: neighbours): one per
-// key (the targets' in block-raster order, or cells), 2^lg places apart;
-// *places of them in all, at most `cap`.  Atomics on one line of 32 counters
-// run one after the other, about 16 ns each, so the counters of lists with many
-// ions per key lie apart (980 000 targets over 5000 cells, 160 lines: k_compact
-// 121 us; 16 places apart 72).  The scan takes the places between for keys
-// without an ion.
-__device__ __forceinline__ uint32_t cs_spread(const GridPlan& P, int q, uint32_t cap, uint32_t* places) {
-    const uint32_t n = q == 1 || P.tblock == 1
-                           ? P.n_cells
-                           : (uint32_t)P.nbx * (uint32_t)P.nby * (((uint32_t)P.dim[2] + 7u) / 8u) * 512u;
-    const uint32_t ions = q == 1 ? P.nB : P.nT;
-    uint32_t lg = 0;
-    while (lg < 5 && ((uint64_t)n << (lg + 1)) <= cap && ions / 16u > (n << lg)) ++lg;
-    *places = n << lg;
-    return lg;
-}
 
 // The rank of an ion within its key (the counting sort), by an atomic on the
 // key's counter.  Ions without a finite position share the lowest cells, and
@@ -402,11 +402,7 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
                                               int64_t i0, int64_t i1) {
     const GridPlan P = *a.plan;
     const double sd = a.zscale ? *a.zscale : 1.0;
-    uint32_t lgt = 0, lgb = 0, places;
-    if (COUNT) {
-        lgt = cs_spread(P, 0, a.n_keys_max, &places);
-        lgb = cs_spread(P, 1, a.n_keys_max, &places);
-    }
+    const uint32_t lgt = COUNT ? P.spread[0] : 0u, lgb = COUNT ? P.spread[1] : 0u;
     constexpr int U = 4;   // list entries and positions in flight per thread
     // ion ids of list entries [j0, j0 + U * kBlock) of `list` (NULL: the
     // entries are the ions themselves), their positions, then f(j, id, x, y, z)
@@ -1080,9 +1076,7 @@ __device__ __forceinline__ void gather(const GatherArgs& a, uint32_t bid, uint32
 __global__ __launch_bounds__(kBlock) void k_cs_scan(CountSortArgs a) {
     const GridPlan P = *a.plan;
     const int q = a.tkeys ? blockIdx.y : 1;
-    uint32_t n;
-    (void)cs_spread(P, q, a.n_keys_max, &n);
-    const uint32_t base = blockIdx.x * (uint32_t)kCsTile;
+    const uint32_t n = cs_keys(P, q) << (q ? P.spread[1] : P.spread[0]), base = blockIdx.x * (uint32_t)kCsTile;
     if (base >= n) return;
     __shared__ uint32_t s_w[kWavesPerBlock], s_d[kWavesPerBlock];
     constexpr uint32_t per = kCsTile / kBlock;
@@ -1120,8 +1114,7 @@ __global__ __launch_bounds__(kBlock) void k_cs_scan(CountSortArgs a) {
 __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
     __shared__ uint32_t s_off[2][kCsTiles], s_w[2][kWavesPerBlock];
     const GridPlan P = *a.plan;
-    uint32_t nk[2];
-    const uint32_t lg[2] = {cs_spread(P, 0, a.n_keys_max, &nk[0]), cs_spread(P, 1, a.n_keys_max, &nk[1])};
+    const uint32_t nk[2] = {cs_keys(P, 0) << P.spread[0], cs_keys(P, 1) << P.spread[1]};
     {
         // where each tile starts: the sums of the tiles before it
         const int t = threadIdx.x, w = t / kWave;
@@ -1144,7 +1137,7 @@ __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
     auto start = [&](int q, uint32_t key) { return a.cnt[q][key] + s_off[q][key / kCsTile]; };
     const uint32_t first = blockIdx.x * kBlock + threadIdx.x, stride = gridDim.x * kBlock;
     for (uint32_t j = first; j < P.nB; j += stride) a.bpos[start(1, a.bkeys[j]) + a.brank[j]] = a.brec[j];
-    for (uint32_t c = first; c <= P.n_cells; c += stride) a.cell_start[c] = c < P.n_cells ? start(1, c << lg[1]) : P.nB;
+    for (uint32_t c = first; c <= P.n_cells; c += stride) a.cell_start[c] = c < P.n_cells ? start(1, c << P.spread[1]) : P.nB;
     if (!a.tkeys) return;
     for (uint32_t j = first; j < P.nT; j += stride) {
         const uint32_t id = a.tid[j], p = start(0, a.tkeys[j]) + a.trank[j];
@@ -1156,7 +1149,7 @@ __global__ __launch_bounds__(kBlock) void k_cs_place(CountSortArgs a) {
     }
     // (mode 3: the targets are in plain cell order)
     if (P.tile_mode == 3 && a.t_cell_start)
-        for (uint32_t c = first; c <= P.n_cells; c += stride) a.t_cell_start[c] = c < P.n_cells ? start(0, c << lg[0]) : P.nT;
+        for (uint32_t c = first; c <= P.n_cells; c += stride) a.t_cell_start[c] = c < P.n_cells ? start(0, c << P.spread[0]) : P.nT;
 }
 
 __global__ __launch_bounds__(kBlock) void k_gather(GatherArgs a) { gather(a, blockIdx.x, gridDim.x); }

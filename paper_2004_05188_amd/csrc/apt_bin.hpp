@@ -162,7 +162,6 @@ struct CompactArgs {
     uint32_t* bcnt = nullptr;
     uint32_t* trank = nullptr;
     uint32_t* brank = nullptr;
-    uint32_t n_keys_max = 0;   // counters per list
 };
 
 // Counting sort of clouds up to kCountSortMax ions: the compaction counts
@@ -184,7 +183,6 @@ static_assert(kCsTiles <= kBlock, "one thread per tile sum");
 
 struct CountSortArgs {
     const GridPlan* plan;
-    uint32_t n_keys_max;    // counters per list
     uint32_t* cnt[2];       // [targets, neighbours] counts, then exclusive prefixes within their tile
     uint32_t* sums[2];      // [kCsTiles] counts of each tile
     uint32_t* distinct[2];  // += keys with a count, or NULL

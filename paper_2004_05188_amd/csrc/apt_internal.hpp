@@ -33,6 +33,7 @@ struct GridPlan {
     uint32_t bits_T;    // bits of the largest target key
     int32_t tblock;     // targets are ordered by blocks of tblock^3 cells (8), or by cell (1)
     int32_t nbx, nby;   // blocks per axis (x, y)
+    uint32_t spread[2]; // counting sort: the counters of a list (targets, neighbours) lie 2^spread places apart
     float eps;          // culling margin covering FP32 cell-assignment error (nm)
     float r_all;        // a radius that reaches every cell from any point of the box
     float rk0;          // first kNN search radius
