@@ -197,6 +197,41 @@ def test_tiles_with_many_candidates(orc, blob):
         assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, 0, 1, 1.0, 2.0, 100))
 
 
+@pytest.mark.parametrize("kind", ["sc", "fcc", "bcc"])
+@pytest.mark.parametrize("k", [1, 4, 5, 8, 10, 12, 13, 16])
+def test_tiles_of_a_lattice(orc, kind, k):
+    """Exact lattices, where many neighbours share a distance: the tiles keep a few more than k by their leading bits,
+    find that the k-th may tie with one left out and leave the target to an exact search.  Every ion, and a random
+    tenth of the sites as neighbours; against the oracle."""
+    import torch
+
+    import paper_2004_05188_amd as aptstat
+
+    print(f"case lattice {kind} k={k}", flush=True)
+    basis = {"sc": [[0, 0, 0]], "fcc": [[0, 0, 0], [.5, .5, 0], [.5, 0, .5], [0, .5, .5]],
+             "bcc": [[0, 0, 0], [.5, .5, .5]]}[kind]
+    m = {"sc": 26, "fcc": 16, "bcc": 20}[kind]
+    cells = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
+    xyz = ((cells + np.array(basis)).reshape(-1, 3) * 0.5).astype(np.float32)
+    rng = np.random.default_rng(k)
+    xyz = xyz[rng.permutation(len(xyz))]
+    lab = (rng.random(len(xyz)) < 0.1).astype(np.uint8)
+    d = rng.random(len(xyz)).astype(np.float32)
+    cloud = aptstat.Cloud(*(torch.from_numpy(v).cuda() for v in (xyz, lab, d)))
+    for A, B, r_max in ((ANY, ANY, 0.6), (0, 1, 1.2)):
+        aptstat.set_tuning(tile_policy=2)
+        try:
+            g = aptstat.knn_rdf(cloud, A, B, 0.1, k, r_max=r_max, n_bins=60, kb_nbins=500)
+        finally:
+            aptstat.set_tuning()
+        t, dist, nid, h = orc.knn(xyz, lab, d, A, B, 0.1, k, kb_rmax=5.0, kb_nbins=500)
+        tid, gd, gn = (v.cpu().numpy() for v in g.trimmed())
+        assert np.array_equal(tid, t) and np.array_equal(gn, nid)
+        assert np.allclose(gd, dist, rtol=1e-6, atol=0)
+        assert np.array_equal(g.knn_hist.cpu().numpy().astype(np.uint64), h)
+        assert np.array_equal(g.rdf_hist.cpu().numpy().astype(np.uint64), orc.rdf(xyz, lab, d, A, B, 0.1, r_max, 60))
+
+
 @pytest.mark.parametrize("n,A,d_srf,n_bins,k", [
     (1 << 18, 1, 0.0, 200, 0), ((1 << 18) + 37, ANY, 0.0, 4000, 0),   # all targets; counters in LDS and global
     (2_000, ANY, 0.1, 200, 0), ((1 << 18) + 1, 1, 0.38, 200, 0), ((1 << 18) + 1, 1, 0.42, 200, 0),   # either side of three targets in five
