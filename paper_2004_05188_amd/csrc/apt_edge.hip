@@ -161,7 +161,6 @@ __global__ void k_edge_plan(EdgeArgs a) {
     // few roundings away from the exact value (of the ions' coordinates, and
     // of the triangles', which may lie farther out)
     T.slack = (float)(1e-5 * (amax + h) + 1e-6 + 1e-6 * (double)__uint_as_float(T.cmax_bits));
-    T.prb2 = isfinite(a.d_prb) ? (double)a.d_prb * (double)a.d_prb : INFINITY;
 }
 
 __device__ __forceinline__ float piece_rho(const TriPlan& T, int j) {
@@ -248,7 +247,6 @@ __global__ void k_edge_plan_pieces(EdgeArgs a) {
     int j = 0;
     while (j < kPieceSizes - 1 && T.pieces_at[j] > (unsigned long long)T.piece_cap) ++j;
     T.rho = piece_rho(T, j);
-    T.n_pieces = (uint32_t)T.pieces_at[j];
 }
 
 // The pieces of 64 triangles per wavefront, dealt to its lanes one by one
@@ -333,7 +331,8 @@ __global__ __launch_bounds__(kBlock) void k_edge_pieces(EdgeArgs a) {
     if (l == 0 && rmax > 0.0f) atomicMax(&a.tp->piece_rmax_bits, __float_as_uint(rmax));
 }
 
-// pieces in the workspace's arrays (as written, never more than they hold)
+// pieces in the workspace's arrays (k_edge_pieces cuts with the radius that
+// k_edge_measure counted them for, so that all fit: at most pieces_at of it)
 __device__ __forceinline__ uint32_t n_pieces(const TriPlan& T) {
     return T.piece_ctr < T.piece_cap ? T.piece_ctr : T.piece_cap;
 }

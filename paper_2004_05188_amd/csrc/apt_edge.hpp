@@ -26,7 +26,6 @@ struct TriPlan {
     unsigned long long pieces_at[kPieceSizes];   // pieces for each candidate piece radius
     uint32_t piece_ctr;          // pieces written so far
     uint32_t piece_rmax_bits;    // largest piece radius
-    uint32_t n_pieces;           // pieces planned
     uint32_t piece_cap;          // pieces the workspace holds
     float rho;                   // piece radius aimed at (triangles no larger are one piece)
     float lo[3];
@@ -35,7 +34,6 @@ struct TriPlan {
     uint32_t n_cells;
     float r_max;                 // largest triangle radius
     float slack;                 // bound on FP32 rounding of cells, centroids and pieces (nm)
-    double prb2;                 // d_prb^2 in FP64 (+inf: no probe limit)
 };
 
 struct EdgeArgs {
