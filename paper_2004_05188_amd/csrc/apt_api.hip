@@ -1342,8 +1342,10 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
     sa.uni = bwd ? 1 : 0;
     sa.n_bins = rb.n_bins;
     // (narrow windows need few buffered terms, so more wavefronts fit the LDS)
-    const bool table = rb.n_bins <= kSmoothTableBins;
-    sa.narrow = table && mw + 1.0 <= 32.0;
+    const bool small = mw + 1.0 <= 32.0, table = smooth_table(bwd, small, rb.n_bins);
+    if (!table) hipLaunchKernelGGL(k_smooth_edges, dim3(16), dim3(256), 0, st, w.plain.E2, rb.r_max, rb.n_bins);
+    sa.E = w.plain.E2;
+    sa.narrow = table && small;
     sa.n_terms = sa.narrow ? kWave : kSmoothTerms;
     sa.hcap = sa.narrow ? kWave : (int)fmin(64.0, floor((double)kSmoothTerms / (mw + 1.0)));
     sa.r_pre = r_pre;
@@ -1360,7 +1362,7 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
         if (W > kSmoothWaves) W = kSmoothWaves;
         sa.W = W;
         TraceSpan span("smooth", st);
-        const size_t lds = smooth_lds_bytes(true, rb.n_bins, sa.n_terms);
+        const size_t lds = smooth_lds_bytes(true, table, rb.n_bins, sa.n_terms);
         hipLaunchKernelGGL(table ? k_smooth_fwd<true> : k_smooth_fwd<false>, dim3(W), dim3(kWave), lds, st, sa);
         SmoothReduceArgs ra{w.plain.plan, w.part, W, rb.n_bins, h};
         hipLaunchKernelGGL(k_smooth_reduce, dim3((rb.n_bins + kReduceBins - 1) / kReduceBins),
@@ -1368,7 +1370,7 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
     } else {
         sa.W = kSmoothWaves;
         TraceSpan span("smooth", st);
-        const size_t lds = smooth_lds_bytes(false, rb.n_bins, sa.n_terms);
+        const size_t lds = smooth_lds_bytes(false, table, rb.n_bins, sa.n_terms);
         hipLaunchKernelGGL(table ? k_smooth_bwd<true> : k_smooth_bwd<false>, dim3(kSmoothWaves), dim3(kWave), lds, st,
                            sa);
         if (grad_s) {

@@ -28,15 +28,24 @@
 namespace apt {
 
 // Dynamic LDS of a workgroup: the terms of a flush, the buffered pairs and,
-// for up to kSmoothTableBins bins, the bin edges with (forward) two copies of
-// the histogram or (adjoint) dL/dh; beyond, one copy of the histogram.
-size_t smooth_lds_bytes(bool fwd, int n_bins, int n_terms) {
-    const bool table = n_bins <= kSmoothTableBins;
+// with the tables (smooth_table), the bin edges with (forward) two copies of
+// the histogram or (adjoint) dL/dh; without, one copy of the histogram.
+size_t smooth_lds_bytes(bool fwd, bool table, int n_bins, int n_terms) {
     size_t b = (size_t)n_terms * 8u + (size_t)kWave * (fwd ? 8u : 5u * 8u + 4u);
     if (fwd) b += (size_t)n_bins * (table ? 16u : 8u);
     else if (table) b += (size_t)n_bins * 8u;
     if (table) b += ((size_t)n_bins + 1u) * 8u;
     return b;
+}
+
+// Edge b of the bins, in FP64.
+__device__ __forceinline__ double smooth_edge(double r_max, int n_bins, int b) {
+    return ((double)b * r_max) / (double)n_bins;
+}
+
+__global__ void k_smooth_edges(double* E, float r_max, int n_bins) {
+    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b <= n_bins; b += gridDim.x * blockDim.x)
+        E[b] = smooth_edge((double)r_max, n_bins, b);
 }
 
 __global__ void k_fill_f32(float* p, int64_t n) {
@@ -72,11 +81,6 @@ __device__ __forceinline__ double smooth_tail(double t) {
     const double h = 0.5 * t, z = h * t, ze = fma(h, t, -z);
     const double e = 0.5 * exp(-z) * (p / fma(2.0, x, 1.0));
     return fma(-e, ze, e);
-}
-
-// Edge b of the bins, in FP64.
-__device__ __forceinline__ double smooth_edge(const SmoothArgs& a, int b) {
-    return ((double)b * a.r_max) / (double)a.n_bins;
 }
 
 // Bins [b0, b1] that meet (D - 6 sigma, D + 6 sigma); D < r_max + 6 sigma
@@ -136,7 +140,7 @@ __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
     // forward: histogram, [2][n_bins] with TABLE; adjoint with TABLE: dL/dh
     double* s_hist = BWD ? reinterpret_cast<double*>(s_mul + kWave) : s_D + kWave;
     double* s_E = s_hist + (size_t)a.n_bins * (PAIRS2 ? 2 : 1);
-    auto edge = [&](int b) { return TABLE ? s_E[b] : smooth_edge(a, b); };
+    auto edge = [&](int b) { return TABLE ? s_E[b] : a.E[b]; };
 
     const GridPlan P = *a.plan;
     const int l = lane_id();
@@ -147,7 +151,7 @@ __device__ __forceinline__ void smooth_body(const SmoothArgs& a) {
     if (!BWD)
         for (int b = l; b < a.n_bins * (PAIRS2 ? 2 : 1); b += kWave) s_hist[b] = 0.0;
     if (TABLE) {
-        for (int b = l; b <= a.n_bins; b += kWave) s_E[b] = smooth_edge(a, b);
+        for (int b = l; b <= a.n_bins; b += kWave) s_E[b] = smooth_edge(a.r_max, a.n_bins, b);
         if (BWD)
             for (int b = l; b < a.n_bins; b += kWave) s_hist[b] = a.grad_h[b];
     }

@@ -13,7 +13,18 @@ constexpr int kSmoothTerms = 1024;     // window edge values buffered per wavefr
 constexpr int kSmoothMaxBins = 4096;   // forward histogram held in LDS
 constexpr int kSmoothWaves = 8192;     // wavefronts of the launch (forward: at most this many)
 constexpr int kReduceBins = 4, kReduceGroups = 256;   // bins and row ranges of a workgroup of the fixed-order reduction
-constexpr int kSmoothTableBins = 1024; // bins whose edges and second histogram are held in LDS
+
+// Whether the bin edges (with, forward, a second histogram, adjoint, dL/dh) are
+// held in LDS.  They save memory reads, and narrow windows (at most 32 edges) go
+// two at a time through them, but their LDS, up to 33 KB per wavefront, leaves
+// few wavefronts on a CU.  Calls without / with them, 2e6 ions, 2 % of them
+// solute, r_max 1 nm, in us.  Forward, windows of 28 bins: 600 bins 233 / 211,
+// 800 246 / 234, 1000 228 / 259; of 120: 200 bins 265 / 265, 300 278 / 290, 1000
+// 322 / 478.  Adjoint, of 28: 400 bins 234 / 188, 600 229 / 219, 800 235 / 241; of 60
+// to 120: 60 bins 292 / 296, 100 286 / 300, 1000 289 / 437.
+inline bool smooth_table(bool bwd, bool narrow, int n_bins) {
+    return n_bins <= (bwd ? (narrow ? 600 : 64) : (narrow ? 800 : 200));
+}
 
 struct SmoothArgs {
     const GridPlan* plan;
@@ -36,6 +47,7 @@ struct SmoothArgs {
     double w6;                   // 6 sigma
     double inv_width;            // n_bins / r_max
     double r_max;                // edge b of the bins: (b * r_max) / n_bins
+    const double* E;             // the edges in memory, where they are not in LDS
     int32_t narrow;              // no window has more than 32 edges: a half-wavefront per pair
     int32_t n_terms;             // terms a flush holds (at most kSmoothTerms)
     const double* grad_h;        // adjoint: dL/dh [n_bins]
@@ -56,7 +68,8 @@ __global__ void k_smooth_fwd(SmoothArgs a);
 template <bool TABLE>
 __global__ void k_smooth_bwd(SmoothArgs a);
 __global__ void k_smooth_reduce(SmoothReduceArgs a);
+__global__ void k_smooth_edges(double* E, float r_max, int n_bins);
 __global__ void k_fill_f32(float* p, int64_t n);
-size_t smooth_lds_bytes(bool fwd, int n_bins, int n_terms);
+size_t smooth_lds_bytes(bool fwd, bool table, int n_bins, int n_terms);
 
 }  // namespace apt

@@ -119,6 +119,28 @@ def test_windows_and_tables_at_their_limits(gpu, orc, synth, n_bins, sigma):
     assert abs(gs - ogs) <= 1e-9 * abs(ogs)
 
 
+# bin counts on both sides of those up to which forward and adjoint hold their tables in LDS, with narrow and with wide
+# windows, and of those whose rows are summed 4 and 64 bins to a workgroup
+@pytest.mark.parametrize("n_bins,edges", [(64, 60), (65, 60), (200, 90), (201, 90), (600, 28), (601, 28), (800, 28),
+                                          (801, 28), (1024, 100), (1025, 100), (4096, 900)])
+def test_bin_counts_at_the_limits_of_the_tables(gpu, orc, synth, n_bins, edges):
+    sigma = (edges - 4) * 1.5 / n_bins / 12.0
+    _say(f"smooth tables n_bins={n_bins} sigma={sigma}")
+    xyz, lab, d = _box(synth, 20_000, 9.0, 22)
+    cloud = _cloud(gpu, xyz, lab, d)
+    args = (SC, SC, 0.5, 1.5, n_bins, sigma)
+    h, st = gpu_fwd(gpu, cloud, *args, 1.02)
+    assert st == 0
+    # (bins below 1e-12 of the largest: sums of far tails, which the two sides cut at slightly different edges)
+    ref = orc.smooth_fwd(xyz, lab, d, *args, 1.02)
+    assert np.all(np.abs(h - ref) <= 1e-12 * (np.abs(ref) + 1e-3 * ref.max()))
+    gh = np.cos(np.arange(n_bins))
+    g, gs = gpu_bwd(gpu, cloud, *args, gh, 1.02)
+    rg, rgs = orc.smooth_bwd(xyz, lab, d, *args, 1.02, gh)
+    assert_grad_close(g, rg)
+    assert abs(gs - rgs) <= 1e-9 * max(abs(rgs), 1e-3 * np.abs(rg).sum())
+
+
 @pytest.mark.parametrize("s", [1.0, 1.05])
 @pytest.mark.parametrize("prob", PROBLEMS, ids=[p[0] for p in PROBLEMS])
 def test_smooth_forward_and_adjoint_match_oracle(gpu, orc, synth, prob, s):
