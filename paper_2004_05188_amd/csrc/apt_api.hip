@@ -1365,8 +1365,8 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
         const size_t lds = smooth_lds_bytes(true, table, rb.n_bins, sa.n_terms);
         hipLaunchKernelGGL(table ? k_smooth_fwd<true> : k_smooth_fwd<false>, dim3(W), dim3(kWave), lds, st, sa);
         SmoothReduceArgs ra{w.plain.plan, w.part, W, rb.n_bins, h};
-        hipLaunchKernelGGL(k_smooth_reduce, dim3((rb.n_bins + kReduceBins - 1) / kReduceBins),
-                           dim3(kReduceBins * kReduceGroups), 0, st, ra);
+        if (rb.n_bins > 1024) hipLaunchKernelGGL(k_smooth_reduce<64>, dim3((rb.n_bins + 63) / 64), dim3(kReduceBlock), 0, st, ra);
+        else hipLaunchKernelGGL(k_smooth_reduce<4>, dim3((rb.n_bins + 3) / 4), dim3(kReduceBlock), 0, st, ra);
     } else {
         sa.W = kSmoothWaves;
         TraceSpan span("smooth", st);
@@ -1375,7 +1375,7 @@ static apt_status run_smooth(bool bwd, const apt_cloud* cl, apt_query q, apt_bin
                            sa);
         if (grad_s) {
             SmoothReduceArgs ra{w.plain.plan, w.part, kSmoothWaves, 1, grad_s};
-            hipLaunchKernelGGL(k_smooth_reduce, dim3(1), dim3(kReduceBins * kReduceGroups), 0, st, ra);
+            hipLaunchKernelGGL(k_smooth_reduce<4>, dim3(1), dim3(kReduceBlock), 0, st, ra);
         }
     }
     return hip_check("smoothed RDF launch");

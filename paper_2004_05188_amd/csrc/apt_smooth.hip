@@ -395,9 +395,13 @@ template __global__ void k_smooth_bwd<true>(SmoothArgs);
 // out[b] = sum over the first min(W, nT) per-wavefront rows of part[w][b], in
 // a fixed order (the same result on every run): kReduceGroups consecutive row
 // ranges, each summed in row order, then the range sums pairwise.  Workgroup:
-// kReduceBins bins x kReduceGroups ranges, so that 200 bins fill 50 workgroups
-// of 256 ranges each (64 bins x 16 ranges were four, 62 us).
-__global__ __launch_bounds__(kReduceBins * kReduceGroups) void k_smooth_reduce(SmoothReduceArgs a) {
+// BINS bins x as many ranges as make kReduceBlock threads.  Few bins: 4, so that
+// 200 of them fill 50 workgroups of 256 ranges each (64 bins x 16 ranges were four,
+// 62 us); many, whose rows are few: 64, a row's as a whole line (4000 bins, 524
+// rows: 7.0 us, 4 bins a workgroup 14.0).
+template <int BINS>
+__global__ __launch_bounds__(kReduceBlock) void k_smooth_reduce(SmoothReduceArgs a) {
+    constexpr int kReduceBins = BINS, kReduceGroups = kReduceBlock / BINS;
     __shared__ double s_p[kReduceGroups][kReduceBins];
     const int tb = threadIdx.x % kReduceBins, g = threadIdx.x / kReduceBins;
     const int b = blockIdx.x * kReduceBins + tb;
@@ -424,5 +428,8 @@ __global__ __launch_bounds__(kReduceBins * kReduceGroups) void k_smooth_reduce(S
     }
     if (g == 0 && b < a.n_bins) a.out[b] = s_p[0][tb];
 }
+
+template __global__ void k_smooth_reduce<4>(SmoothReduceArgs);
+template __global__ void k_smooth_reduce<64>(SmoothReduceArgs);
 
 }  // namespace apt

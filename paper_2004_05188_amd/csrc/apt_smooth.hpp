@@ -12,7 +12,7 @@ namespace apt {
 constexpr int kSmoothTerms = 1024;     // window edge values buffered per wavefront
 constexpr int kSmoothMaxBins = 4096;   // forward histogram held in LDS
 constexpr int kSmoothWaves = 8192;     // wavefronts of the launch (forward: at most this many)
-constexpr int kReduceBins = 4, kReduceGroups = 256;   // bins and row ranges of a workgroup of the fixed-order reduction
+constexpr int kReduceBlock = 1024;     // threads of a workgroup of the fixed-order reduction
 
 // Whether the bin edges (with, forward, a second histogram, adjoint, dL/dh) are
 // held in LDS.  They save memory reads, and narrow windows (at most 32 edges) go
@@ -67,7 +67,8 @@ template <bool TABLE>
 __global__ void k_smooth_fwd(SmoothArgs a);
 template <bool TABLE>
 __global__ void k_smooth_bwd(SmoothArgs a);
-__global__ void k_smooth_reduce(SmoothReduceArgs a);
+template <int BINS>
+__global__ void k_smooth_reduce(SmoothReduceArgs a);   // BINS bins a workgroup
 __global__ void k_smooth_edges(double* E, float r_max, int n_bins);
 __global__ void k_fill_f32(float* p, int64_t n);
 size_t smooth_lds_bytes(bool fwd, bool table, int n_bins, int n_terms);
