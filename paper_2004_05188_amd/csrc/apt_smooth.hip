@@ -58,6 +58,7 @@ __global__ void k_fill_f32(float* p, int64_t n) {
 // y in [-1, 1] in 80-digit arithmetic (its next coefficients are below 1e-16),
 // after M. M. Shepherd and J. G. Laframboise, Math. Comp. 36 (1981) 249.
 constexpr int kTailTerms = 23;
+static_assert(kTailTerms % 2 == 1, "pairs of an odd and an even power beside the constant");
 __device__ constexpr double kTail[kTailTerms] = {
     1.2375126308378275, -0.14024059858554525, 0.0035854154854790257, 0.08227673848999506,
     -0.10880393014244462, 0.09230432116428125, -0.05869339857664934, 0.028362277372111139,
@@ -75,11 +76,22 @@ __device__ constexpr double kTail[kTailTerms] = {
 __device__ __forceinline__ double smooth_tail(double t) {
     const double x = fabs(t) * M_SQRT1_2;
     const double y = (x - 3.75) / (x + 3.75);
-    double p = kTail[kTailTerms - 1];
+    // (even and odd powers in chains of their own, half as long as one; the
+    // constant term, the largest, comes last, so that their roundings are a
+    // tenth of its)
+    const double y2 = y * y;
+    double odd = kTail[kTailTerms - 2], even = kTail[kTailTerms - 1];
 #pragma unroll
-    for (int q = kTailTerms - 2; q >= 0; --q) p = fma(p, y, kTail[q]);
+    for (int q = kTailTerms - 4; q >= 1; q -= 2) {
+        odd = fma(odd, y2, kTail[q]);
+        even = fma(even, y2, kTail[q + 1]);
+    }
+    const double p = fma(fma(even, y, odd), y, kTail[0]);
     const double h = 0.5 * t, z = h * t, ze = fma(h, t, -z);
-    const double e = 0.5 * exp(-z) * (p / fma(2.0, x, 1.0));
+    // (p over its factor, by the reciprocal that does not wait for p and a
+    // correction of the quotient)
+    const double d = fma(2.0, x, 1.0), r = 1.0 / d, q0 = p * r, q = fma(fma(-q0, d, p), r, q0);
+    const double e = 0.5 * exp(-z) * q;
     return fma(-e, ze, e);
 }
 
