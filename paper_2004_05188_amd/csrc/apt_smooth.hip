@@ -68,7 +68,7 @@ __device__ constexpr double kTail[kTailTerms] = {
     3.1979266716668042e-08, -1.9551358868985616e-09, -2.6231073471334759e-09};
 
 // The tail of the normal distribution beyond |t|: 0.5 erfc(|t| / sqrt 2),
-// within about 5e-16 of its value for all t (exp(-t^2/2) takes the rounding of
+// within 7e-16 of its value for all t (exp(-t^2/2) takes the rounding of
 // t^2/2 into account).  One path for all lanes, about 80 FP64 instructions;
 // erfc() has several, and the lanes of a wavefront, at the edges of one
 // pair's window, took all of them; through |t| / sqrt 2 it was off by up to
