@@ -335,13 +335,15 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
     // counters: atomics on one line of 32 run one after the other, about 16 ns each
     // (980 000 targets over 5000 cells, 160 lines: k_compact 121 us; 16 places
     // apart 72).  The scan takes the places between for keys without an ion.
-    for (int q = 0; q < 2; ++q) {
-        const uint32_t ions = q == 1 ? totB : totT;
-        uint64_t places = cs_keys(P, q);
-        uint32_t lg = 0;
-        for (; lg < 5 && 2u * places <= pp.key_cap && places < ions / 16u; ++lg) places *= 2u;
-        (q ? P.spread[1] : P.spread[0]) = lg;
-    }
+    // (To about 16 ions per counter: the difference of the leading bits.)
+    auto spread = [&](uint32_t keys, uint32_t ions) {
+        if (ions / 16u <= keys) return 0u;
+        uint32_t lg = min((uint32_t)(__clz(keys) - __clz(ions / 16u)), 5u);
+        while (lg > 0u && ((uint64_t)keys << lg) > pp.key_cap) --lg;
+        return lg;
+    };
+    P.spread[0] = spread(cs_keys(P, 0), totT);
+    P.spread[1] = spread(P.n_cells, totB);
     // (x - lo) * inv_h in FP32 misplaces a point by at most ~3 ulps of the
     // extent; cull with a margin well above that
     P.eps = (float)fmin(fmax(1e-5, 8.0 * 5.9604645e-8 * (emax + amax)), 3.0e38);
@@ -375,6 +377,7 @@ constexpr int kCompactTile = kBlock * kCompactItems;
 // their atomics would run one after the other: those of a wavefront that meet on
 // a counter are one (every second of 2e5 ions without one, every ion as a
 // neighbour: the call 1205 us, now 109; radix sort 154).
+// (`finite` may be false for others too: it only says which may share.)
 __device__ __forceinline__ uint32_t cs_rank(uint32_t* cnt, uint32_t place, bool finite) {
     const uint64_t odd = __ballot(!finite);
     if (odd) {
@@ -436,7 +439,7 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
     auto tput = [&](uint32_t j, uint32_t, float x, float y, float z) {
         const uint32_t key = target_key(P, x, y, z) << lgt;
         a.tkeys[j] = key;
-        if (COUNT) a.trank[j] = cs_rank(a.tcnt, key, isfinite(x) && isfinite(y) && isfinite(z));
+        if (COUNT) a.trank[j] = cs_rank(a.tcnt, key, isfinite(x + y + z));
         else a.tvals[j] = j;
     };
     if (!COUNT || a.tkeys) run(a.tid, t0, t1, tput);
@@ -444,7 +447,7 @@ __device__ __forceinline__ void compact_keys(const CompactArgs& a, uint32_t t0, 
     auto bkey = [&](uint32_t j, uint32_t id, float x, float y, float z) {
         const uint32_t key = cell_id(P, x, y, z) << lgb;
         a.bkeys[j] = key;
-        if (COUNT) a.brank[j] = cs_rank(a.bcnt, key, isfinite(x) && isfinite(y) && isfinite(z));
+        if (COUNT) a.brank[j] = cs_rank(a.bcnt, key, isfinite(x + y + z));
         brec[j] = make_float4(x, y, z, __builtin_bit_cast(float, id));
     };
     if (a.bsel) run(a.bsel, b0, b1, bkey);
