@@ -160,7 +160,11 @@ __global__ void k_edge_plan(EdgeArgs a) {
     // cell indices, centroids and piece vertices are FP32: each may sit a
     // few roundings away from the exact value (of the ions' coordinates, and
     // of the triangles', which may lie farther out)
-    T.slack = (float)(1e-5 * (amax + h) + 1e-6 + 1e-6 * (double)__uint_as_float(T.cmax_bits));
+    const double cmax = (double)__uint_as_float(T.cmax_bits);
+    T.slack = (float)(1e-5 * (amax + h) + 1e-6 + 1e-6 * cmax);
+    // (FP32 squared distances between such coordinates may overflow: no bound
+    // excludes a piece)
+    if (!(fmax(amax, cmax) < 5e18)) T.slack = INFINITY;
 }
 
 __device__ __forceinline__ float piece_rho(const TriPlan& T, int j) {
@@ -480,8 +484,8 @@ __device__ __forceinline__ bool edge_rows(const TriPlan& T, const uint32_t* __re
             const int cz = cz0 + r / ny, cy = cy0 + r % ny;
             const float gy = axis_gap(T, 1, y0, y1, cy), gz = axis_gap(T, 2, z0, z1, cz);
             const float rest = S * S - (gy * gy + gz * gz);
-            if (rest >= 0.0f) {
-                const float ex = sqrtf(rest);
+            if (!(rest < 0.0f)) {
+                const float ex = rest < INFINITY ? sqrtf(rest) : INFINITY;   // (squares that overflowed: the whole row)
                 const uint32_t row = ((uint32_t)cz * (uint32_t)T.dim[1] + (uint32_t)cy) * (uint32_t)T.dim[0];
                 st = tstart[row + (uint32_t)edge_axis(T, 0, x0 - ex)];
                 len = tstart[row + (uint32_t)edge_axis(T, 0, x1 + ex) + 1u] - st;
@@ -583,7 +587,7 @@ __global__ __launch_bounds__(kWave, 4) void k_edge_dist(EdgeArgs a) {
                                              [&](bool ok, uint32_t k) {
                                                  const float4 c = a.tsorted[k];
                                                  const float dx = c.x - cx, dy = c.y - cy, dz = c.z - cz;
-                                                 if (ok) near2 = fminf(near2, dx * dx + dy * dy + dz * dz);
+                                                 if (ok) near2 = fminf(near2, fminf(dx * dx + dy * dy + dz * dz, 3e38f));
                                              });
                 near2 = wave_min_f(near2);
                 return whole;
@@ -688,7 +692,7 @@ __global__ __launch_bounds__(kWave, 4) void k_edge_dist(EdgeArgs a) {
                                     const float4 c = a.tsorted[k];
                                     const float dx = c.x - cx, dy = c.y - cy, dz = c.z - cz;
                                     const float lb = sqrtf(dx * dx + dy * dy + dz * dz) * 0.99999f - c.w - T.slack - hd;
-                                    const bool keep = ok && lb <= B;
+                                    const bool keep = ok && !(lb > B);
                                     const uint64_t m = __ballot(keep);
                                     if (keep) {
                                         const uint32_t t = a.torder[k];

@@ -205,3 +205,19 @@ def test_tuned_cells(gpu, orc, needle, cell_occ):
         check(orc, gpu, xyz[:20_000], mesh, 1.5)
     finally:
         gpu[0].set_tuning()
+
+
+@pytest.mark.parametrize("d_prb", [0.4, float("inf")])
+@pytest.mark.parametrize("scale", [1e-3, 1e15, 3e17, 1e18, 3e19, 1e30])
+def test_coordinates_whose_squares_overflow(gpu, orc, scale, d_prb):
+    """Ions and triangles of any finite size (FP32 squares overflow from 1.8e19): both large, or one triangle among
+    others, and alone."""
+    _say(f"case edge scale={scale} d_prb={d_prb}")
+    rng = np.random.default_rng(8)
+    xyz = rng.random((400, 3))
+    tri = rng.random((60, 1, 3)) * 1.4 - 0.2 + 0.1 * rng.standard_normal((60, 3, 3))
+    far = np.array([[0.3, 0.4, 0.5], [0.35, 0.4, 0.5], [0.3, 0.5, 0.55]])[None] * scale
+    for ions, t, unit in ((xyz * scale, tri * scale, scale), (xyz, far, scale), (xyz, np.concatenate([tri, far]), 1.0)):
+        reach = float(np.float32(d_prb * unit))
+        g, _ = check(orc, gpu, ions.astype(np.float32), t.astype(np.float32), reach, method="brute")
+        assert np.isfinite(reach) or np.isfinite(g).all()
